@@ -29,6 +29,10 @@ constexpr int TILE_WORDS = TILE / 32;
 // Per stored tile: FP64 row sums [0, TILE), column sums of rows 0..63 [TILE, 2 TILE) and of
 // rows 64..127 [2 TILE, 3 TILE); two tile-max slots (one per row half).
 constexpr int TSUM_STRIDE = 3 * TILE;
+// FP64 form, whose workgroups cover 32 x 64 parts of a tile: row sums of each 64-column half
+// [0, 2 TILE), column sums of each 32-row quarter [2 TILE, 6 TILE).  Cross tests: row sums
+// over the x2 columns of each half [0, 2 TILE), over the y2 columns [2 TILE, 4 TILE).
+constexpr int TSUM_STRIDE_F64 = 6 * TILE;
 constexpr int TMAX_PER_TILE = 2;
 constexpr int NP = 256;              // split columns per resampling chunk
 constexpr int MAX_CC = 8;            // chunks per resampling workgroup, at most
@@ -125,6 +129,7 @@ struct TestDesc {
   void* nrm;
   void* D;
   double* tsum;
+  int64_t tsum_stride;  // doubles between the sums of successive tiles
   float* tmax;       // [ntiles][2] largest |entry| of each row half of each stored tile
   double* rsum;
   double* obs;       // [0..2] S_XX, S_YY, S_XY; [3] observed statistic; [4] R;

@@ -56,16 +56,23 @@ __global__ void __launch_bounds__(CF_THREADS) k_cross_final(const TestDesc* __re
   const TestDesc d = descs[0];
   const int64_t n_side = d.nx;  // x-side rows: x1 then y1
   const int64_t nx1 = d.cnx1, ny1 = d.cny1, nx2 = d.cnx2, ny2 = (int64_t)d.ny - d.cnx2;
-  const bool ed = d.kind == KIND_ED;
+  const bool ed = d.kind == KIND_ED, f64 = d.prec == PREC_F64;
   double* v = d.rsum;  // v(a) of every x-side row
   Csum sx, sy;
   for (int64_t a = threadIdx.x; a < n_side; a += CF_THREADS) {
     const int64_t i = a / TILE, r = a % TILE;
     Csum s2, s3;
     for (int jc = 0; jc < d.ty; ++jc) {
-      const double* ts = d.tsum + (i * d.ty + jc) * TSUM_STRIDE;
-      s2.add(ts[r]);
-      s3.add(ts[TILE + r]);
+      const double* ts = d.tsum + (i * d.ty + jc) * d.tsum_stride;
+      if (f64) {  // two column halves each
+        s2.add(ts[r]);
+        s2.add(ts[TILE + r]);
+        s3.add(ts[2 * TILE + r]);
+        s3.add(ts[3 * TILE + r]);
+      } else {
+        s2.add(ts[r]);
+        s3.add(ts[TILE + r]);
+      }
     }
     const double m2 = s2.value() / (double)nx2, m3 = s3.value() / (double)ny2;
     const double val = ed ? m3 - m2 : m2 - m3;

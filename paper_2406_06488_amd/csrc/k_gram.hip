@@ -85,7 +85,7 @@ __device__ inline BlockOut own_out(const TestDesc& d, const TileCtx& c) {
   const int64_t t = c.t;
   return BlockOut{d.kind, d.cross ? cross_split(d, c.j) : -1, d.gamma,
                   d.cross ? nullptr : (float*)d.D + t * TILE * TILE,
-                  d.tsum + t * TSUM_STRIDE, d.tmax + t * TMAX_PER_TILE};
+                  d.tsum + t * d.tsum_stride, d.tmax + t * TMAX_PER_TILE};
 }
 __device__ inline BlockOut partner_out(const TestDesc& d, const TileCtx& c) {
   const int64_t t = c.t;
@@ -893,93 +893,195 @@ k_gram_finish(const TestDesc* __restrict__ descs,
 }
 
 // ---------------------------------------------------------------- FP64 direct
-// Alg. 3 literally: sum over k of (x_ak - y_bk)^2 on the FP64 vector ALU.
-// Thread (tr, tc) owns rows tr + 16 a and columns tc + 16 b (a, b < 8).
-constexpr int KC64 = 16;
-__global__ void __launch_bounds__(256) k_dist_f64(const TestDesc* __restrict__ descs,
-                                                  const int64_t* __restrict__ offs, int ntests) {
-  __shared__ double As[TILE * (KC64 + 1)];
-  __shared__ double Bs[TILE * (KC64 + 1)];
-  __shared__ double rp[TILE * 16];
-  __shared__ double cp[16 * TILE];
-  const int ti = find_test(offs, ntests, blockIdx.x);
-  const TestDesc d = descs[ti];
-  const TileCtx c = tile_ctx(d, blockIdx.x - offs[ti]);
-  const double* Wa = (const double*)d.W + (int64_t)c.i * TILE * d.p_pad;
-  const double* Wb = (const double*)d.W + (int64_t)c.j * TILE * d.p_pad;
-  const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-  double acc[8][8];
-  for (int a = 0; a < 8; ++a)
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
-  for (int k0 = 0; k0 < d.p_pad; k0 += KC64) {
-    __syncthreads();
-    for (int e = tid; e < TILE * KC64; e += 256) {
-      const int row = e / KC64, k = e % KC64;
-      As[row * (KC64 + 1) + k] = Wa[(int64_t)row * d.p_pad + k0 + k];
-      Bs[row * (KC64 + 1) + k] = Wb[(int64_t)row * d.p_pad + k0 + k];
+// Alg. 3 literally: sum over k of (x_ak - y_bk)^2 on the FP64 vector ALU, two instructions
+// per pair and coordinate.  A workgroup computes 32 rows x 64 columns of a stored tile and
+// its eight waves take an eighth of the coordinates each (4 of every 32), so that even the
+// four tiles of a 200 + 200 test spread over 32 CUs with two waves on every SIMD; the eight
+// partial sums are added in a fixed order at the end.  A lane holds 4 x 8 entries: per
+// coordinate 12 8-byte LDS reads feed 64 FP64 instructions, which keeps the LDS below the
+// vector ALU's time.  Rounds of 32 coordinates go straight into a ring of three LDS buffers
+// (global_load_lds), two rounds ahead; the 16 pieces (two coordinates) of a staged row are
+// stored at slot piece ^ (row % 8), so that the 8 rows of a fragment read lie in distinct
+// banks.  Measured against one 128 x 128 tile per workgroup: 200 + 200 x 1000 (cross test,
+// 4 tiles) 639 -> 48 us, latency-bound before and after; 1000 + 1000 x 500 303 -> 116 us (52
+// us of vector-ALU time); four waves instead of eight took 59 and 107 us.
+constexpr int DF_THREADS = 512;
+constexpr int DF_ROWS = 32, DF_COLS = 64;      // entries of one workgroup
+constexpr int DF_K = 32;                       // coordinates per round (4 per wave)
+constexpr int DF_NBUF = 3;
+constexpr int DF_BUF = (DF_ROWS + DF_COLS) * DF_K;  // doubles per buffer
+constexpr int DF_PARTS = (TILE / DF_ROWS) * (TILE / DF_COLS);
+
+// Block values, stored entries and sums of the rows lr + 8 w of a 32 x 64 part: v[b] is the
+// squared distance of entry (r0 + lr + 8 w, c0 + lc + 8 b).  Column sums of the wave's 8
+// rows go to cs[w].  Cross tests keep the row sums over the x2 columns and over the y2
+// columns apart and store no tile.
+__device__ inline void dist_emit_f64(const TestDesc& d, const TileCtx& c, int r0, int c0, int w,
+                                     int lane, const double (&v)[8], double (*cs)[64]) {
+  const int lr = lane >> 3, lc = lane & 7, ch = c0 / 64;
+  const int split = d.cross ? cross_split(d, c.j) : -1;
+  const int r = r0 + 8 * w + lr;
+  double s0 = 0.0, s1 = 0.0, col[8];
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const int cc = c0 + lc + 8 * b;
+    double x;
+    if (r >= c.rows_i || cc >= c.rows_j) x = 0.0;
+    else if (c.diag && r == cc) x = d.kind == KIND_ED ? 0.0 : 1.0;
+    else x = d.kind == KIND_ED ? sqrt(v[b]) : exp(-d.gamma * v[b]);
+    if (split < 0) ((double*)d.D)[(int64_t)c.t * TILE * TILE + r * TILE + cc] = x;
+    if (split >= 0 && cc >= split) s1 += x;
+    else s0 += x;
+    col[b] = x;
+  }
+#pragma unroll
+  for (int m = 1; m < 8; m <<= 1) {  // over the row's 8 lanes
+    s0 += __shfl_xor(s0, m, 64);
+    s1 += __shfl_xor(s1, m, 64);
+  }
+  double* ts = d.tsum + (int64_t)c.t * d.tsum_stride;
+  if (lc == 0) {
+    ts[ch * TILE + r] = s0;
+    if (split >= 0) ts[(2 + ch) * TILE + r] = s1;
+  }
+  if (split >= 0) return;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {  // over the wave's 8 rows
+#pragma unroll
+    for (int m = 8; m < 64; m <<= 1) col[b] += __shfl_xor(col[b], m, 64);
+    if (lr == 0) cs[w][lc + 8 * b] = col[b];
+  }
+}
+
+__device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int part, double* sm) {
+  constexpr int NLD = DF_BUF * 8 / 1024 / (DF_THREADS / 64);  // kilobyte loads per wave
+  const int rq = part >> 1, ch = part & 1;
+  const int r0 = rq * DF_ROWS, c0 = ch * DF_COLS;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int lr = lane >> 3, lc = lane & 7;  // entries (lr + 8 a, lc + 8 b), a < 4, b < 8
+  const double* Wa = (const double*)d.W + ((int64_t)c.i * TILE + r0) * d.p_pad;
+  const double* Wb = (const double*)d.W + ((int64_t)c.j * TILE + c0) * d.p_pad;
+  // a part that holds only padding has no coordinates to add (its entries are 0)
+  const int nk = r0 < c.rows_i && c0 < c.rows_j ? d.p_pad : 0;
+  // Load f = NLD w + q of a round moves staged rows 4 f .. + 3 (the 32 rows, then the 64
+  // columns); this lane fills slot lane % 16 of row 4 f + lane / 16.
+  const int row4 = lane >> 4;
+  const int pk0 = 2 * ((lane & 15) ^ row4), pk1 = 2 * ((lane & 15) ^ (4 + row4));  // f even, odd
+  auto issue = [&](int round) {
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) {
+      const int f = NLD * w + q;
+      const double* src = 4 * f < DF_ROWS ? Wa + (int64_t)4 * f * d.p_pad
+                                          : Wb + (int64_t)(4 * f - DF_ROWS) * d.p_pad;
+      // pieces past the row's end (never multiplied) read its last piece instead
+      const int k = min(round * DF_K + ((f & 1) ? pk1 : pk0), nk - 2);
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(src + (uint32_t)(row4 * d.p_pad + k)),
+          (__attribute__((address_space(3))) void*)(sm + (round % DF_NBUF) * DF_BUF + f * 128),
+          16, 0, 0);
     }
-    __syncthreads();
-    for (int k = 0; k < KC64; ++k) {
-      double av[8], bv[8];
-      for (int a = 0; a < 8; ++a) av[a] = As[(tr + 16 * a) * (KC64 + 1) + k];
-      for (int b = 0; b < 8; ++b) bv[b] = Bs[(tc + 16 * b) * (KC64 + 1) + k];
-      for (int a = 0; a < 8; ++a)
+  };
+  double acc[4][8];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0;
+  const int rounds = (nk + DF_K - 1) / DF_K;
+#pragma unroll
+  for (int r = 0; r < DF_NBUF - 1; ++r)
+    if (r < rounds) issue(r);
+  for (int r = 0; r < rounds; ++r) {
+    // wait for this wave's loads of round r (those of round r + 1 stay in flight), then for
+    // everyone's; the buffer of round r - 1, read by all, is refilled
+    __builtin_amdgcn_sched_barrier(0);
+    if (r + 1 < rounds) __builtin_amdgcn_s_waitcnt(0x0070 | NLD);  // vmcnt(NLD) lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (r + DF_NBUF - 1 < rounds) issue(r + DF_NBUF - 1);
+    if (r * DF_K + 4 * w >= nk) continue;  // p_pad is a multiple of 16: whole groups of 4
+    const double* A = sm + (r % DF_NBUF) * DF_BUF + lr * DF_K;
+    const double* B = sm + (r % DF_NBUF) * DF_BUF + (DF_ROWS + lc) * DF_K;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // coordinate 4 w + k of the round, in piece 2 w + k / 2
+      const int ao = 2 * ((2 * w + (k >> 1)) ^ lr) + (k & 1);
+      const int bo = 2 * ((2 * w + (k >> 1)) ^ lc) + (k & 1);
+      double av[4], bv[8];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) av[a] = A[8 * a * DF_K + ao];
+#pragma unroll
+      for (int b = 0; b < 8; ++b) bv[b] = B[8 * b * DF_K + bo];
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
         for (int b = 0; b < 8; ++b) {
           const double df = av[a] - bv[b];
           acc[a][b] = fma(df, df, acc[a][b]);
         }
+      if (k == 1) __builtin_amdgcn_sched_barrier(0);  // at most two coordinates' reads ahead
     }
   }
-  // cross tests: row sums over the x2 columns (rs) and the y2 columns (cs, in place of the
-  // column sums), no stored tile
-  const int split = d.cross ? cross_split(d, c.j) : -1;
-  double* D = d.cross ? nullptr : (double*)d.D + (int64_t)c.t * TILE * TILE;
-  double rs[8], cs[8];
-  for (int a = 0; a < 8; ++a) rs[a] = 0.0;
-  for (int b = 0; b < 8; ++b) cs[b] = 0.0;
-  for (int a = 0; a < 8; ++a)
-    for (int b = 0; b < 8; ++b) {
-      const int r = tr + 16 * a, col = tc + 16 * b;
-      double v;
-      if (r >= c.rows_i || col >= c.rows_j) v = 0.0;
-      else if (c.diag && r == col) v = d.kind == KIND_ED ? 0.0 : 1.0;
-      else v = d.kind == KIND_ED ? sqrt(acc[a][b]) : exp(-d.gamma * acc[a][b]);
-      if (split >= 0) {
-        if (col < split) rs[a] += v;
-        else cs[a] += v;
-      } else {
-        D[r * TILE + col] = v;
-        rs[a] += v;
-        cs[b] += v;
-      }
-    }
-  if (split >= 0) {
-    for (int a = 0; a < 8; ++a) rp[(tr + 16 * a) * 16 + tc] = rs[a];
-    for (int a = 0; a < 8; ++a) cp[(tr + 16 * a) * 16 + tc] = cs[a];
-    __syncthreads();
-    if (tid < TILE) {
-      double s0 = 0.0, s1 = 0.0;
-      for (int q = 0; q < 16; ++q) {
-        s0 += rp[tid * 16 + q];
-        s1 += cp[tid * 16 + q];
-      }
-      d.tsum[(int64_t)c.t * TSUM_STRIDE + tid] = s0;
-      d.tsum[(int64_t)c.t * TSUM_STRIDE + TILE + tid] = s1;
-    }
-    return;
-  }
-  for (int a = 0; a < 8; ++a) rp[(tr + 16 * a) * 16 + tc] = rs[a];
-  for (int b = 0; b < 8; ++b) cp[tr * TILE + tc + 16 * b] = cs[b];
+  // The waves' partial sums meet in LDS: waves 4..7 hand theirs to waves 0..3, which then
+  // finish row group a = w (rows lr + 8 w) each and hand their other three groups over.
   __syncthreads();
-  double s = 0.0;
-  if (tid < TILE) {
-    for (int q = 0; q < 16; ++q) s += rp[tid * 16 + q];
-    d.tsum[(int64_t)c.t * TSUM_STRIDE + tid] = s;
-  } else {
-    const int col = tid - TILE;
-    for (int q = 0; q < 16; ++q) s += cp[q * TILE + col];
-    d.tsum[(int64_t)c.t * TSUM_STRIDE + TILE + col] = s;  // all 128 rows in one slot
-    d.tsum[(int64_t)c.t * TSUM_STRIDE + 2 * TILE + col] = 0.0;
+  if (w >= 4) {
+#pragma unroll
+    for (int o = 0; o < 32; ++o) sm[((w - 4) * 32 + o) * 64 + lane] = acc[o >> 3][o & 7];
+  }
+  __syncthreads();
+  if (w < 4) {
+#pragma unroll
+    for (int o = 0; o < 32; ++o) acc[o >> 3][o & 7] += sm[(w * 32 + o) * 64 + lane];
+  }
+  __syncthreads();
+  // slot of (source wave q, group a != q)
+  auto slot = [&](int q, int a) { return sm + ((q * 3 + (a < q ? a : a - 1)) * 8) * 64 + lane; };
+  double v[8];  // this wave's own part of its group, then the sums
+#pragma unroll
+  for (int b = 0; b < 8; ++b) v[b] = 0.0;
+  if (w < 4) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      if (a != w) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) slot(w, a)[b * 64] = acc[a][b];
+      } else {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) v[b] = acc[a][b];
+      }
+  }
+  __syncthreads();
+  double (*cs)[DF_COLS] = (double (*)[DF_COLS])(sm + 4 * 3 * 8 * 64);
+  if (w < 4) {
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      double s = 0.0;  // in the order of the waves, whichever of them adds
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s += q == w ? v[b] : slot(q, w)[b * 64];
+      v[b] = s;
+    }
+    dist_emit_f64(d, c, r0, c0, w, lane, v, cs);
+  }
+  __syncthreads();
+  if (!d.cross && tid < DF_COLS)
+    (d.tsum + (int64_t)c.t * d.tsum_stride)[(2 + rq) * TILE + c0 + tid] =
+        (cs[0][tid] + cs[1][tid]) + (cs[2][tid] + cs[3][tid]);
+}
+
+// DF_PARTS units per stored tile; a grid smaller than the `units` of all tests (one dispatch
+// holds fewer than 2^32 work-items) strides over them.
+__global__ void __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests,
+           int64_t units) {
+  __shared__ __attribute__((aligned(16))) double sm[DF_NBUF * DF_BUF];
+  static_assert(4 * 32 * 64 <= DF_NBUF * DF_BUF, "the partial sums fit the operand buffers");
+  for (int64_t g = blockIdx.x; g < units; g += gridDim.x) {
+    const int64_t u = xcd_grouped(g, units);
+    const int64_t bid = u / DF_PARTS;
+    const int ti = find_test(offs, ntests, bid);
+    const TestDesc& d = descs[ti];
+    dist_part_f64(d, tile_ctx(d, bid - offs[ti]), (int)(u % DF_PARTS), sm);
+    __syncthreads();  // the next unit's loads reuse the buffers
   }
 }
 
@@ -994,9 +1096,12 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
       hipLaunchKernelGGL(k_gram_super<false>, g, b, 0, st, d, offs, n);
     return;
   }
-  if (gop == GOP_F64)
-    hipLaunchKernelGGL(k_dist_f64, g, b, 0, st, d, offs, n);
-  else if (gop == GOP_F16PAIR && dual)
+  if (gop == GOP_F64) {
+    // the launch table counts stored tiles
+    const int64_t units = blocks * DF_PARTS;
+    hipLaunchKernelGGL(k_dist_f64, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
+                       dim3(DF_THREADS), 0, st, d, offs, n, units);
+  } else if (gop == GOP_F16PAIR && dual)
     hipLaunchKernelGGL(k_gram_f16x3<true>, g, b, 0, st, d, offs, n);
   else if (gop == GOP_F16PAIR)
     hipLaunchKernelGGL(k_gram_f16x3<false>, g, b, 0, st, d, offs, n);

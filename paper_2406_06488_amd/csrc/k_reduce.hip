@@ -26,10 +26,16 @@ __global__ void __launch_bounds__(64) k_rowsum(const TestDesc* __restrict__ desc
   const bool isx = i < d.tx;
   double s = 0.0;
   // row sums of tile (i, j); column sums (two row halves) of tile (j, i)
-  auto rowsum = [&](int j) { return ts[(int64_t)tile_index(i, j, d.nt) * TSUM_STRIDE + r]; };
+  // (FP64 form: row sums of two column halves, column sums of four row quarters)
+  const bool f64 = d.prec == PREC_F64;
+  auto rowsum = [&](int j) {
+    const double* t = ts + tile_index(i, j, d.nt) * d.tsum_stride;
+    return f64 ? t[r] + t[TILE + r] : t[r];
+  };
   auto colsum = [&](int j) {
-    const double* t = ts + (int64_t)tile_index(j, i, d.nt) * TSUM_STRIDE;
-    return t[TILE + r] + t[2 * TILE + r];
+    const double* t = ts + tile_index(j, i, d.nt) * d.tsum_stride;
+    return f64 ? (t[2 * TILE + r] + t[3 * TILE + r]) + (t[4 * TILE + r] + t[5 * TILE + r])
+               : t[TILE + r] + t[2 * TILE + r];
   };
   // unrolled so that several tile sums are in flight; the additions stay in order of j
   if (!cross) {

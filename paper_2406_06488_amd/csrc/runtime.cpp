@@ -217,6 +217,7 @@ TestPlan make_plan(const etest_request& r, int64_t kc_override, int mode) {
   sz[B_RESULT] = sizeof(DevResult);
   sz[B_PERMOUT] = 0;  // set by build_batch when an internal output is needed
   if (mode != PLAN_EFFICIENT) {  // no centred planes or resampling buffers
+    if (f64) sz[B_TSUM] = (size_t)d.ntiles * TSUM_STRIDE_F64 * 8;
     sz[B_PLANES] = 0;
     sz[B_PART] = 0;
     sz[B_PSTAT] = 0;
@@ -394,6 +395,14 @@ void assign_pointers(TestPlan& P, char* r, DevResult* result) {
   d.nrm = r + P.off[B_NRM];
   d.D = r + P.off[B_D];
   d.tsum = (double*)(r + P.off[B_TSUM]);
+  d.tsum_stride = TSUM_STRIDE;
+  if (d.prec == PREC_F64) {
+    // the FP64 block stage writes more sums per tile; a test with centred planes keeps them
+    // in its plane region, which the centring fills only after the sums have been read
+    const bool planes = P.size[B_PLANES] > 0;
+    if (planes) d.tsum = (double*)(r + P.off[B_PLANES]);
+    d.tsum_stride = planes ? TILE * TILE : TSUM_STRIDE_F64;
+  }
   d.tmax = (float*)(r + P.off[B_TMAX]);
   d.rsum = (double*)(r + P.off[B_RSUM]);
   d.obs = (double*)(r + P.off[B_OBS]);
@@ -1336,7 +1345,8 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
   sz[C_COLMEAN] = f64 ? 0 : (size_t)r.p * 8;
   sz[C_W] = (size_t)npad * d.p_pad * el_w;
   sz[C_NRM] = (size_t)npad * (f64 ? 8 : 4);
-  sz[C_TSUM] = (size_t)d.ntiles * TSUM_STRIDE * 8;
+  d.tsum_stride = f64 ? 4 * TILE : TSUM_STRIDE;
+  sz[C_TSUM] = (size_t)d.ntiles * d.tsum_stride * 8;
   sz[C_TMAX] = (size_t)d.ntiles * TMAX_PER_TILE * 4;
   sz[C_V] = (size_t)npad * 8;
   sz[C_OBS] = 8 * 8;
