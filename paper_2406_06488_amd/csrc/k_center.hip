@@ -22,21 +22,12 @@
 // A-fragment order: fragment (mb, kb) holds rows 32 mb.. and columns 64 kb.., lane
 // row%32 + 32 * ((col%64)/32) holding 32 bytes (columns in order), stored as two 16-byte
 // halves: [fragment][half][lane][16 bytes].
-// FP64 form: one FP64 row-major tile.
+// FP64 form: one FP64 tile in the order v_mfma_f64_16x16x4f64 reads its A operand: fragment
+// (rb, kp) holds rows 16 rb .. and columns 8 kp .., lane row%16 + 16 * ((col%8)/2) holding
+// two adjacent columns (one for each of two instructions).
 #include "common.h"
 
 namespace et {
-
-__device__ inline double center_value(const TestDesc& d, int i, int j, int r, int col, int rows_i,
-                                      int rows_j, double v, double inv_n, double c0) {
-  if (r >= rows_i || col >= rows_j) return 0.0;
-  const int64_t pa = (int64_t)i * TILE + r, pb = (int64_t)j * TILE + col;
-  const double ca = (d.rsum[pa * 2] + d.rsum[pa * 2 + 1]) * inv_n;
-  const double cb = (d.rsum[pb * 2] + d.rsum[pb * 2 + 1]) * inv_n;
-  double x = ((v - ca) - cb) + c0;
-  if (i == j) x *= 0.5;
-  return x;
-}
 
 // FP64 -> FP32, kept as a separate step: folded into the fp16 conversion that follows it,
 // it would become one FP64 -> fp16 rounding, which has no hardware instruction.
@@ -145,30 +136,62 @@ __global__ void __launch_bounds__(256) k_center_split(const TestDesc* __restrict
   }
 }
 
+// One unit per 16-row fragment block of a stored tile, every load first (8 units per tile:
+// with one workgroup per tile, 64 entries in turn per thread, three tiles took 14-20 us and
+// 136 tiles 24 us, now 4 and 9); a grid smaller than the units strides over them.
+constexpr int CF_PARTS = TILE / 16;
 __global__ void __launch_bounds__(256) k_center_f64(const TestDesc* __restrict__ descs,
-                                                    const int64_t* __restrict__ offs, int ntests) {
-  const int ti = find_test(offs, ntests, blockIdx.x);
-  const TestDesc d = descs[ti];
-  const int t = (int)(blockIdx.x - offs[ti]);
-  int i, j;
-  tile_coords(t, d.nt, &i, &j);
-  const int rows_i = tile_rows(d, i), rows_j = tile_rows(d, j);
-  const double n = (double)d.nx + (double)d.ny;
-  const double inv_n = 1.0 / n;
-  const double c0 = d.obs[4] / (n * n);
-  const double* Dt = (const double*)d.D + (int64_t)t * TILE * TILE;
-  double* P = (double*)d.planes + (int64_t)t * TILE * TILE;
-  for (int e = threadIdx.x; e < TILE * TILE; e += 256) {
-    const int r = e / TILE, col = e % TILE;
-    P[e] = center_value(d, i, j, r, col, rows_i, rows_j, Dt[e], inv_n, c0);
+                                                    const int64_t* __restrict__ offs, int ntests,
+                                                    int64_t units) {
+  for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+    const int64_t bid = u / CF_PARTS;
+    const int rb = (int)(u % CF_PARTS);
+    const int ti = find_test(offs, ntests, bid);
+    const TestDesc& d = descs[ti];
+    const int t = (int)(bid - offs[ti]);
+    int i, j;
+    tile_coords(t, d.nt, &i, &j);
+    const int rows_i = tile_rows(d, i), rows_j = tile_rows(d, j);
+    const double n = (double)d.nx + (double)d.ny;
+    const double inv_n = 1.0 / n;
+    const double c0 = d.obs[4] / (n * n);
+    const double half = i == j ? 0.5 : 1.0;
+    // fragments kp = (threadIdx.x >> 6) + 4 s; this thread's row is the same in all of them
+    const int lane = threadIdx.x & 63, r = rb * 16 + (lane & 15);
+    const int64_t pa = (int64_t)i * TILE + r;
+    const double ca = (d.rsum[pa * 2] + d.rsum[pa * 2 + 1]) * inv_n;
+    const double* D = (const double*)d.D + (int64_t)t * TILE * TILE;
+    double2* P = (double2*)((double*)d.planes + (int64_t)t * TILE * TILE) + rb * 16 * 64;
+    double2 v[4], ra[4], rc[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int col = 8 * ((int)(threadIdx.x >> 6) + 4 * s) + 2 * (lane >> 4);
+      v[s] = *(const double2*)(D + r * TILE + col);
+      const double2* rs = (const double2*)(d.rsum + ((int64_t)j * TILE + col) * 2);
+      ra[s] = rs[0];
+      rc[s] = rs[1];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kp = (int)(threadIdx.x >> 6) + 4 * s, col = 8 * kp + 2 * (lane >> 4);
+      const double cb0 = (ra[s].x + ra[s].y) * inv_n, cb1 = (rc[s].x + rc[s].y) * inv_n;
+      double2 x = make_double2(0.0, 0.0);
+      if (r < rows_i && col < rows_j) x.x = (((v[s].x - ca) - cb0) + c0) * half;
+      if (r < rows_i && col + 1 < rows_j) x.y = (((v[s].y - ca) - cb1) + c0) * half;
+      P[kp * 64 + lane] = x;
+    }
   }
 }
 
 void launch_center(bool f64, int64_t blocks, hipStream_t st, const TestDesc* d,
                    const int64_t* offs, int n) {
   if (blocks <= 0) return;
-  if (f64) hipLaunchKernelGGL(k_center_f64, dim3((unsigned)blocks), dim3(256), 0, st, d, offs, n);
-  else hipLaunchKernelGGL(k_center_split, dim3((unsigned)blocks), dim3(256), 0, st, d, offs, n);
+  if (f64) {  // the launch table counts stored tiles
+    const int64_t units = blocks * CF_PARTS;
+    hipLaunchKernelGGL(k_center_f64, dim3((unsigned)(units < (1 << 23) ? units : (1 << 23))),
+                       dim3(256), 0, st, d, offs, n, units);
+  } else
+    hipLaunchKernelGGL(k_center_split, dim3((unsigned)blocks), dim3(256), 0, st, d, offs, n);
 }
 
 }  // namespace et

@@ -17,8 +17,7 @@
 // v_mfma_scale_f32_32x32x64_f8f6f4 (unit block scales), which takes 64 columns per
 // instruction at about 1.6x the fp16 rate.  Every product is exact, so only the FP32
 // accumulation order differs from an exact evaluation; partial sums per row range are
-// reduced in FP64.  FP64 form: the same quadratic form on the FP64 vector ALU, one thread
-// per split.
+// reduced in FP64.  FP64 form: the same quadratic form on the FP64 MFMA.
 #include "common.h"
 
 namespace et {
@@ -255,16 +254,23 @@ __global__ void __launch_bounds__(PERM_THREADS) k_perm_mfma(const TestDesc* __re
   }
 }
 
-// FP64: thread = split column (a workgroup covers 256 columns of a chunk); each workgroup
-// takes one 32-row strip of its row unit's centred tiles (the row units of an FP64 test are
-// PC_STRIPS times as many as its row-unit walk gives: unit rks = row unit rks / PC_STRIPS,
-// strip rks % PC_STRIPS), so that even a test of two tiles spreads over several CUs.
+// FP64: v_mfma_f64_16x16x4f64, whose products with the split bits (0.0 or 1.0) are exact.
+// The work units are those of 32-row strips (unit rks = row unit rks / PC_STRIPS, strip
+// rks % PC_STRIPS), so that even a test of two tiles spreads over several CUs; a workgroup
+// covers the 256 columns of a chunk, each wave 64 of them: 2 row blocks x 4 column blocks of
+// 16 x 16.  The centred tile is stored in the order the A operand is read (k_center.hip), so
+// a wave loads its fragments straight from memory, 32 columns ahead of the products, and the
+// four waves of the workgroup meet in the L1: no LDS and no barrier.  Bound by the FP64 MFMA
+// rate on large tests, by one unit's chain on small ones.  Measured against one thread per
+// split and an FMA per entry: 1000 + 1000 rows, B = 200: 208 -> 31 us; 100 + 100 rows, B =
+// 1000: 71 -> 14 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 __global__ void __launch_bounds__(256) k_perm_f64(const TestDesc* __restrict__ descs,
                                                   const int64_t* __restrict__ offs, int ntests,
                                                   const int32_t* __restrict__ pcr) {
-  __shared__ double Ts[PC_ROWS * TILE];
   const int ti = find_test(offs, ntests, blockIdx.x);
-  const TestDesc d = descs[ti];
+  const TestDesc& d = descs[ti];
   const int pc0 = pcr ? pcr[2 * ti] : 0;
   const int pcn = pcr ? pcr[2 * ti + 1] : (int)(d.B_pad / NP);
   const int ncr = (pcn + d.cc - 1) / d.cc;
@@ -275,40 +281,71 @@ __global__ void __launch_bounds__(256) k_perm_f64(const TestDesc* __restrict__ d
   int i, j0, j1;
   rowk_coords(d, rks / PC_STRIPS, &i, &j0, &j1);
   const int cb = pc0 + cr * d.cc, ce = min(pc0 + pcn, cb + d.cc);
-  const int tid = threadIdx.x;
-  const uint32_t* Z = d.Z;
-  constexpr int NLD = PC_ROWS * TILE / 2 / 256;  // 16-byte loads per thread per strip
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, cl = lane & 15, kq = lane >> 4;
+  const int64_t BP = d.B_pad;
+  // fragments of row blocks 2 h and 2 h + 1 of tile (i, j0); successive j are adjacent tiles
+  const double2* A0 = (const double2*)((const double*)d.planes +
+                                       tile_index(i, j0, d.nt) * TILE * TILE) +
+                      2 * h * 16 * 64 + lane;
+  const int steps = (j1 - j0) * TILE_WORDS;  // of 32 columns: one membership word each
   for (int c = cb; c < ce; ++c) {
-    const int64_t col = (int64_t)c * NP + tid;
-    const uint32_t zi = Z[(int64_t)(i * TILE_WORDS + h) * d.B_pad + col];
-    double acc = 0.0;
-    for (int j = j0; j < j1; ++j) {
-      uint32_t zj[TILE_WORDS];
+    const int64_t col = (int64_t)c * NP + w * 64 + cl;  // of column block 0
+    const uint32_t* Zj = d.Z + (int64_t)j0 * TILE_WORDS * BP + col;
+    f64x4 acc[2][4];
 #pragma unroll
-      for (int q = 0; q < TILE_WORDS; ++q) zj[q] = Z[(int64_t)(j * TILE_WORDS + q) * d.B_pad + col];
-      const double2* Tt = (const double2*)((const double*)d.planes +
-                                           (int64_t)tile_index(i, j, d.nt) * TILE * TILE +
-                                           (int64_t)h * PC_ROWS * TILE);
-      double2 v[NLD];  // every load of the strip in flight before the first LDS store
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) v[k] = Tt[tid + 256 * k];
-      __syncthreads();
+      for (int nb = 0; nb < 4; ++nb) acc[rb][nb] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double2 a[2][4], an[2][4];
+    uint32_t z[4], zn[4];
+    auto load = [&](int s, double2 (&x)[2][4], uint32_t (&y)[4]) {
+      const double2* A = A0 + (int64_t)(s >> 2) * (TILE * TILE / 2) + (s & 3) * 4 * 64;
 #pragma unroll
-      for (int k = 0; k < NLD; ++k) ((double2*)Ts)[tid + 256 * k] = v[k];
-      __syncthreads();
-      for (int rr = 0; rr < PC_ROWS; ++rr) {
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-        for (int q = 0; q < TILE_WORDS; ++q) {
-          const uint32_t wq = zj[q];
+        for (int kp = 0; kp < 4; ++kp) x[rb][kp] = A[(rb * 16 + kp) * 64];
 #pragma unroll
-          for (int b = 0; b < 32; ++b)
-            a[b & 3] = fma(Ts[rr * TILE + q * 32 + b], (double)((wq >> b) & 1u), a[b & 3]);
-        }
-        if ((zi >> rr) & 1u) acc += (a[0] + a[1]) + (a[2] + a[3]);
-      }
+      for (int nb = 0; nb < 4; ++nb) y[nb] = Zj[(int64_t)s * BP + 16 * nb];
+    };
+    auto multiply = [&](const double2 (&x)[2][4], const uint32_t (&y)[4]) {
+      // columns 8 kp + 2 kq + e of the step: bit 8 kp + e of the shifted word
+#pragma unroll
+      for (int kp = 0; kp < 4; ++kp)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int nb = 0; nb < 4; ++nb) {
+            const int bit = __builtin_amdgcn_sbfe((int)(y[nb] >> (2 * kq)), 8 * kp + e, 1);
+            const double b = __hiloint2double(bit & 0x3FF00000, 0);
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+              acc[rb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e ? x[rb][kp].y : x[rb][kp].x, b,
+                                                                 acc[rb][nb], 0, 0, 0);
+          }
+    };
+    load(0, a, z);
+    for (int s = 0; s < steps; s += 2) {  // steps is a multiple of 4
+      load(s + 1, an, zn);
+      multiply(a, z);
+      if (s + 2 < steps) load(s + 2, a, z);
+      multiply(an, zn);
     }
-    d.part[(int64_t)rks * d.B_pad + col] = acc;
+    // fold the row weights: element e of an accumulator is row kq + 4 e of its row block
+    double q[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      const uint32_t zi = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col + 16 * nb] >> kq;
+      double f = 0.0;
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f += (zi >> (16 * rb + 4 * e)) & 1u ? acc[rb][nb][e] : 0.0;
+      f += __shfl_xor(f, 16, 64);
+      f += __shfl_xor(f, 32, 64);
+      q[nb] = f;
+    }
+    const double mine = kq == 0 ? q[0] : kq == 1 ? q[1] : kq == 2 ? q[2] : q[3];
+    d.part[(int64_t)rks * BP + col + 16 * kq] = mine;
   }
 }
 

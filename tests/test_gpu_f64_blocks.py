@@ -40,3 +40,20 @@ def test_blocks_and_sums(nx, ny, p):
             (want[1][:hy, hy:].mean() - want[2][hx:, :hy].mean())
         c = api.cross(tx, ty, "ed", "f64")
         assert abs(c["statistic"] - float(u)) <= (tol + 64 * EPS) * (2 * sxy + sxx + syy + 4)
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (15, 17), (33, 95), (128, 129), (260, 381)])
+@pytest.mark.parametrize("B", [1, 255, 256, 700])
+@pytest.mark.parametrize("kind", ["ed", "mmd"])
+def test_resampling_edges(nx, ny, B, kind):
+    """Centring and resampling at the edges of their 16-row blocks, 32-row strips and 256-split
+    chunks, by the oracle's rules for the FP64 form."""
+    import torch
+
+    import oracle
+    from tests.gpu_helpers import compare_run
+    g = np.random.Generator(np.random.PCG64(nx + 7 * ny + B))
+    X, Y = g.standard_normal((nx, 5)), g.standard_normal((ny, 5)) + 0.3
+    got = api.run(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), B, 3, kind, "f64", 0.2)
+    want = oracle.run_test(X, Y, B, 3, api.KINDS[kind], 0.2)
+    compare_run(got, want, "f64")
