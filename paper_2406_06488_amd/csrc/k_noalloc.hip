@@ -64,8 +64,6 @@ void launch_put_desc(const TestDesc& d, const int64_t* offs, TestDesc* dd, int64
   hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, st, a, dd, doffs);
 }
 
-static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
 }  // namespace et
 
 using namespace et;

@@ -24,15 +24,6 @@ etest_status set_error(etest_status s, const std::string& msg) {
   return s;
 }
 
-#define HIP_OK(call, what)                                                                   \
-  do {                                                                                       \
-    hipError_t e_ = (call);                                                                  \
-    if (e_ != hipSuccess)                                                                    \
-      return set_error(ETEST_EDEVICE, std::string(what) + ": " + hipGetErrorString(e_));     \
-  } while (0)
-
-static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
 static int env_int(const char* name, int dflt, int lo, int hi) {
   const char* v = getenv(name);
   if (!v || !*v) return dflt;
@@ -695,7 +686,7 @@ struct Profile {
 };
 static thread_local Profile g_prof;
 
-static const StageEvents* profile_events() {
+const StageEvents* profile_events() {
   if (!g_prof.on) return nullptr;
   StageEvents* ev = nullptr;
   if (!g_prof.spare.empty()) {
@@ -716,7 +707,7 @@ static const StageEvents* profile_events() {
 }
 
 // Adds the elapsed times of every pending pass (waiting for their last events).
-static void profile_collect() {
+void profile_collect() {
   for (StageEvents* ev : g_prof.pending) {
     for (int k = 0; k < NSTAGE; ++k) {
       if (!(ev->mask >> k & 1u)) continue;
@@ -748,7 +739,7 @@ etest_status dev_to_result(const DevResult& r, etest_result* out) {
 }
 
 // Pinned staging for result copies (one per thread).
-static DevResult* pinned_results(size_t n) {
+DevResult* pinned_results(size_t n) {
   static thread_local DevResult* buf = nullptr;
   static thread_local size_t cap = 0;
   if (cap < n) {
@@ -1424,297 +1415,3 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
   out->n_refined = hb->flags[1];
   return ETEST_OK;
 }
-
-// ------------------------------------------------- baselines: standard and pre-computation
-namespace et {
-
-// Staging, blocks, block sums and observed statistic of the first m tests of a batch (the
-// launch tables of a prefix of the tests are prefixes of the batch's tables).
-static void enqueue_blocks(const Batch& b, int m, hipStream_t st) {
-  const int n = (int)b.plans.size();
-  auto offs = [&](Slot s) { return b.d_offs + (size_t)s * (n + 1); };
-  auto total = [&](Slot s) { return b.offs[(size_t)s * (n + 1) + m]; };
-  const TestDesc* D = b.d_descs;
-  launch_clear_flags(st, D, nullptr, m);
-  launch_colpart(total(S_COLPART), st, D, offs(S_COLPART), m);
-  launch_colmean(total(S_COLMEAN), st, D, offs(S_COLMEAN), m);
-  launch_stage(total(S_STAGE), st, D, offs(S_STAGE), m);
-  launch_gram_slots(offs, total, st, D, m, false);
-  launch_rowsum(total(S_ROWSUM), st, D, offs(S_ROWSUM), m);
-  launch_observed(st, D, nullptr, m);
-}
-
-// Device result -> host, free the workspaces, wait.
-static etest_status finish_baseline(DevResult* d_res, Batch* b, void* aux, hipStream_t st,
-                                    hipError_t e, const char* what, etest_result* out) {
-  DevResult* h = pinned_results(1);
-  if (e == hipSuccess) e = hipGetLastError();
-  if (e == hipSuccess && h) e = hipMemcpyAsync(h, d_res, sizeof(DevResult), hipMemcpyDeviceToHost, st);
-  free_batch(b, st, true);
-  if (aux) (void)hipFreeAsync(aux, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (!h) return set_error(ETEST_ENOMEM, "pinned result buffer");
-  if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
-  return dev_to_result(*h, out);
-}
-
-// Standard test: the B + 1 splits (drawn splits 0..B-1, identity B) are recomputed in
-// passes of up to 256 tests that share one batch workspace; each test stages its split's
-// X*, Y* through a row map and runs staging, Gram, block sums and the observed statistic.
-static etest_status run_standard(const etest_request& r, hipStream_t st, etest_result* out) {
-  init_pool_once();
-  const int64_t n = r.nx + r.ny, W = (n + 31) / 32, B = r.B;
-  etest_request q = r;
-  q.B = 0;
-  q.perm_stats = nullptr;
-  const TestPlan P0 = make_plan(q, 0, PLAN_BLOCKS);
-  const int64_t budget = 4LL << 30;
-  const int64_t chunk =
-      std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(B + 1, 256),
-                                             budget / std::max<int64_t>(1, (int64_t)P0.bytes)));
-  size_t aoff[5], asz[5] = {(size_t)(chunk * n * 4), (size_t)(chunk * W * 4),
-                            (size_t)((B + 1) * 8), (size_t)(FLAG_WORDS * 4), sizeof(DevResult)};
-  size_t atotal = 0;
-  for (int k = 0; k < 5; ++k) {
-    aoff[k] = atotal;
-    atotal += align256(asz[k]);
-  }
-  void* aux = nullptr;
-  hipError_t e = hipMallocAsync(&aux, atotal, st);
-  if (e != hipSuccess || !aux) {
-    (void)hipGetLastError();
-    return set_error(ETEST_ENOMEM, "standard test buffers of " + std::to_string(atotal) + " bytes");
-  }
-  char* a = (char*)aux;
-  int32_t* rowmaps = (int32_t*)(a + aoff[0]);
-  uint32_t* words = (uint32_t*)(a + aoff[1]);
-  double* stats = (double*)(a + aoff[2]);
-  int32_t* flags = (int32_t*)(a + aoff[3]);
-  DevResult* d_res = (DevResult*)(a + aoff[4]);
-  Batch b;
-  b.plans.assign((size_t)chunk, P0);
-  for (int64_t k = 0; k < chunk; ++k) b.plans[(size_t)k].d.rowmap = rowmaps + k * n;
-  etest_status s = place_batch(&b, st, true);
-  if (s != ETEST_OK) {
-    (void)hipFreeAsync(aux, st);
-    return s;
-  }
-  e = hipMemsetAsync(flags, 0, FLAG_WORDS * 4, st);
-  for (int64_t c0 = 0; e == hipSuccess && c0 <= B; c0 += chunk) {
-    const int m = (int)std::min<int64_t>(chunk, B + 1 - c0);
-    const int64_t drawn = std::max<int64_t>(0, std::min<int64_t>(m, B - c0));
-    launch_member_public(r.nx, r.ny, r.seed, c0, drawn, words, st);
-    launch_rowmap(words, drawn, m, n, r.nx, rowmaps, st);
-    enqueue_blocks(b, m, st);
-    launch_collect(b.d_descs, m, c0, B, stats, flags, st);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) launch_count(stats, B, flags, r.perm_stats, d_res, st);
-  return finish_baseline(d_res, &b, aux, st, e, "standard test", out);
-}
-
-// Pre-computation test: the pooled Gram (D_WW: upper tiles, or with `dense` the whole
-// nt x nt grid as Alg. 5 prints it), the split stream, then the per-split class sums of
-// every stored entry and the statistics.
-// Stage timing (etest_profile_enable): 0 staging, 1 blocks, 2 split stream, 5 class sums,
-// 6 statistics + p-value.
-static etest_status run_precomputed(const etest_request& r, hipStream_t st, etest_result* out,
-                                    bool dense) {
-  init_pool_once();
-  Batch b;
-  b.plans.push_back(make_plan(r, 0, dense ? PLAN_PRECOMP_DENSE : PLAN_PRECOMP));
-  // one workgroup per (stored tile, 32-row strip, 64 split columns)
-  const int64_t groups = (r.B + 1 + 63) / 64;
-  if ((int64_t)b.plans[0].d.ntiles * PC_STRIPS > 2147483647LL / groups)
-    return set_error(ETEST_EINVAL, "pre-computation test: tiles x strips x split groups must "
-                                   "stay below 2^31");
-  etest_status s = place_batch(&b, st, true);
-  if (s != ETEST_OK) return s;
-  const TestDesc& d = b.descs[0];
-  const TestDesc* D = b.d_descs;
-  auto offs = [&](Slot k) { return b.d_offs + (size_t)k * 2; };
-  auto total = [&](Slot k) { return b.offs[(size_t)k * 2 + 1]; };
-  const StageEvents* ev = profile_events();
-  auto mark = [&](int k, bool begin) {
-    if (ev && (ev->mask >> k & 1u)) (void)hipEventRecord(begin ? ev->begin[k] : ev->end[k], st);
-  };
-  launch_clear_flags(st, D, nullptr, 1);
-  mark(0, true);
-  launch_colpart(total(S_COLPART), st, D, offs(S_COLPART), 1);
-  launch_colmean(total(S_COLMEAN), st, D, offs(S_COLMEAN), 1);
-  launch_stage(total(S_STAGE), st, D, offs(S_STAGE), 1);
-  mark(0, false);
-  mark(2, true);
-  launch_member(total(S_MEMBER), st, D, offs(S_MEMBER), 1);
-  mark(2, false);
-  mark(1, true);
-  launch_gram_slots(offs, total, st, D, 1, false);
-  mark(1, false);
-  mark(5, true);
-  launch_precomp(r.prec == ETEST_PREC_F64, D, d.ntiles, r.B, d.part, st);
-  mark(5, false);
-  mark(6, true);
-  launch_precomp_stat(D, d.ntiles, r.B, d.part, d.pstat, st);
-  launch_count(d.pstat, r.B, d.flags, r.perm_stats, b.d_results, st);
-  mark(6, false);
-  etest_status rs = finish_baseline(b.d_results, &b, nullptr, st, hipSuccess, "pre-computation test", out);
-  profile_collect();
-  return rs;
-}
-
-// HSIC independence test: the Gaussian kernel matrices of x and of y as two one-sample Grams
-// in one batch (staging and blocks only), then dense zero-diagonal copies, row sums, the
-// permutations, the per-permutation terms, the statistics and the p-value.
-// Stage timing (etest_profile_enable): 0 staging, 1 blocks, 2 permutations, 3 dense
-// matrices and row sums, 5 per-permutation terms, 6 statistics + p-value.
-static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_result* out) {
-  init_pool_once();
-  const int64_t n = h.n, B = h.B, nperm = h.B + 1;
-  const bool f64 = h.prec == ETEST_PREC_F64;
-  etest_request rx{}, ry{};
-  rx.kind = ry.kind = ETEST_MMD;
-  rx.prec = ry.prec = h.prec;
-  rx.nx = ry.nx = n;
-  rx.ny = ry.ny = 0;  // one sample: the Gram covers the x (or y) rows alone
-  rx.p = h.p;
-  ry.p = h.q;
-  rx.gamma = h.gamma_x;
-  ry.gamma = h.gamma_y;
-  rx.X = rx.Y = h.X;
-  ry.X = ry.Y = h.Y;
-  Batch b;
-  b.plans.push_back(make_plan(rx, 0, PLAN_BLOCKS));
-  b.plans.push_back(make_plan(ry, 0, PLAN_BLOCKS));
-  const int64_t nblk = (n + HSIC_RB - 1) / HSIC_RB;
-  const size_t el = f64 ? 8 : 4;
-  enum { H_KX, H_KY, H_RX, H_RY, H_HS, H_FLAGS, H_PERMS, H_PART, H_STATS, H_RES, H_N };
-  size_t sz[H_N] = {(size_t)(n * n) * el, (size_t)(n * n) * el, (size_t)n * 8, (size_t)n * 8,
-                    2 * 8, FLAG_WORDS * 4, (size_t)(nperm * n) * 4, (size_t)(nperm * nblk) * 16,
-                    (size_t)nperm * 8, sizeof(DevResult)};
-  size_t off[H_N], total = 0;
-  for (int k = 0; k < H_N; ++k) {
-    off[k] = total;
-    total += align256(sz[k]);
-  }
-  void* aux = nullptr;
-  hipError_t e = hipMallocAsync(&aux, total, st);
-  if (e != hipSuccess || !aux) {
-    (void)hipGetLastError();
-    return set_error(ETEST_ENOMEM, "HSIC test buffers of " + std::to_string(total) + " bytes");
-  }
-  char* a = (char*)aux;
-  etest_status s = place_batch(&b, st, true);
-  if (s != ETEST_OK) {
-    (void)hipFreeAsync(aux, st);
-    return s;
-  }
-  double* rxs = (double*)(a + off[H_RX]);
-  double* rys = (double*)(a + off[H_RY]);
-  double* hs = (double*)(a + off[H_HS]);
-  int32_t* flags = (int32_t*)(a + off[H_FLAGS]);
-  int32_t* perms = (int32_t*)(a + off[H_PERMS]);
-  double* part = (double*)(a + off[H_PART]);
-  double* stats = (double*)(a + off[H_STATS]);
-  DevResult* d_res = (DevResult*)(a + off[H_RES]);
-  const TestDesc* D = b.d_descs;
-  auto offs = [&](Slot k) { return b.d_offs + (size_t)k * 3; };
-  auto tot = [&](Slot k) { return b.offs[(size_t)k * 3 + 2]; };
-  const StageEvents* ev = profile_events();
-  auto mark = [&](int k, bool begin) {
-    if (ev && (ev->mask >> k & 1u)) (void)hipEventRecord(begin ? ev->begin[k] : ev->end[k], st);
-  };
-  launch_clear_flags(st, D, nullptr, 2);
-  mark(0, true);
-  launch_colpart(tot(S_COLPART), st, D, offs(S_COLPART), 2);
-  launch_colmean(tot(S_COLMEAN), st, D, offs(S_COLMEAN), 2);
-  launch_stage(tot(S_STAGE), st, D, offs(S_STAGE), 2);
-  mark(0, false);
-  mark(1, true);
-  launch_gram_slots(offs, tot, st, D, 2, false);
-  mark(1, false);
-  mark(2, true);
-  launch_permgen(n, h.seed, 0, B, nperm, perms, st);
-  mark(2, false);
-  mark(3, true);
-  launch_hsic_prep(f64, D, n, a + off[H_KX], a + off[H_KY], rxs, rys, hs, flags, st);
-  mark(3, false);
-  mark(5, true);
-  launch_hsic_terms(f64, a + off[H_KX], a + off[H_KY], n, perms, nperm, rxs, rys, part, st);
-  mark(5, false);
-  mark(6, true);
-  launch_hsic_stat(part, n, nperm, hs, stats, st);
-  launch_count(stats, B, flags, h.perm_stats, d_res, st);
-  mark(6, false);
-  etest_status rs = finish_baseline(d_res, &b, aux, st, hipSuccess, "HSIC test", out);
-  profile_collect();
-  return rs;
-}
-
-static etest_status validate_hsic(const etest_hsic_request& h) {
-  // The unbiased HSIC is a small difference of three large terms (on high-dimensional data
-  // about 1e-5 of the kernel entries under independence): 8-bit coordinates cannot carry it,
-  // so the test has the FP64 and FP32 forms only.
-  if (h.prec != ETEST_PREC_F64 && h.prec != ETEST_PREC_F32)
-    return set_error(ETEST_EINVAL, "HSIC test: prec must be ETEST_PREC_F64 or ETEST_PREC_F32");
-  if (h.n < 4 || h.n > HSIC_NMAX)
-    return set_error(ETEST_EINVAL, "HSIC test needs 4 <= n <= " + std::to_string(HSIC_NMAX));
-  if (h.p < 1 || h.q < 1 || h.p > 2147483647LL || h.q > 2147483647LL)
-    return set_error(ETEST_EINVAL, "p and q must be >= 1");
-  if (h.B < 0 || h.B >= 2147483647LL) return set_error(ETEST_EINVAL, "B out of range");
-  if (!(h.gamma_x > 0.0) || !(h.gamma_y > 0.0) || !std::isfinite(h.gamma_x) ||
-      !std::isfinite(h.gamma_y))
-    return set_error(ETEST_EINVAL, "gamma_x and gamma_y must be finite and > 0");
-  if (!h.X || !h.Y) return set_error(ETEST_EINVAL, "X and Y must not be NULL");
-  if (h.reserved != 0) return set_error(ETEST_EINVAL, "reserved field must be 0");
-  // the term pass launches one workgroup per (permutation, block of HSIC_RB rows)
-  const int64_t nblk = (h.n + HSIC_RB - 1) / HSIC_RB;
-  if ((h.B + 1) > 2147483647LL / nblk)
-    return set_error(ETEST_EINVAL, "HSIC test: (B + 1) * ceil(n / " + std::to_string(HSIC_RB) +
-                                       ") must stay below 2^31");
-  return ETEST_OK;
-}
-
-}  // namespace et
-
-extern "C" {
-
-etest_status etest_hsic(const etest_hsic_request* req, void* stream, etest_result* out) {
-  if (!req || !out) return set_error(ETEST_EINVAL, "NULL argument");
-  etest_status s = validate_hsic(*req);
-  if (s != ETEST_OK) return s;
-  return run_hsic(*req, (hipStream_t)stream, out);
-}
-
-etest_status etest_permutations(int64_t n, uint64_t seed, int64_t b0, int64_t count,
-                                int32_t* perms, void* stream) {
-  if (n < 1 || n > HSIC_NMAX) return set_error(ETEST_EINVAL, "permutations need 1 <= n <= " + std::to_string(HSIC_NMAX));
-  if (b0 < 0 || count < 0 || !perms) return set_error(ETEST_EINVAL, "bad range or NULL perms");
-  hipStream_t st = (hipStream_t)stream;
-  launch_permgen(n, seed, b0, count, count, perms, st);
-  HIP_OK(hipGetLastError(), "permutations launch");
-  HIP_OK(hipStreamSynchronize(st), "permutations");
-  return ETEST_OK;
-}
-
-etest_status etest_standard(const etest_request* req, void* stream, etest_result* out) {
-  if (!req || !out) return set_error(ETEST_EINVAL, "NULL argument");
-  etest_status s = validate_request(*req);
-  if (s != ETEST_OK) return s;
-  return run_standard(*req, (hipStream_t)stream, out);
-}
-
-etest_status etest_precomputed(const etest_request* req, void* stream, etest_result* out) {
-  if (!req || !out) return set_error(ETEST_EINVAL, "NULL argument");
-  etest_status s = validate_request(*req);
-  if (s != ETEST_OK) return s;
-  return run_precomputed(*req, (hipStream_t)stream, out, false);
-}
-
-etest_status etest_precomputed_dense(const etest_request* req, void* stream, etest_result* out) {
-  if (!req || !out) return set_error(ETEST_EINVAL, "NULL argument");
-  etest_status s = validate_request(*req);
-  if (s != ETEST_OK) return s;
-  return run_precomputed(*req, (hipStream_t)stream, out, true);
-}
-
-}  // extern "C"

@@ -107,6 +107,13 @@ struct TestPlan {
 
 // Sets the calling thread's error message; returns the status.
 etest_status set_error(etest_status s, const std::string& msg);
+#define HIP_OK(call, what)                                                                   \
+  do {                                                                                       \
+    hipError_t e_ = (call);                                                                  \
+    if (e_ != hipSuccess)                                                                    \
+      return set_error(ETEST_EDEVICE, std::string(what) + ": " + hipGetErrorString(e_));     \
+  } while (0)
+inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 etest_status validate_request(const etest_request& r);
 // EINVAL when a launch of the plans would exceed what one dispatch can address.
 etest_status check_launch_sizes(const TestPlan* plans, size_t n);
@@ -175,6 +182,13 @@ struct StageEvents {
   hipEvent_t begin[NSTAGE], end[NSTAGE];
   uint32_t mask = 0;  // stages (bit k = stage k) whose events are recorded
 };
+
+// Stage events of one pass while stage timing is on (else null), and their collection once
+// the pass has been waited for.
+const StageEvents* profile_events();
+void profile_collect();
+// Pinned host staging for n result copies (one buffer per thread; null when out of memory).
+DevResult* pinned_results(size_t n);
 
 // Optional second stream for the split stream, which does not depend on the data:
 // it is forked after the descriptor copy and joined before the resampling stage.
