@@ -151,8 +151,8 @@ KERNEL_SOURCES = {"k_gram_f16x3": ["k_gram.hip", "k_prep.hip", "common.h", "runt
                   "k_dist_f64": ["k_gram.hip", "common.h", "runtime.cpp"],
                   "k_perm_mfma": ["k_perm.hip", "common.h", "runtime.cpp"],
                   "k_perm_f64": ["k_perm.hip", "common.h", "runtime.cpp"],
-                  "k_precomp": ["k_baseline.hip", "common.h", "runtime.cpp"],
-                  "k_hsic_terms": ["k_hsic.hip", "common.h", "runtime.cpp"]}
+                  "k_precomp": ["k_baseline.hip", "common.h", "baselines.cpp"],
+                  "k_hsic_terms": ["k_hsic.hip", "common.h", "baselines.cpp"]}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.md")
 
 

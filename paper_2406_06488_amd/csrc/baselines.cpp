@@ -168,11 +168,14 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   Batch b;
   b.plans.push_back(make_plan(rx, 0, PLAN_BLOCKS));
   b.plans.push_back(make_plan(ry, 0, PLAN_BLOCKS));
-  const int64_t nblk = (n + HSIC_RB - 1) / HSIC_RB;
   const size_t el = f64 ? 8 : 4;
-  enum { H_KX, H_KY, H_RX, H_RY, H_HS, H_FLAGS, H_PERMS, H_PART, H_STATS, H_RES, H_N };
-  size_t sz[H_N] = {(size_t)(n * n) * el, (size_t)(n * n) * el, (size_t)n * 8, (size_t)n * 8,
-                    2 * 8, FLAG_WORDS * 4, (size_t)(nperm * n) * 4, (size_t)(nperm * nblk) * 16,
+  const int64_t ld = (n + 255) / 256 * 256, nparts = hsic_parts(f64, n);
+  // Permutations go in passes whose tables and partial sums take at most 1 GiB.
+  const int64_t pass = std::min<int64_t>(
+      nperm, std::max<int64_t>(64, ((int64_t)1 << 30) / (4 * ld + 8 * nparts)));
+  enum { H_KX, H_RX, H_RY, H_HS, H_FLAGS, H_PERMS, H_INV, H_PART, H_STATS, H_RES, H_N };
+  size_t sz[H_N] = {(size_t)(n * ld) * el, (size_t)n * 8, (size_t)n * 8, 2 * 8, FLAG_WORDS * 4,
+                    (size_t)(pass * ld) * 2, (size_t)(pass * ld) * 2, (size_t)(pass * nparts) * 8,
                     (size_t)nperm * 8, sizeof(DevResult)};
   size_t off[H_N], total = 0;
   for (int k = 0; k < H_N; ++k) {
@@ -195,7 +198,8 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   double* rys = (double*)(a + off[H_RY]);
   double* hs = (double*)(a + off[H_HS]);
   int32_t* flags = (int32_t*)(a + off[H_FLAGS]);
-  int32_t* perms = (int32_t*)(a + off[H_PERMS]);
+  uint16_t* p16 = (uint16_t*)(a + off[H_PERMS]);
+  uint16_t* inv16 = (uint16_t*)(a + off[H_INV]);
   double* part = (double*)(a + off[H_PART]);
   double* stats = (double*)(a + off[H_STATS]);
   DevResult* d_res = (DevResult*)(a + off[H_RES]);
@@ -215,17 +219,21 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   mark(1, true);
   launch_gram_slots(offs, tot, st, D, 2, false);
   mark(1, false);
-  mark(2, true);
-  launch_permgen(n, h.seed, 0, B, nperm, perms, st);
-  mark(2, false);
   mark(3, true);
-  launch_hsic_prep(f64, D, n, a + off[H_KX], a + off[H_KY], rxs, rys, hs, flags, st);
+  launch_hsic_prep(f64, D, b.descs[0].nt, n, ld, a + off[H_KX], rxs, rys, hs, flags, st);
   mark(3, false);
-  mark(5, true);
-  launch_hsic_terms(f64, a + off[H_KX], a + off[H_KY], n, perms, nperm, rxs, rys, part, st);
-  mark(5, false);
-  mark(6, true);
-  launch_hsic_stat(part, n, nperm, hs, stats, st);
+  for (int64_t c0 = 0; c0 < nperm; c0 += pass) {
+    const int64_t m = std::min(pass, nperm - c0), drawn = std::min(m, B - c0);
+    const bool first = c0 == 0, last = c0 + m == nperm;  // stage events: the first pass's
+    if (first) mark(2, true);
+    launch_hsic_perms(n, ld, h.seed, c0, drawn, m, p16, inv16, st);
+    if (first) mark(2, false);
+    if (first) mark(5, true);
+    launch_hsic_terms(f64, D, a + off[H_KX], n, ld, p16, inv16, m, part, st);
+    if (first) mark(5, false);
+    if (last) mark(6, true);
+    launch_hsic_stat(part, nparts, n, ld, p16, rxs, rys, m, hs, stats + c0, st);
+  }
   launch_count(stats, B, flags, h.perm_stats, d_res, st);
   mark(6, false);
   etest_status rs = finish_baseline(d_res, &b, aux, st, hipSuccess, "HSIC test", out);
@@ -249,7 +257,7 @@ static etest_status validate_hsic(const etest_hsic_request& h) {
     return set_error(ETEST_EINVAL, "gamma_x and gamma_y must be finite and > 0");
   if (!h.X || !h.Y) return set_error(ETEST_EINVAL, "X and Y must not be NULL");
   if (h.reserved != 0) return set_error(ETEST_EINVAL, "reserved field must be 0");
-  // the term pass launches one workgroup per (permutation, block of HSIC_RB rows)
+  // bound on the work of one call: (permutation, block of HSIC_RB rows) pairs
   const int64_t nblk = (h.n + HSIC_RB - 1) / HSIC_RB;
   if ((h.B + 1) > 2147483647LL / nblk)
     return set_error(ETEST_EINVAL, "HSIC test: (B + 1) * ceil(n / " + std::to_string(HSIC_RB) +

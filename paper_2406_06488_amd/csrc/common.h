@@ -43,7 +43,7 @@ constexpr int FLAG_COUNT = 4;        // int32 index of the 64-bit (count, finish
 constexpr int FLAG_WORDS = 8;
 constexpr int FLAG_XMAX = 6;         // FP32 form: bits of max |input| (a non-negative float)
 constexpr int HSIC_NMAX = 4096;      // HSIC test: largest n (one sort and one kernel row in LDS)
-constexpr int HSIC_RB = 8;           // HSIC test: rows of Kt per workgroup of the term pass
+constexpr int HSIC_RB = 8;           // HSIC test: rows per block in the bound on (B + 1) x blocks
 constexpr int PC_ROWS = 32;          // pre-computation test: tile rows per strip
 constexpr int PC_STRIPS = TILE / PC_ROWS;
 // Threads per workgroup of the kernels whose launch sizes the host checks.
