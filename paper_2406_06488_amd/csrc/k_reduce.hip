@@ -10,31 +10,23 @@
 
 namespace et {
 
-// Thread q < npad: same-sample part of position q; q >= npad: cross-sample part of
-// position q - npad.  One wave per workgroup so that the short grid spreads over the CUs.
-__global__ void __launch_bounds__(64) k_rowsum(const TestDesc* __restrict__ descs,
-                                               const int64_t* __restrict__ offs, int ntests) {
-  const int ti = find_test(offs, ntests, blockIdx.x);
-  const TestDesc d = descs[ti];
-  const int64_t npad = (int64_t)d.nt * TILE;
-  const int64_t q = (blockIdx.x - offs[ti]) * 64 + threadIdx.x;
-  if (q >= 2 * npad) return;
-  const bool cross = q >= npad;
-  const int64_t pos = cross ? q - npad : q;
+// Row sum of position `pos` (same-sample part, or cross-sample part) from the tile sums.
+template <bool F64>
+__device__ inline double row_part(const TestDesc& d, int64_t pos, bool cross) {
   const int i = (int)(pos / TILE), r = (int)(pos % TILE);
   const double* ts = d.tsum;
+  const int64_t stride = F64 ? d.tsum_stride : TSUM_STRIDE;
   const bool isx = i < d.tx;
   double s = 0.0;
-  // row sums of tile (i, j); column sums (two row halves) of tile (j, i)
-  // (FP64 form: row sums of two column halves, column sums of four row quarters)
-  const bool f64 = d.prec == PREC_F64;
+  // row sums of tile (i, j); column sums (two row halves) of tile (j, i); the FP64 form has
+  // row sums of two column halves, column sums of four row quarters
   auto rowsum = [&](int j) {
-    const double* t = ts + tile_index(i, j, d.nt) * d.tsum_stride;
-    return f64 ? t[r] + t[TILE + r] : t[r];
+    const double* t = ts + tile_index(i, j, d.nt) * stride;
+    return F64 ? t[r] + t[TILE + r] : t[r];
   };
   auto colsum = [&](int j) {
-    const double* t = ts + tile_index(j, i, d.nt) * d.tsum_stride;
-    return f64 ? (t[2 * TILE + r] + t[3 * TILE + r]) + (t[4 * TILE + r] + t[5 * TILE + r])
+    const double* t = ts + tile_index(j, i, d.nt) * stride;
+    return F64 ? (t[2 * TILE + r] + t[3 * TILE + r]) + (t[4 * TILE + r] + t[5 * TILE + r])
                : t[TILE + r] + t[2 * TILE + r];
   };
   // unrolled so that several tile sums are in flight; the additions stay in order of j
@@ -51,7 +43,22 @@ __global__ void __launch_bounds__(64) k_rowsum(const TestDesc* __restrict__ desc
 #pragma unroll 8
     for (int j = 0; j < d.tx; ++j) s += colsum(j);
   }
-  d.rsum[pos * 2 + (cross ? 1 : 0)] = s;
+  return s;
+}
+
+// Thread q < npad: same-sample part of position q; q >= npad: cross-sample part of
+// position q - npad.  One wave per workgroup so that the short grid spreads over the CUs.
+__global__ void __launch_bounds__(64) k_rowsum(const TestDesc* __restrict__ descs,
+                                               const int64_t* __restrict__ offs, int ntests) {
+  const int ti = find_test(offs, ntests, blockIdx.x);
+  const TestDesc d = descs[ti];
+  const int64_t npad = (int64_t)d.nt * TILE;
+  const int64_t q = (blockIdx.x - offs[ti]) * 64 + threadIdx.x;
+  if (q >= 2 * npad) return;
+  const bool cross = q >= npad;
+  const int64_t pos = cross ? q - npad : q;
+  d.rsum[pos * 2 + (cross ? 1 : 0)] =
+      d.prec == PREC_F64 ? row_part<true>(d, pos, cross) : row_part<false>(d, pos, cross);
 }
 
 constexpr int OBS_BATCH = 8;
