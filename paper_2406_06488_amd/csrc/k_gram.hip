@@ -170,12 +170,12 @@ __device__ inline void emit_half(const BlockOut& o, int half, const float* tl, f
 // once per entry, so no second set of values is held in registers).  put(half) writes rows
 // half*64 .. +63 of the tile into tl (row stride TILE_LDS) and is called between barriers;
 // fix(half, first) may then rewrite staged entries, each thread only those of its own
-// transform slots (f = tid + 256 k: row f / 128, column f % 128).  All 256 threads of the
-// workgroup take part.
+// transform slots (f = tid + 256 k: row f / 128, column f % 128).  tile_max_bits: two words of
+// LDS.  All 256 threads of the workgroup take part.
 template <bool D2, class Put, class Fix>
-__device__ __attribute__((always_inline)) inline void finish_tile_with(const TileCtx& c, float* tl, Put put, Fix fix,
+__device__ __attribute__((always_inline)) inline void finish_tile_with(const TileCtx& c, float* tl,
+                                        unsigned int* tile_max_bits, Put put, Fix fix,
                                         const BlockOut o0, const BlockOut o1, const bool has1) {
-  __shared__ unsigned int tile_max_bits[2];
   const int tid = threadIdx.x;
   float vmax0 = 0.0f, vmax1 = 0.0f;
   auto stage = [&](int half, bool first) __attribute__((always_inline)) {
@@ -232,9 +232,9 @@ __device__ __attribute__((always_inline)) inline void finish_tile_with(const Til
 // 128-tile workgroups: v[mb][nb][e] is the entry of row wm*64 + mb*32 + 8*(e/4) + 4*h + e%4,
 // column wn*64 + nb*32 + lr: the waves with wm == half hold half `half`.
 template <bool DUAL>
-__device__ inline void finish_tile(const TileCtx& c, float* tl, const f32x16 (&v)[2][2], int wm,
-                                   int wn, int h, int lr, const BlockOut o0, const BlockOut o1,
-                                   const bool has1) {
+__device__ inline void finish_tile(const TileCtx& c, float* tl, unsigned int* tile_max_bits,
+                                   const f32x16 (&v)[2][2], int wm, int wn, int h, int lr,
+                                   const BlockOut o0, const BlockOut o1, const bool has1) {
   auto put = [&](int half) {
     if (wm == half) {
 #pragma unroll
@@ -248,7 +248,7 @@ __device__ inline void finish_tile(const TileCtx& c, float* tl, const f32x16 (&v
           }
     }
   };
-  finish_tile_with<DUAL>(c, tl, put, [](int, bool) {}, o0, o1, has1);
+  finish_tile_with<DUAL>(c, tl, tile_max_bits, put, [](int, bool) {}, o0, o1, has1);
 }
 
 // Gram entry -> squared distance.  d^2 = |w_a|^2 + |w_b|^2 - 2 g; pairs with
@@ -295,10 +295,9 @@ __device__ inline void add_refined(const TestDesc& d, int refined) {
 // (VALUES false) or the test's own block values (VALUES true), in place.
 template <bool VALUES>
 __device__ inline void gram_epilogue(const TestDesc& d, const TileCtx& c, f32x16 (&acc)[2][2],
-                                     int wm, int wn, int h, int lr) {
-  // the tile's 128 row norms and 128 column norms, staged once instead of two global
-  // loads per entry
-  __shared__ float snorm[2 * TILE];
+                                     int wm, int wn, int h, int lr, float* snorm) {
+  // snorm (LDS): the tile's 128 row norms and 128 column norms, staged once instead of two
+  // global loads per entry
   const int tid = threadIdx.x;
   {
     const float* nrm = (const float*)d.nrm;
@@ -339,6 +338,8 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
   __shared__ __attribute__((aligned(16))) float smem[HALF * TILE_LDS > 2 * TILE * LDS_ROW_F16
                                                          ? HALF * TILE_LDS
                                                          : 2 * TILE * LDS_ROW_F16];
+  __shared__ float snorm[2 * TILE];
+  __shared__ unsigned int tile_max_bits[2];
   const int64_t bid = xcd_grouped(blockIdx.x, gridDim.x);
   const int ti = find_test(offs, ntests, bid);
   const TestDesc d = descs[ti];
@@ -417,13 +418,13 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
   // DUAL: launches that hold a test feeding an MMD test keep the squared distances for two
   // outputs; plain launches turn them into block values at once
   if (DUAL) {
-    gram_epilogue<false>(d, c, acc, wm, wn, h, lr);
-    finish_tile<true>(c, smem, acc, wm, wn, h, lr, own_out(d, c), partner_out(d, c),
-                      d.pD != nullptr);
+    gram_epilogue<false>(d, c, acc, wm, wn, h, lr, snorm);
+    finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
+                      partner_out(d, c), d.pD != nullptr);
   } else {
-    gram_epilogue<true>(d, c, acc, wm, wn, h, lr);
+    gram_epilogue<true>(d, c, acc, wm, wn, h, lr, snorm);
     const BlockOut o = own_out(d, c);
-    finish_tile<false>(c, smem, acc, wm, wn, h, lr, o, o, false);
+    finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
   }
 }
 
@@ -436,6 +437,8 @@ k_gram_bf16(const TestDesc* __restrict__ descs,
                                                    const int64_t* __restrict__ offs, int ntests) {
   __shared__ __attribute__((aligned(16))) float smem[HALF * TILE_LDS > TILE * LDS_ROW_BF16 ? HALF * TILE_LDS
                                                               : TILE * LDS_ROW_BF16];
+  __shared__ float snorm[2 * TILE];
+  __shared__ unsigned int tile_max_bits[2];
   const int64_t bid = xcd_grouped(blockIdx.x, gridDim.x);
   const int ti = find_test(offs, ntests, bid);
   const TestDesc d = descs[ti];
@@ -507,13 +510,271 @@ k_gram_bf16(const TestDesc* __restrict__ descs,
   // DUAL: launches that hold a test feeding an MMD test keep the squared distances for two
   // outputs; plain launches turn them into block values at once
   if (DUAL) {
-    gram_epilogue<false>(d, c, acc, wm, wn, h, lr);
-    finish_tile<true>(c, smem, acc, wm, wn, h, lr, own_out(d, c), partner_out(d, c),
-                      d.pD != nullptr);
+    gram_epilogue<false>(d, c, acc, wm, wn, h, lr, snorm);
+    finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
+                      partner_out(d, c), d.pD != nullptr);
   } else {
-    gram_epilogue<true>(d, c, acc, wm, wn, h, lr);
+    gram_epilogue<true>(d, c, acc, wm, wn, h, lr, snorm);
     const BlockOut o = own_out(d, c);
-    finish_tile<false>(c, smem, acc, wm, wn, h, lr, o, o, false);
+    finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
+  }
+}
+
+// --------------------------------------------------- small grids: operands by a deep LDS ring
+// Grids of at most one or two workgroups per CU wait on memory and on their own epilogue, not
+// on the matrix cores: with the register-staged kernels above (one slice ahead) a 32-wide slice
+// took 1.5-2.4 us there, against 0.3 us of products.  Here the operands go straight into LDS
+// (global_load_lds), four or five stages ahead: a stage is two 64-byte chunks of every row
+// (fp16 pairs: 32 coordinates; BF16: 64) and the ring takes most of a CU's LDS, so one
+// workgroup fills a CU, with two waves on every SIMD (2 x 4 waves of TR/2 x 32).  TR = 64: half
+// a stored tile (64 rows x 128 columns), which spreads the smallest grids over twice as many
+// CUs; TR = 128: a whole tile.  Chunk layout, swizzle and the order in which each entry's
+// products are added are the super-tile kernel's, and the sums keep the order of the 128-tile
+// kernels, so all shapes agree bit for bit.  Measured (FP32 form, register-staged kernel ->
+// ring): 10 tiles at p = 1000 51 -> 20 us, 256 tiles (cross test) at p = 1000 55 -> 38 us, 136
+// tiles at p = 500 38 -> 25 us.  With one wave per SIMD instead of two: 28, 46 and 33 us.
+constexpr int GR_THREADS = 512;
+template <bool F16, int TR>
+__global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __restrict__ descs,
+                                                          const int64_t* __restrict__ offs,
+                                                          int ntests) {
+  constexpr int MB = TR / 64;                    // 32-row blocks per wave
+  constexpr int NCH = 2;                         // chunks per stage
+  constexpr int NSTEP = NCH * (F16 ? 1 : 2);     // K steps of 16 per stage
+  constexpr int NPL = F16 ? 2 : 1;               // operand halves per K step (F16: hi, lo)
+  constexpr int NF = (TR + TILE) / 16;           // kilobyte loads per chunk
+  constexpr int CHP = NF * 64;                   // 16-byte pieces per chunk
+  constexpr int BUFP = NCH * CHP;                // pieces per stage
+  constexpr int NBUF = TR == TILE ? 5 : 6;       // 160 or 144 KB
+  constexpr int LOADS = NCH * NF / (GR_THREADS / 64);  // loads per wave and stage
+  constexpr int EPI = TR * TILE_LDS / 4;         // the epilogue's tile, in pieces
+  static_assert(EPI + 2 * TILE / 4 + 1 <= NBUF * BUFP, "the epilogue fits the ring");
+  __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * BUFP];
+  const int64_t u = blockIdx.x;
+  const int64_t bid = TR == TILE ? u : u >> 1;
+  const int half = TR == TILE ? 0 : (int)(u & 1);
+  const int ti_ = find_test(offs, ntests, bid);
+  const TestDesc& d = descs[ti_];
+  const TileCtx c = tile_ctx(d, bid - offs[ti_]);
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63,
+            h = lane >> 5, lr = lane & 31;
+  const int wm = w >> 2, wn = w & 3;
+  const int64_t nch = d.p_pad / (F16 ? 16 : 32);      // chunks per row, even
+  const int64_t tstride = nch * TILE * CHUNK_HALVES;  // halves per staged tile
+  const uint32_t lane_src = (uint32_t)(lane >> 2) * CHUNK_HALVES +
+                            (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 8);
+  const uint16_t* srcA = (const uint16_t*)d.W + c.i * tstride + half * HALF * CHUNK_HALVES + lane_src;
+  const uint16_t* srcB = (const uint16_t*)d.W + c.j * tstride + lane_src;
+  const int nst = (int)(nch / NCH);
+  // the epilogue's norms and scale, loaded ahead of everything else
+  float nreg = 0.0f;
+  if (tid < 2 * TILE)
+    nreg = ((const float*)d.nrm)[(int64_t)(tid < TILE ? c.i : c.j) * TILE + (tid & (TILE - 1))];
+  const float unscale = F16 ? ldexpf(1.0f, -2 * f16_split_exponent(d)) : 1.0f;
+  auto issue = [&](int st, int buf) {
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) {
+      const int g = w * LOADS + q, cc = g / NF, f = g % NF;
+      const uint16_t* src = f < TR / 16 ? srcA + f * (16 * CHUNK_HALVES)
+                                        : srcB + (f - TR / 16) * (16 * CHUNK_HALVES);
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)(src + (int64_t)(st * NCH + cc) *
+                                                                    (TILE * CHUNK_HALVES)),
+          (__attribute__((address_space(3))) void*)(lds + buf * BUFP + cc * CHP + f * 64), 16, 0, 0);
+    }
+  };
+  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+  const int sw = (lane >> 2) & 3;
+  const int rd0 = lr * 4 + (h ^ sw);        // piece h       (BF16 first step; F16 hi)
+  const int rd1 = lr * 4 + ((2 + h) ^ sw);  // piece 2 + h   (BF16 second step; F16 lo)
+  u32x4 ca[MB * NPL], cb[NPL], na[MB * NPL], nb[NPL];
+  auto read = [&](int buf, int ks, u32x4 (&fa)[MB * NPL], u32x4 (&fb)[NPL]) {
+    const uint4* base = lds + buf * BUFP + (F16 ? ks : ks >> 1) * CHP;
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl) {
+      const int rd = (F16 ? pl : ks & 1) ? rd1 : rd0;
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+        fa[pl * MB + m] = __builtin_bit_cast(u32x4, base[(wm * MB + m) * 128 + rd]);
+      fb[pl] = __builtin_bit_cast(u32x4, base[TR * 4 + wn * 128 + rd]);
+    }
+  };
+  f32x16 acc[MB];
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[a][e] = 0.0f;
+  // one K step's products; per accumulator the terms keep the order hi hi, hi lo, lo hi
+  auto mfma = [&]() {
+#pragma unroll
+    for (int term = 0; term < (F16 ? 3 : 1); ++term)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const u32x4 x = ca[(term == 2 ? MB : 0) + mb], y = cb[term == 1 ? 1 : 0];
+        if (F16)
+          acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+              __builtin_bit_cast(f16x8_t, x), __builtin_bit_cast(f16x8_t, y), acc[mb], 0, 0, 0);
+        else
+          acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              __builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), acc[mb], 0, 0, 0);
+      }
+  };
+  // this wave's own reads have completed and its loads of stage st have landed (those of up to
+  // NBUF - 2 later stages stay in flight); then everyone's
+  auto arrive = [&](int st) {
+    const int later = min(NBUF - 2, nst - 1 - st);
+    __builtin_amdgcn_sched_barrier(0);
+    // vmcnt in bits 3:0 and 15:14, expcnt not waited, lgkmcnt(0)
+#define GR_WAIT(N) \
+  __builtin_amdgcn_s_waitcnt(0x0070 | (((N) * LOADS) & 15) | ((((N) * LOADS) >> 4) << 14))
+    static_assert((NBUF - 2) * LOADS < 64, "vmcnt");
+    if (NBUF > 5 && later >= 4) GR_WAIT(NBUF > 5 ? 4 : 0);
+    else if (later >= 3) GR_WAIT(3);
+    else if (later == 2) GR_WAIT(2);
+    else if (later == 1) GR_WAIT(1);
+    else GR_WAIT(0);
+#undef GR_WAIT
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int q = 0; q < NBUF - 1; ++q)
+    if (q < nst) issue(q, q);
+  arrive(0);
+  read(0, 0, ca, cb);
+  int buf = 0;  // st % NBUF
+  for (int st = 0; st < nst; ++st) {
+    const int prev = buf == 0 ? NBUF - 1 : buf - 1, next = buf == NBUF - 1 ? 0 : buf + 1;
+    if (st + NBUF - 1 < nst) issue(st + NBUF - 1, prev);  // stage st - 1's, read by all
+#pragma unroll
+    for (int ks = 0; ks < NSTEP; ++ks) {
+      if (ks + 1 < NSTEP) {
+        read(buf, ks + 1, na, nb);
+      } else if (st + 1 < nst) {
+        arrive(st + 1);
+        read(next, 0, na, nb);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mfma();
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < MB * NPL; ++k) ca[k] = na[k];
+#pragma unroll
+      for (int k = 0; k < NPL; ++k) cb[k] = nb[k];
+    }
+    buf = next;
+  }
+  __syncthreads();  // the ring is free for the epilogue
+  // Epilogue: the Gram entries of all TR rows staged at once, block values formed in place,
+  // then the 128-tile kernels' sums and stores (emit_half) with the same additions in the same
+  // order, every LDS read of a sum issued first.
+  float* tl = (float*)lds;
+  float* snorm = tl + EPI * 4;
+  unsigned int* tile_max_bits = (unsigned int*)(snorm + 2 * TILE);
+  if (tid < 2 * TILE) snorm[tid] = nreg;
+  if (tid == 0) tile_max_bits[0] = 0u;
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      tl[(wm * (TR / 2) + mb * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * TILE_LDS + wn * 32 + lr] =
+          acc[mb][e] * unscale;
+  __syncthreads();
+  // Gram entries -> block values, four adjacent columns at a time, in a rolled loop: unrolled
+  // over a lane's accumulators (each with its near-pair path) the kernel was 72 KB of code,
+  // whose instruction fetches took longer than the products of a small grid.
+  int refined = 0;
+#pragma unroll 1
+  for (int f = tid; f < TR * TILE / 4; f += GR_THREADS) {
+    const int rl = f >> 5, c4 = 4 * (f & 31), r = half * HALF + rl;
+    float4* q = (float4*)(tl + rl * TILE_LDS + c4);
+    const float4 g = *q, n4 = *(const float4*)(snorm + TILE + c4);
+    const float gv[4] = {g.x, g.y, g.z, g.w}, nv[4] = {n4.x, n4.y, n4.z, n4.w}, nr = snorm[r];
+    float v[4];
+    uint32_t near = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = nr + nv[e] - 2.0f * gv[e];
+      if (needs_refine(d, c, r, c4 + e, v[e], nr, nv[e])) near |= 1u << e;
+    }
+    while (near) {
+      const int e = __builtin_ctz(near);
+      near &= near - 1u;
+      const float x = direct_d2(d, c, r, c4 + e);
+      v[0] = e == 0 ? x : v[0];
+      v[1] = e == 1 ? x : v[1];
+      v[2] = e == 2 ? x : v[2];
+      v[3] = e == 3 ? x : v[3];
+      ++refined;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = block_value_f32(d.kind, d.gamma, c, r, c4 + e, v[e]);
+    *q = make_float4(v[0], v[1], v[2], v[3]);
+  }
+  add_refined(d, refined);
+  __syncthreads();
+  const BlockOut o = own_out(d, c);
+  float vmax = 0.0f;
+  if (tid < 4 * TR) {  // row sums: four threads per row
+    const int q = tid & 3, rl = tid >> 2, r = half * HALF + rl;
+    float x[32];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float4 v = *(const float4*)(tl + rl * TILE_LDS + q * 32 + 4 * k);
+      x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+    }
+    // emit_half's order: thread q starts at its column q
+    double s0 = 0.0, s1 = 0.0;
+    auto add = [&](int k) {
+      if (o.split >= 0 && q * 32 + k >= o.split) s1 += (double)x[k];
+      else s0 += (double)x[k];
+      vmax = fmaxf(vmax, fabsf(x[k]));
+    };
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k >= q) add(k);
+#pragma unroll
+    for (int k = 3; k < 32; ++k) add(k);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (k < q) add(k);
+    s0 += __shfl_xor(s0, 1, 64);
+    s0 += __shfl_xor(s0, 2, 64);
+    if (q == 0) o.tsum[r] = s0;
+    if (o.split >= 0) {
+      s1 += __shfl_xor(s1, 1, 64);
+      s1 += __shfl_xor(s1, 2, 64);
+      if (q == 0) o.tsum[TILE + r] = s1;
+    }
+  }
+  if (o.split < 0) {
+    // column sums of each half: two threads per column in one wave
+    const int t = TR == TILE ? tid : tid - 4 * TR;  // TR = 64: the threads without a row
+    if (t >= 0) {
+      const int hf = t >> 8, col = ((t >> 6) & 3) * 32 + (t & 31), part = (t >> 5) & 1;
+      float x[32];
+#pragma unroll
+      for (int k = 0; k < 32; ++k) x[k] = tl[(hf * HALF + part * 32 + k) * TILE_LDS + col];
+      double s = 0.0;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) s += (double)x[k];
+      s += __shfl_xor(s, 32, 64);
+      if (part == 0) o.tsum[TILE * (1 + half + hf) + col] = s;
+    }
+    float4* dst = (float4*)(o.D + half * HALF * TILE);
+#pragma unroll
+    for (int k = 0; k < TR * TILE / 4 / GR_THREADS; ++k) {
+      const int f = tid + GR_THREADS * k;
+      dst[f] = *(const float4*)(tl + (f >> 5) * TILE_LDS + 4 * (f & 31));
+    }
+  }
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, 64));
+  if (lane == 0) atomicMax(tile_max_bits, __float_as_uint(vmax));
+  __syncthreads();
+  if (tid == 0) {
+    o.tmax[half] = __uint_as_float(tile_max_bits[0]);
+    if (TR == TILE) o.tmax[1] = 0.0f;
   }
 }
 
@@ -1085,6 +1346,12 @@ k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs,
   }
 }
 
+// Largest grids (stored tiles of all tests of the launch) for the ring kernels: one workgroup
+// per CU, of half tiles while two of them per tile still fit.  Past them the ring's workgroups
+// would go in two rounds of one per CU (272 tiles: 2 x 25 us at p = 500), where three
+// register-staged ones share a CU (45 us).
+constexpr int64_t GRAM_RING_MAX_HALVES = 128, GRAM_RING_MAX_TILES = 256;
+
 void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, const TestDesc* d,
                  const int64_t* offs, int n, bool dual) {
   if (blocks <= 0) return;
@@ -1101,6 +1368,16 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
     const int64_t units = blocks * DF_PARTS;
     hipLaunchKernelGGL(k_dist_f64, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
                        dim3(DF_THREADS), 0, st, d, offs, n, units);
+  } else if (!dual && blocks <= GRAM_RING_MAX_TILES) {
+    const dim3 rb(GR_THREADS);
+    if (blocks <= GRAM_RING_MAX_HALVES) {
+      const dim3 g2((unsigned)(2 * blocks));
+      if (gop == GOP_F16PAIR) hipLaunchKernelGGL((k_gram_ring<true, 64>), g2, rb, 0, st, d, offs, n);
+      else hipLaunchKernelGGL((k_gram_ring<false, 64>), g2, rb, 0, st, d, offs, n);
+    } else if (gop == GOP_F16PAIR)
+      hipLaunchKernelGGL((k_gram_ring<true, 128>), g, rb, 0, st, d, offs, n);
+    else
+      hipLaunchKernelGGL((k_gram_ring<false, 128>), g, rb, 0, st, d, offs, n);
   } else if (gop == GOP_F16PAIR && dual)
     hipLaunchKernelGGL(k_gram_f16x3<true>, g, b, 0, st, d, offs, n);
   else if (gop == GOP_F16PAIR)
