@@ -126,21 +126,36 @@ __global__ void __launch_bounds__(1024) k_count(const double* __restrict__ stats
 // With the dense pooled matrix (Alg. 5 as printed: every tile of the nt x nt grid, D_YX
 // included) every tile holds both orders of its pairs and takes the diagonal-tile rule: the
 // X*X*, Y*Y* and X*Y* sub-blocks are read entry by entry and the Y*X* entries are skipped.
-// Padding entries are 0.  One wave per (tile, 32-row strip, 64 splits): the strip sits in
-// LDS and every lane (one split) reads the same entry, selects it by its own column bit and
-// adds it in FP64.  No matrix product: this is the per-split extraction of Alg. 5.
-// The strip is held in LDS as FP64 (the stored FP32 entries converted once).  An entry is
-// selected by a fused multiply-add with the lane's column bit as 0.0 or 1.0, which adds it
-// exactly or leaves the sum as it is; the bits, fixed for the whole strip, are converted
-// once, so each entry costs one FMA.
+// Padding entries are 0.  One wave per (tile, 32-row strip, 64 splits): every entry of the
+// strip is multiplied by each split's column bit as 0.0 or 1.0, which adds it exactly or leaves
+// the sum as it is, and added in FP64 -- on v_mfma_f64_16x16x4f64, 2 row blocks x 4 column
+// blocks of 16 x 16; s_y is the row's total less s_x.  No centring and no quadratic form: this
+// is the per-split extraction of Alg. 5.  The lanes read their entries straight from the
+// stored tile (four adjacent columns each, FP32 entries converted once) and the waves of a
+// workgroup, 64 splits each, meet in the L1.  Bound by the FP64 MFMA rate; 211 us on the vector
+// ALU (one FMA per entry and split, one wave per SIMD) -> 34 us for 1000 + 1000 rows and 201
+// splits.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// four adjacent entries
+__device__ inline void load4(const float* p, double (&v)[4]) {
+  const float4 x = *(const float4*)p;
+  v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+}
+__device__ inline void load4(const double* p, double (&v)[4]) {
+  const double2 x = *(const double2*)p, y = *(const double2*)(p + 2);
+  v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+}
+
 template <typename T>
-__global__ void __launch_bounds__(64) k_precomp(const TestDesc* __restrict__ descs,
-                                                double* __restrict__ part, int64_t sg) {
-  __shared__ double Ds[PC_ROWS * TILE];
-  __shared__ double half_tot[PC_ROWS][2];
-  const TestDesc d = descs[0];
-  const int64_t g = blockIdx.x % sg;  // group of 64 split columns
-  const int64_t u = blockIdx.x / sg;  // strip u: tile u / PC_STRIPS, rows 32 (u % PC_STRIPS) ..
+__global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ descs,
+                                                 double* __restrict__ part, int64_t sg) {
+  const TestDesc& d = descs[0];
+  const int64_t sg4 = (sg + 3) / 4;  // groups of 64 split columns, four per workgroup
+  const int64_t id = xcd_grouped(blockIdx.x, gridDim.x);
+  const int64_t g = (id % sg4) * 4 + (threadIdx.x >> 6);
+  const int64_t u = id / sg4;  // strip u: tile u / PC_STRIPS, rows 32 (u % PC_STRIPS) ..
+  if (g >= sg) return;
   const int t = (int)(u / PC_STRIPS), h = (int)(u % PC_STRIPS);
   int i, j;
   if (d.dense) {
@@ -149,66 +164,92 @@ __global__ void __launch_bounds__(64) k_precomp(const TestDesc* __restrict__ des
   } else {
     tile_coords(t, d.nt, &i, &j);
   }
-  const int lane = threadIdx.x;
-  {  // the 32 x 128 strip: every 16-byte load of the lane in flight before the LDS stores
-    const uint4* src = (const uint4*)((const T*)d.D + (int64_t)t * TILE * TILE +
-                                      (int64_t)h * PC_ROWS * TILE);
-    constexpr int PER = 16 / sizeof(T);                  // entries per load
-    constexpr int NLD = PC_ROWS * TILE / PER / 64;       // loads per lane
-    uint4 v[NLD];
+  const int lane = threadIdx.x & 63, cl = lane & 15, kq = lane >> 4;
+  const int64_t BP = d.B_pad, col = g * 64 + cl;  // of column block 0; Z columns past B are 0
+  // the strip's rows cl and 16 + cl, columns 4 kq .. + 3 of every 16
+  const T* src = (const T*)d.D + (int64_t)t * TILE * TILE + (h * PC_ROWS + cl) * TILE + 4 * kq;
+  const uint32_t* Zj = d.Z + (int64_t)j * TILE_WORDS * BP + col;
+  f64x4 acc[2][4];
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) v[k] = src[lane + 64 * k];
+  for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const T* e = (const T*)&v[k];
+    for (int nb = 0; nb < 4; ++nb) acc[rb][nb] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // steps of 32 columns (one membership word), the next step's entries loaded ahead
+  double a[2][2][4], an[2][2][4];
+  uint32_t z[4], zn[4];
+  auto load = [&](int s, double (&x)[2][2][4], uint32_t (&y)[4]) {
 #pragma unroll
-      for (int q = 0; q < PER; ++q) Ds[(lane + 64 * k) * PER + q] = (double)e[q];
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) load4(src + rb * 16 * TILE + 32 * s + 16 * q, x[rb][q]);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) y[nb] = Zj[(int64_t)s * BP + 16 * nb];
+  };
+  auto multiply = [&](const double (&x)[2][2][4], const uint32_t (&y)[4]) {
+    // column 16 q + 4 kq + e of the step: bit 16 q + e of the shifted word
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+          const int bit = __builtin_amdgcn_sbfe((int)(y[nb] >> (4 * kq)), 16 * q + e, 1);
+          const double b = __hiloint2double(bit & 0x3FF00000, 0);
+#pragma unroll
+          for (int rb = 0; rb < 2; ++rb)
+            acc[rb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rb][q][e], b, acc[rb][nb], 0, 0, 0);
+        }
+  };
+  load(0, a, z);
+#pragma unroll 1
+  for (int s = 0; s < TILE_WORDS; s += 2) {
+    load(s + 1, an, zn);
+    multiply(a, z);
+    if (s + 2 < TILE_WORDS) load(s + 2, a, z);
+    multiply(an, zn);
+  }
+  // element e of an accumulator is row 16 rb + kq + 4 e of the strip, whose total the Gram left
+  const double* ts = d.tsum + (int64_t)t * d.tsum_stride + h * PC_ROWS + kq;
+  double tot[2][4];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double* p = ts + 16 * rb + 4 * e;
+      tot[rb][e] = sizeof(T) == 8 ? p[0] + p[TILE] : p[0];
     }
-  }
-  __syncthreads();
-  {  // row totals of the strip, two lanes per row, fixed order
-    const int r = lane >> 1, hf = lane & 1;
-    double s = 0.0;
-    for (int c = 0; c < TILE / 2; ++c) s += Ds[r * TILE + hf * (TILE / 2) + c];
-    half_tot[r][hf] = s;
-  }
-  __syncthreads();
-  const int64_t s = g * 64 + lane;  // < B_pad: Z columns past B hold no members
-  uint32_t zc[TILE_WORDS];
-#pragma unroll
-  for (int q = 0; q < TILE_WORDS; ++q) zc[q] = d.Z[(int64_t)(j * TILE_WORDS + q) * d.B_pad + s];
-  const uint32_t zr = d.Z[(int64_t)(i * TILE_WORDS + h) * d.B_pad + s];
   // a tile holding both orders of its pairs: a diagonal tile, or any tile of the dense matrix
   const bool both_orders = d.dense || i == j;
-  double wxx = 0.0, wyy = 0.0, wxy = 0.0;
-  for (int r = 0; r < PC_ROWS; ++r) {
-    const double* row = Ds + r * TILE;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+  double w[4][3];
 #pragma unroll
-    for (int c = 0; c < TILE; ++c)
-      a[c & 3] = fma(row[c], (double)((zc[c >> 5] >> (c & 31)) & 1u), a[c & 3]);
-    const double sx = (a[0] + a[1]) + (a[2] + a[3]);
-    const double sy = (half_tot[r][0] + half_tot[r][1]) - sx;
-    const bool member = (zr >> r) & 1u;
-    if (both_orders) {
-      if (member) {
-        wxx += sx;
-        wxy += sy;
-      } else {
-        wyy += sy;
+  for (int nb = 0; nb < 4; ++nb) {
+    const uint32_t zr = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col + 16 * nb] >> kq;
+    double wxx = 0.0, wyy = 0.0, wxy = 0.0;
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double sx = acc[rb][nb][e], sy = tot[rb][e] - sx;
+        const bool member = (zr >> (16 * rb + 4 * e)) & 1u;
+        wxx += member ? sx : 0.0;
+        wyy += member ? 0.0 : sy;
+        wxy += member ? sy : both_orders ? 0.0 : sx;
       }
-    } else if (member) {
-      wxx += 2.0 * sx;
-      wxy += sy;
-    } else {
-      wxy += sx;
-      wyy += 2.0 * sy;
+    const double scale = both_orders ? 1.0 : 2.0;
+    w[nb][0] = scale * wxx;
+    w[nb][1] = scale * wyy;
+    w[nb][2] = wxy;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      w[nb][k] += __shfl_xor(w[nb][k], 16, 64);
+      w[nb][k] += __shfl_xor(w[nb][k], 32, 64);
     }
   }
+  const int64_t s = col + 16 * kq;  // this lane writes column block kq
   if (s <= d.B) {
-    part[(u * 3 + 0) * d.B_pad + s] = wxx;
-    part[(u * 3 + 1) * d.B_pad + s] = wyy;
-    part[(u * 3 + 2) * d.B_pad + s] = wxy;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      part[(u * 3 + k) * BP + s] = kq == 0 ? w[0][k] : kq == 1 ? w[1][k] : kq == 2 ? w[2][k] : w[3][k];
   }
 }
 
@@ -223,26 +264,33 @@ struct Csum2 {  // Neumaier-compensated sum
   __device__ double value() const { return s + c; }
 };
 
-// Statistics of 64 split columns per workgroup: 16 groups of waves each take every 16th
-// strip (compensated sums), then wave 0 adds the 16 group sums in order.
-constexpr int PCS_GROUPS = 16;
-__global__ void __launch_bounds__(64 * PCS_GROUPS) k_precomp_stat(const TestDesc* __restrict__ descs,
-                                                                  const double* __restrict__ part,
-                                                                  int64_t nstrips,
-                                                                  double* __restrict__ stats) {
-  __shared__ double red[3][PCS_GROUPS][64];
-  const TestDesc d = descs[0];
-  const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int64_t s = (int64_t)blockIdx.x * 64 + c;  // < B_pad
+// Statistics of 16 split columns per workgroup: 64 groups of lanes each take every 64th strip
+// (compensated sums, the loads of two strips together), then the first adds the group sums in
+// order (64 columns in 16 groups left 34 strips in turn to each lane of 4 workgroups: 16 us
+// for 136 tiles, 10 us now).
+constexpr int PCS_COLS = 16, PCS_GROUPS = 64;
+__global__ void __launch_bounds__(PCS_COLS * PCS_GROUPS) k_precomp_stat(
+    const TestDesc* __restrict__ descs, const double* __restrict__ part, int64_t nstrips,
+    double* __restrict__ stats) {
+  __shared__ double red[3][PCS_GROUPS][PCS_COLS];
+  const TestDesc& d = descs[0];
+  const int c = threadIdx.x % PCS_COLS, g = threadIdx.x / PCS_COLS;
+  const int64_t s = (int64_t)blockIdx.x * PCS_COLS + c, BP = d.B_pad;  // s < B_pad
   Csum2 acc[3];
-  for (int64_t u = g; u < nstrips; u += PCS_GROUPS)
+#pragma unroll 2
+  for (int64_t u = g; u < nstrips; u += PCS_GROUPS) {
+    double x[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) acc[k].add(part[(u * 3 + k) * d.B_pad + s]);
+    for (int k = 0; k < 3; ++k) x[k] = part[(u * 3 + k) * BP + s];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) acc[k].add(x[k]);
+  }
 #pragma unroll
   for (int k = 0; k < 3; ++k) red[k][g][c] = acc[k].value();
   __syncthreads();
   if (g != 0 || s > d.B) return;
   Csum2 w[3];
+#pragma unroll 4
   for (int q = 0; q < PCS_GROUPS; ++q)
 #pragma unroll
     for (int k = 0; k < 3; ++k) w[k].add(red[k][q][c]);
@@ -273,16 +321,14 @@ void launch_count(const double* stats, int64_t B, const int32_t* flags, double* 
 void launch_precomp(bool f64, const TestDesc* d, int64_t ntiles, int64_t B, double* part,
                     hipStream_t st) {
   const int64_t sg = (B + 1 + 63) / 64;
-  const int64_t blocks = ntiles * PC_STRIPS * sg;
-  if (f64)
-    hipLaunchKernelGGL(k_precomp<double>, dim3((unsigned)blocks), dim3(64), 0, st, d, part, sg);
-  else
-    hipLaunchKernelGGL(k_precomp<float>, dim3((unsigned)blocks), dim3(64), 0, st, d, part, sg);
+  const dim3 grid((unsigned)(ntiles * PC_STRIPS * ((sg + 3) / 4)));
+  if (f64) hipLaunchKernelGGL(k_precomp<double>, grid, dim3(256), 0, st, d, part, sg);
+  else hipLaunchKernelGGL(k_precomp<float>, grid, dim3(256), 0, st, d, part, sg);
 }
 void launch_precomp_stat(const TestDesc* d, int64_t ntiles, int64_t B, const double* part,
                          double* stats, hipStream_t st) {
-  hipLaunchKernelGGL(k_precomp_stat, dim3((unsigned)((B + 1 + 63) / 64)), dim3(64 * PCS_GROUPS), 0,
-                     st, d, part, ntiles * PC_STRIPS, stats);
+  hipLaunchKernelGGL(k_precomp_stat, dim3((unsigned)((B + PCS_COLS) / PCS_COLS)),
+                     dim3(PCS_COLS * PCS_GROUPS), 0, st, d, part, ntiles * PC_STRIPS, stats);
 }
 
 }  // namespace et

@@ -57,3 +57,21 @@ def test_resampling_edges(nx, ny, B, kind):
     got = api.run(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), B, 3, kind, "f64", 0.2)
     want = oracle.run_test(X, Y, B, 3, api.KINDS[kind], 0.2)
     compare_run(got, want, "f64")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("nx,ny,B", [(1, 1, 1), (31, 33, 63), (129, 100, 64), (200, 260, 257)])
+def test_precomputed_edges(nx, ny, B, dense, prec):
+    """Per-split entry sums at the edges of 32-row strips and groups of 64 splits."""
+    import torch
+
+    import oracle
+    from tests.gpu_helpers import compare_run
+    g = np.random.Generator(np.random.PCG64(nx + 3 * ny + B))
+    dt = np.float64 if prec == "f64" else np.float32
+    X = g.standard_normal((nx, 5)).astype(dt)
+    Y = (g.standard_normal((ny, 5)) + 0.3).astype(dt)
+    got = api.precomputed(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), B, 3, "ed", prec,
+                          dense=dense)
+    compare_run(got, oracle.run_test(X.astype(np.float64), Y.astype(np.float64), B, 3), prec)
