@@ -166,6 +166,10 @@ struct TestDesc {
   // increasing order, then y* items), so one split's X* and Y* are staged without copying
   // the data; NULL reads the items in their own order.
   const int32_t* rowmap;
+  // Standard permutation test, recomputations: W and nrm hold the pooled rows staged once, in
+  // their own order; the Gram reads position t's row through the row map (staged_row) and
+  // keeps the tile sums only (D is NULL).
+  int32_t gather;
 };
 
 // Input row t of the pooled sample, in staging order: x rows then y rows (through the
@@ -184,6 +188,15 @@ __device__ inline const T* pooled_row(const TestDesc& d, int64_t t) {
   t -= d.cny1;
   if (t < d.cnx2) return X + (d.cnx1 + t) * d.p;
   return Y + (d.cny1 + t - d.cnx2) * d.p;
+}
+
+// Staged row of row r of pooled tile i of a test whose rows were staged once in their own order
+// (TestDesc::gather); rows past the tile's end read its first row's.
+__device__ inline int64_t staged_row(const TestDesc& d, int i, int rows_i, int r) {
+  if (r >= rows_i) r = 0;
+  const int64_t t = i < d.tx ? (int64_t)i * TILE + r : d.nx + (int64_t)(i - d.tx) * TILE + r;
+  const int64_t item = d.rowmap[t];
+  return item < d.nx ? item : (int64_t)d.tx * TILE + (item - d.nx);
 }
 
 // Workgroups of a launch are dealt to the 8 XCDs in turn (workgroup b on XCD b % 8), and

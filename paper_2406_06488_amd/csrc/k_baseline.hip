@@ -62,6 +62,16 @@ __global__ void __launch_bounds__(256) k_rowmap(const uint32_t* __restrict__ wor
   }
 }
 
+// Flag words of m recomputations: the staging's non-finite flag and input maximum, the rest 0.
+__global__ void k_sum_flags(const TestDesc* __restrict__ descs, int m,
+                            const int32_t* __restrict__ staged) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= m) return;
+  int32_t* f = descs[k].flags;
+#pragma unroll
+  for (int w = 0; w < FLAG_WORDS; ++w) f[w] = w == 0 || w == FLAG_XMAX ? staged[w] : 0;
+}
+
 // Statistic of each recomputed test (its observed statistic, eq. 1 / eq. 2) into the list
 // of split statistics; the identity split's refined-pair count; non-finite input.
 __global__ void k_collect(const TestDesc* __restrict__ descs, int m, int64_t c0, int64_t B,
@@ -306,6 +316,11 @@ void launch_rowmap(const uint32_t* words, int64_t count, int64_t maps, int64_t n
   if (maps > 0)
     hipLaunchKernelGGL(k_rowmap, dim3((unsigned)maps), dim3(256), 0, st, words, count, n, nx,
                        rowmap);
+}
+void launch_sum_flags(const TestDesc* d, int m, const int32_t* staged, hipStream_t st) {
+  if (m > 0)
+    hipLaunchKernelGGL(k_sum_flags, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st, d, m,
+                       staged);
 }
 void launch_collect(const TestDesc* d, int m, int64_t c0, int64_t B, double* stats,
                     int32_t* flags, hipStream_t st) {

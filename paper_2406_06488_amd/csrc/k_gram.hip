@@ -84,7 +84,7 @@ __device__ inline int cross_split(const TestDesc& d, int j) {
 __device__ inline BlockOut own_out(const TestDesc& d, const TileCtx& c) {
   const int64_t t = c.t;
   return BlockOut{d.kind, d.cross ? cross_split(d, c.j) : -1, d.gamma,
-                  d.cross ? nullptr : (float*)d.D + t * TILE * TILE,
+                  d.cross || !d.D ? nullptr : (float*)d.D + t * TILE * TILE,
                   d.tsum + t * d.tsum_stride, d.tmax + t * TMAX_PER_TILE};
 }
 __device__ inline BlockOut partner_out(const TestDesc& d, const TileCtx& c) {
@@ -155,6 +155,7 @@ __device__ inline void emit_half(const BlockOut& o, int half, const float* tl, f
     s += __shfl_xor(s, 32, 64);
     if (part == 0) o.tsum[TILE * (1 + half) + col] = s;
   }
+  if (!o.D) return;  // only the sums are kept
   float4* dst = (float4*)(o.D + half * HALF * TILE);
 #pragma unroll
   for (int k = 0; k < HALF * TILE / 4 / 256; ++k) {
@@ -293,7 +294,7 @@ __device__ inline void add_refined(const TestDesc& d, int refined) {
 
 // Gram entries of a full-tile workgroup (2 x 2 waves of 64 x 64) -> squared distances
 // (VALUES false) or the test's own block values (VALUES true), in place.
-template <bool VALUES>
+template <bool VALUES, bool GATHER = false>
 __device__ inline void gram_epilogue(const TestDesc& d, const TileCtx& c, f32x16 (&acc)[2][2],
                                      int wm, int wn, int h, int lr, float* snorm) {
   // snorm (LDS): the tile's 128 row norms and 128 column norms, staged once instead of two
@@ -301,7 +302,9 @@ __device__ inline void gram_epilogue(const TestDesc& d, const TileCtx& c, f32x16
   const int tid = threadIdx.x;
   {
     const float* nrm = (const float*)d.nrm;
-    snorm[tid] = nrm[(int64_t)(tid < TILE ? c.i : c.j) * TILE + (tid & (TILE - 1))];
+    const int i = tid < TILE ? c.i : c.j, r = tid & (TILE - 1);
+    snorm[tid] = nrm[GATHER ? staged_row(d, i, tid < TILE ? c.rows_i : c.rows_j, r)
+                            : (int64_t)i * TILE + r];
   }
   __syncthreads();
   int refined = 0;
@@ -332,7 +335,8 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 constexpr int KS16 = 32;                // pairs per K slice
 constexpr int LDS_ROW_F16 = KS16 + 8;   // halves per LDS row (80 bytes)
 
-template <bool DUAL>
+// GATHER: rows staged once in their own order (standard test), read through the row map.
+template <bool DUAL, bool GATHER = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests) {
   __shared__ __attribute__((aligned(16))) float smem[HALF * TILE_LDS > 2 * TILE * LDS_ROW_F16
@@ -363,9 +367,22 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
   // owns rows (tid >> 2) + 64 s, coordinates c8 .. c8 + 7 of the slice (chunk c8 / 16), hi
   // ([s][0]) and lo ([s][1])
   const int lrow = tid >> 2, c8 = (tid & 3) * 8;
-  const uint16_t* ga = Wa + ((c8 >> 4) * TILE + lrow) * CHUNK_HALVES + (c8 & 15);
-  const uint16_t* gb = Wb + ((c8 >> 4) * TILE + lrow) * CHUNK_HALVES + (c8 & 15);
-  const int64_t rstep = (int64_t)64 * CHUNK_HALVES;
+  const int coff = (c8 >> 4) * TILE * CHUNK_HALVES + (c8 & 15);
+  const uint16_t* ga[2];
+  const uint16_t* gb[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int r = lrow + 64 * s;
+    if (GATHER) {
+      const int64_t ra = staged_row(d, c.i, c.rows_i, r), rb = staged_row(d, c.j, c.rows_j, r);
+      const uint16_t* W = (const uint16_t*)d.W;
+      ga[s] = W + (ra / TILE * 2 * d.p_pad) * TILE + (ra % TILE) * CHUNK_HALVES + coff;
+      gb[s] = W + (rb / TILE * 2 * d.p_pad) * TILE + (rb % TILE) * CHUNK_HALVES + coff;
+    } else {
+      ga[s] = Wa + r * CHUNK_HALVES + coff;
+      gb[s] = Wb + r * CHUNK_HALVES + coff;
+    }
+  }
   uint4 pa[2][2], pb[2][2];
   // slice k0 starts at chunk k0 / 16, i.e. 2 k0 TILE halves on
   auto load = [&](int k0) {
@@ -373,8 +390,8 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int pl = 0; pl < 2; ++pl) {
-        pa[s][pl] = gload16(ga + (int64_t)k0 * 2 * TILE + pl * 16 + s * rstep);
-        pb[s][pl] = gload16(gb + (int64_t)k0 * 2 * TILE + pl * 16 + s * rstep);
+        pa[s][pl] = gload16(ga[s] + (int64_t)k0 * 2 * TILE + pl * 16);
+        pb[s][pl] = gload16(gb[s] + (int64_t)k0 * 2 * TILE + pl * 16);
       }
   };
   load(0);
@@ -422,7 +439,7 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
     finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
                       partner_out(d, c), d.pD != nullptr);
   } else {
-    gram_epilogue<true>(d, c, acc, wm, wn, h, lr, snorm);
+    gram_epilogue<true, GATHER>(d, c, acc, wm, wn, h, lr, snorm);
     const BlockOut o = own_out(d, c);
     finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
   }
@@ -431,7 +448,7 @@ k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ off
 // ---------------------------------------------------------------- BF16 MFMA
 // Same arrangement with v_mfma_f32_32x32x16_bf16; pairs whose Gram-based d^2
 // falls below 1e-3 of the norm sum are recomputed from the FP32 input rows.
-template <bool DUAL>
+template <bool DUAL, bool GATHER = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_gram_bf16(const TestDesc* __restrict__ descs,
                                                    const int64_t* __restrict__ offs, int ntests) {
@@ -461,13 +478,26 @@ k_gram_bf16(const TestDesc* __restrict__ descs,
   // wave's load covers 8 rows of both chunks, two contiguous 512-byte runs.  The next slice
   // is loaded into registers while the current one is multiplied.
   const int lrow = tid >> 3, c8 = (tid & 7) * 8;
-  const uint16_t* ga = Wa + ((c8 >> 5) * TILE + lrow) * CHUNK_HALVES + (c8 & 31);
-  const uint16_t* gb = Wb + ((c8 >> 5) * TILE + lrow) * CHUNK_HALVES + (c8 & 31);
-  const int64_t rstep = (int64_t)32 * CHUNK_HALVES;
-  uint4 pa0 = gload16(ga), pa1 = gload16(ga + rstep);
-  uint4 pa2 = gload16(ga + 2 * rstep), pa3 = gload16(ga + 3 * rstep);
-  uint4 pb0 = gload16(gb), pb1 = gload16(gb + rstep);
-  uint4 pb2 = gload16(gb + 2 * rstep), pb3 = gload16(gb + 3 * rstep);
+  const int coff = (c8 >> 5) * TILE * CHUNK_HALVES + (c8 & 31);
+  const uint16_t* ga[4];
+  const uint16_t* gb[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int r = lrow + 32 * s;
+    if (GATHER) {
+      const int64_t ra = staged_row(d, c.i, c.rows_i, r), rb = staged_row(d, c.j, c.rows_j, r);
+      const uint16_t* W = (const uint16_t*)d.W;
+      ga[s] = W + (ra / TILE * d.p_pad) * TILE + (ra % TILE) * CHUNK_HALVES + coff;
+      gb[s] = W + (rb / TILE * d.p_pad) * TILE + (rb % TILE) * CHUNK_HALVES + coff;
+    } else {
+      ga[s] = Wa + r * CHUNK_HALVES + coff;
+      gb[s] = Wb + r * CHUNK_HALVES + coff;
+    }
+  }
+  uint4 pa0 = gload16(ga[0]), pa1 = gload16(ga[1]);
+  uint4 pa2 = gload16(ga[2]), pa3 = gload16(ga[3]);
+  uint4 pb0 = gload16(gb[0]), pb1 = gload16(gb[1]);
+  uint4 pb2 = gload16(gb[2]), pb3 = gload16(gb[3]);
   for (int k0 = 0; k0 < d.p_pad; k0 += 64) {
     __syncthreads();
     uint16_t* la = As + lrow * LDS_ROW_BF16 + c8;
@@ -483,16 +513,15 @@ k_gram_bf16(const TestDesc* __restrict__ descs,
     __syncthreads();
     if (k0 + 64 < d.p_pad) {
       // slice k0 + 64 starts at chunk (k0 + 64) / 32, i.e. (k0 + 64) * TILE halves on
-      const uint16_t* na = ga + (int64_t)(k0 + 64) * TILE;
-      const uint16_t* nb2 = gb + (int64_t)(k0 + 64) * TILE;
-      pa0 = gload16(na);
-      pa1 = gload16(na + rstep);
-      pa2 = gload16(na + 2 * rstep);
-      pa3 = gload16(na + 3 * rstep);
-      pb0 = gload16(nb2);
-      pb1 = gload16(nb2 + rstep);
-      pb2 = gload16(nb2 + 2 * rstep);
-      pb3 = gload16(nb2 + 3 * rstep);
+      const int64_t ko = (int64_t)(k0 + 64) * TILE;
+      pa0 = gload16(ga[0] + ko);
+      pa1 = gload16(ga[1] + ko);
+      pa2 = gload16(ga[2] + ko);
+      pa3 = gload16(ga[3] + ko);
+      pb0 = gload16(gb[0] + ko);
+      pb1 = gload16(gb[1] + ko);
+      pb2 = gload16(gb[2] + ko);
+      pb3 = gload16(gb[3] + ko);
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -514,7 +543,7 @@ k_gram_bf16(const TestDesc* __restrict__ descs,
     finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
                       partner_out(d, c), d.pD != nullptr);
   } else {
-    gram_epilogue<true>(d, c, acc, wm, wn, h, lr, snorm);
+    gram_epilogue<true, GATHER>(d, c, acc, wm, wn, h, lr, snorm);
     const BlockOut o = own_out(d, c);
     finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
   }
@@ -1190,7 +1219,7 @@ __device__ inline void dist_emit_f64(const TestDesc& d, const TileCtx& c, int r0
     if (r >= c.rows_i || cc >= c.rows_j) x = 0.0;
     else if (c.diag && r == cc) x = d.kind == KIND_ED ? 0.0 : 1.0;
     else x = d.kind == KIND_ED ? sqrt(v[b]) : exp(-d.gamma * v[b]);
-    if (split < 0) ((double*)d.D)[(int64_t)c.t * TILE * TILE + r * TILE + cc] = x;
+    if (split < 0 && d.D) ((double*)d.D)[(int64_t)c.t * TILE * TILE + r * TILE + cc] = x;
     if (split >= 0 && cc >= split) s1 += x;
     else s0 += x;
     col[b] = x;
@@ -1214,6 +1243,8 @@ __device__ inline void dist_emit_f64(const TestDesc& d, const TileCtx& c, int r0
   }
 }
 
+// GATHER: rows staged once in their own order (standard test), read through the row map.
+template <bool GATHER>
 __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int part, double* sm) {
   constexpr int NLD = DF_BUF * 8 / 1024 / (DF_THREADS / 64);  // kilobyte loads per wave
   const int rq = part >> 1, ch = part & 1;
@@ -1228,6 +1259,17 @@ __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int pa
   // columns); this lane fills slot lane % 16 of row 4 f + lane / 16.
   const int row4 = lane >> 4;
   const int pk0 = 2 * ((lane & 15) ^ row4), pk1 = 2 * ((lane & 15) ^ (4 + row4));  // f even, odd
+  const double* grow[GATHER ? NLD : 1];
+  if (GATHER) {
+#pragma unroll
+    for (int q = 0; q < NLD; ++q) {
+      const int row = 4 * (NLD * w + q) + row4;
+      grow[GATHER ? q : 0] =
+          (const double*)d.W + (row < DF_ROWS ? staged_row(d, c.i, c.rows_i, r0 + row)
+                                              : staged_row(d, c.j, c.rows_j, c0 + row - DF_ROWS)) *
+                                   d.p_pad;
+    }
+  }
   auto issue = [&](int round) {
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
@@ -1237,7 +1279,8 @@ __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int pa
       // pieces past the row's end (never multiplied) read its last piece instead
       const int k = min(round * DF_K + ((f & 1) ? pk1 : pk0), nk - 2);
       __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(src + (uint32_t)(row4 * d.p_pad + k)),
+          (const __attribute__((address_space(1))) void*)(GATHER ? grow[q] + k
+                                                                 : src + (uint32_t)(row4 * d.p_pad + k)),
           (__attribute__((address_space(3))) void*)(sm + (round % DF_NBUF) * DF_BUF + f * 128),
           16, 0, 0);
     }
@@ -1331,6 +1374,7 @@ __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int pa
 
 // DF_PARTS units per stored tile; a grid smaller than the `units` of all tests (one dispatch
 // holds fewer than 2^32 work-items) strides over them.
+template <bool GATHER>
 __global__ void __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests,
            int64_t units) {
@@ -1341,7 +1385,7 @@ k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs,
     const int64_t bid = u / DF_PARTS;
     const int ti = find_test(offs, ntests, bid);
     const TestDesc& d = descs[ti];
-    dist_part_f64(d, tile_ctx(d, bid - offs[ti]), (int)(u % DF_PARTS), sm);
+    dist_part_f64<GATHER>(d, tile_ctx(d, bid - offs[ti]), (int)(u % DF_PARTS), sm);
     __syncthreads();  // the next unit's loads reuse the buffers
   }
 }
@@ -1366,7 +1410,7 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
   if (gop == GOP_F64) {
     // the launch table counts stored tiles
     const int64_t units = blocks * DF_PARTS;
-    hipLaunchKernelGGL(k_dist_f64, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
+    hipLaunchKernelGGL(k_dist_f64<false>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
                        dim3(DF_THREADS), 0, st, d, offs, n, units);
   } else if (!dual && blocks <= GRAM_RING_MAX_TILES) {
     const dim3 rb(GR_THREADS);
@@ -1386,6 +1430,21 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
     hipLaunchKernelGGL(k_gram_bf16<true>, g, b, 0, st, d, offs, n);
   else
     hipLaunchKernelGGL(k_gram_bf16<false>, g, b, 0, st, d, offs, n);
+}
+
+// Tile sums of recomputations that share one staging (TestDesc::gather): `blocks` stored tiles.
+void launch_gram_sums(int gop, int64_t blocks, hipStream_t st, const TestDesc* d,
+                      const int64_t* offs, int n) {
+  if (blocks <= 0) return;
+  const dim3 g((unsigned)blocks), b(256);
+  const int64_t units = blocks * DF_PARTS;
+  if (gop == GOP_F64)
+    hipLaunchKernelGGL(k_dist_f64<true>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
+                       dim3(DF_THREADS), 0, st, d, offs, n, units);
+  else if (gop == GOP_F16PAIR)
+    hipLaunchKernelGGL((k_gram_f16x3<false, true>), g, b, 0, st, d, offs, n);
+  else
+    hipLaunchKernelGGL((k_gram_bf16<false, true>), g, b, 0, st, d, offs, n);
 }
 
 void launch_gram_finish(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs,

@@ -212,7 +212,9 @@ TestPlan make_plan(const etest_request& r, int64_t kc_override, int mode) {
     sz[B_PLANES] = 0;
     sz[B_PART] = 0;
     sz[B_PSTAT] = 0;
-    if (mode == PLAN_BLOCKS) sz[B_Z] = 0;
+    if (!precomp) sz[B_Z] = 0;
+    if (mode == PLAN_STAGE) sz[B_D] = sz[B_TSUM] = sz[B_TMAX] = sz[B_RSUM] = 0;
+    if (mode == PLAN_SUMS) sz[B_D] = sz[B_COLPART] = sz[B_COLMEAN] = sz[B_W] = sz[B_NRM] = 0;
     if (precomp) {
       sz[B_PART] = (size_t)d.ntiles * PC_STRIPS * 3 * d.B_pad * 8;
       sz[B_PSTAT] = (size_t)d.B_pad * 8;
@@ -232,7 +234,9 @@ TestPlan make_plan(const etest_request& r, int64_t kc_override, int mode) {
   P.wg[S_COLMEAN] = f32like ? (r.p + 63) / 64 : 0;
   P.wg[S_STAGE] = stage_wgs(npad, d.p_pad);
   // the dense grid keeps one 128-tile workgroup per tile
-  d.gshape = d.dense ? GSHAPE_TILE : gram_shape(r, d.nt);
+  // (and the recomputations of the standard test, whose rows are read through a row map)
+  d.gshape = d.dense || mode == PLAN_SUMS ? GSHAPE_TILE : gram_shape(r, d.nt);
+  d.gather = mode == PLAN_SUMS ? 1 : 0;
   const bool sup = d.gshape == GSHAPE_SUPER;
   P.wg[S_GRAM_F64] = f64 ? d.ntiles : 0;
   P.wg[S_GRAM_F32] = d.gop == GOP_F16PAIR && !sup ? d.ntiles : 0;
@@ -254,7 +258,12 @@ TestPlan make_plan(const etest_request& r, int64_t kc_override, int mode) {
   if (mode != PLAN_EFFICIENT)
     for (int k : {S_CENTER_F64, S_CENTER_SPLIT, S_PERM_F64, S_PERM_S2, S_PERM_S3, S_PSTAT})
       P.wg[k] = 0;
-  if (mode == PLAN_BLOCKS) P.wg[S_MEMBER] = 0;
+  if (mode != PLAN_EFFICIENT && !precomp) P.wg[S_MEMBER] = 0;
+  if (mode == PLAN_STAGE) {
+    for (int k : GRAM_SLOTS) P.wg[k] = 0;
+    P.wg[S_ROWSUM] = 0;
+  }
+  if (mode == PLAN_SUMS) P.wg[S_COLPART] = P.wg[S_COLMEAN] = P.wg[S_STAGE] = 0;
   if (precomp) P.wg[S_ROWSUM] = 0;
   return P;
 }
@@ -384,7 +393,11 @@ void assign_pointers(TestPlan& P, char* r, DevResult* result) {
   d.colmean = (double*)(r + P.off[B_COLMEAN]);
   d.W = r + P.off[B_W];
   d.nrm = r + P.off[B_NRM];
-  d.D = r + P.off[B_D];
+  d.D = P.staged ? nullptr : r + P.off[B_D];
+  if (P.staged) {
+    d.W = P.staged->W;
+    d.nrm = P.staged->nrm;
+  }
   d.tsum = (double*)(r + P.off[B_TSUM]);
   d.tsum_stride = TSUM_STRIDE;
   if (d.prec == PREC_F64) {

@@ -23,6 +23,8 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
                  const int64_t* offs, int n, bool dual = false);
 void launch_gram_finish(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs,
                         int n, bool dual);
+void launch_gram_sums(int gop, int64_t blocks, hipStream_t st, const TestDesc* d,
+                      const int64_t* offs, int n);
 void launch_rowsum(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs, int n);
 void launch_observed(hipStream_t st, const TestDesc* d, const int64_t* sel, int n);
 void launch_center(bool f64, int64_t blocks, hipStream_t st, const TestDesc* d,
@@ -41,6 +43,7 @@ void launch_perm(int variant, int64_t blocks, hipStream_t st, const TestDesc* d,
 void launch_pstat(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs, int n);
 void launch_rowmap(const uint32_t* words, int64_t count, int64_t maps, int64_t n, int64_t nx,
                    int32_t* rowmap, hipStream_t st);
+void launch_sum_flags(const TestDesc* d, int m, const int32_t* staged, hipStream_t st);
 void launch_collect(const TestDesc* d, int m, int64_t c0, int64_t B, double* stats,
                     int32_t* flags, hipStream_t st);
 void launch_count(const double* stats, int64_t B, const int32_t* flags, double* perm_out,
@@ -108,6 +111,7 @@ struct TestPlan {
   bool internal_perm = false;  // per-split output lives in the region (off[B_PERMOUT])
   int partner = -1;          // ED test: index of the MMD test whose blocks its Gram writes
   bool share_z = false;      // ... and whose split stream it provides
+  const TestDesc* staged = nullptr;  // PLAN_SUMS: the test whose W and nrm it reads
   int64_t wg[S_COUNT] = {};  // workgroups per launch slot
 };
 
@@ -127,7 +131,10 @@ etest_status check_launch_sizes(const TestPlan* plans, size_t n);
 // the standard test); pooled blocks, split stream and the pre-computation test's buffers.
 // PLAN_PRECOMP: the pre-computation test on the symmetric upper tiles; PLAN_PRECOMP_DENSE:
 // the same test on the dense pooled matrix (every tile of the nt x nt grid).
-enum PlanMode { PLAN_EFFICIENT = 0, PLAN_BLOCKS = 1, PLAN_PRECOMP = 2, PLAN_PRECOMP_DENSE = 3 };
+// PLAN_STAGE: staged rows only; PLAN_SUMS: tile sums, block sums and observed statistic of one
+// recomputation whose rows another plan staged (TestPlan::staged).
+enum PlanMode { PLAN_EFFICIENT = 0, PLAN_BLOCKS = 1, PLAN_PRECOMP = 2, PLAN_PRECOMP_DENSE = 3,
+                PLAN_STAGE = 4, PLAN_SUMS = 5 };
 TestPlan make_plan(const etest_request& r, int64_t kc_override = 0, int mode = PLAN_EFFICIENT);
 
 // A set of tests laid out in one device workspace, ready to launch.
