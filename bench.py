@@ -115,8 +115,6 @@ def roofline(stage_ms, tests, prec, workload=None, gram_tests=None):
     Gram products one launch of the block stage computes (default: the same tests; an ED
     and an MMD test on the same data share one Gram)."""
     gram_tests = tests if gram_tests is None else gram_tests
-    # the Gram variant that also writes a partner test's blocks runs when tests share one
-    dual = "true" if len(tests) > len(gram_tests) else "false"
     gflops = sum(gram_flops(nx, ny, p) for nx, ny, p, B in gram_tests)
     upd = sum(packed_pairs(nx, ny) * B for nx, ny, p, B in tests)
     if not stage_ms.get("blocks") or not stage_ms.get("resampling"):
@@ -135,8 +133,7 @@ def roofline(stage_ms, tests, prec, workload=None, gram_tests=None):
         peak = {"f64": PEAK["fp64_TF"], "f32": PEAK["f16x3_TF"], "bf16r": PEAK["bf16_TF"]}[prec]
         r = {"bound": "alu" if prec == "f64" else "mfma", "achieved": gram_tf, "peak": peak,
              "unit": "TFLOP/s",
-             "kernel": {"f64": "k_dist_f64", "f32": "k_gram_f16x3<%s>" % dual,
-                        "bf16r": "k_gram_bf16<%s>" % dual}[prec],
+             "kernel": "k_dist_f64" if prec == "f64" else "k_gram_ring",
              "algorithmic": "2p flops per distinct Gram entry = %.4g per launch" % gflops}
     r["frac"] = r["achieved"] / r["peak"]
     r["traffic"] = measured_traffic(r["kernel"], workload) if workload else None
@@ -144,8 +141,7 @@ def roofline(stage_ms, tests, prec, workload=None, gram_tests=None):
 
 
 # a kernel's traffic depends on its source and on the launch shape the runtime picks
-KERNEL_SOURCES = {"k_gram_f16x3": ["k_gram.hip", "k_prep.hip", "common.h", "runtime.cpp"],
-                  "k_gram_bf16": ["k_gram.hip", "k_prep.hip", "common.h", "runtime.cpp"],
+KERNEL_SOURCES = {"k_gram_ring": ["k_gram.hip", "k_prep.hip", "common.h", "runtime.cpp"],
                   "k_gram_super": ["k_gram.hip", "k_prep.hip", "common.h", "runtime.cpp"],
                   "k_gram_finish": ["k_gram.hip", "common.h", "runtime.cpp"],
                   "k_dist_f64": ["k_gram.hip", "common.h", "runtime.cpp"],
@@ -483,7 +479,7 @@ def run_cross(args):
     flops = 2.0 * wl.p * rows * cols  # every cross pair once: no symmetry to use
     gram_tf = flops / (stage["blocks"] * 1e-3) / 1e12
     peak = PEAK["f16x3_TF"] if prec == "f32" else PEAK["bf16_TF"]
-    kernel = "k_gram_f16x3<false>" if prec == "f32" else "k_gram_bf16<false>"
+    kernel = "k_gram_ring"
     line = base_line(args, name, args.steps / elapsed, elapsed, args.steps,
                      "f32" if prec == "f32" else "bf16",
                      {"nx": wl.nx, "ny": wl.ny, "p": wl.p, "statistic": "cross-ed",

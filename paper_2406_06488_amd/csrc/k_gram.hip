@@ -15,17 +15,6 @@ namespace et {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int LDS_ROW_BF16 = 72;  // 64 staged k + 8 pad (bf16)
-
-// 16-byte load through a global-address-space pointer.  Operand prefetches use it: a
-// generic (flat) load also counts against the LDS wait counter, so the waits for fragment
-// reads from LDS would also wait for the next slice's operands and serialise the prefetch.
-__device__ inline uint4 gload16(const void* p) {
-  typedef __attribute__((ext_vector_type(4))) unsigned int v4;
-  const v4 v = *(const __attribute__((address_space(1))) v4*)p;
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 struct TileCtx {
   int t, i, j;
   int rows_i, rows_j;
@@ -101,59 +90,78 @@ constexpr int HALF = TILE / 2;
 // 32 lanes.
 constexpr int TILE_LDS = TILE + 4;
 
-// Staged half tile (64 rows of block values) -> FP64 row sums, FP64 column sums of the
-// half, the stored rows and the running max |value|.  All 256 threads take part:
-//  row sums: four threads per row, thread q reading columns q*32 + (k + q) % 32;
-//  column sums: two threads per column in one wave (rows 0..31 and 32..63);
-//  store: float4 reads of whole rows (32 lanes per row), coalesced float4 stores.
+// Sums of a tile, in one order for every kernel:
+//  row sums: four threads per row, thread q adding columns 32 q .. + 31 in order, then
+//    (q 0 + q 1) + (q 2 + q 3);
+//  column sums of a half tile (64 rows): for each h = 0, 1 the rows 8 i + 4 h .. + 3 (i < 4) of
+//    the first and of the second 32 rows are added in order, then the two, then the two h --
+//    the rows an MFMA accumulator's lane holds, so that they can be added in registers.
+// Row sums of one row's quarter from LDS (a 16-byte boundary); cross tests keep the sums over
+// the x2 columns (below `split`) and over the y2 columns apart.  Thread q writes for the row.
+// Two batches of 16 entries, so that the accumulators may stay in registers beside them.
+__device__ inline void emit_row(const BlockOut& o, int r, int q, const float* src, float& vmax) {
+  double s0 = 0.0, s1 = 0.0;
+#pragma unroll 1
+  for (int b = 0; b < 32; b += 16) {
+    float x[16];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float4 v = *(const float4*)(src + b + 4 * k);
+      x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) vmax = fmaxf(vmax, x[k]);  // block values are not negative
+    if (o.split < 0) {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) s0 += (double)x[k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const bool x2 = q * 32 + b + k < o.split;
+        s0 += x2 ? (double)x[k] : 0.0;
+        s1 += x2 ? 0.0 : (double)x[k];
+      }
+    }
+  }
+  s0 += __shfl_xor(s0, 1, 64);
+  s0 += __shfl_xor(s0, 2, 64);
+  if (q == 0) o.tsum[r] = s0;
+  if (o.split < 0) return;
+  s1 += __shfl_xor(s1, 1, 64);
+  s1 += __shfl_xor(s1, 2, 64);
+  if (q == 0) o.tsum[TILE + r] = s1;
+}
+// Column sum of one column of a half tile at `src` (two threads per column, h = 0 and 1, 32
+// lanes apart).
+__device__ inline void emit_col(const BlockOut& o, int half, int col, int h, const float* src) {
+  double s = 0.0;
+#pragma unroll 1
+  for (int b = 0; b < 2; ++b) {
+    float x[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = src[(b * 32 + 8 * (k >> 2) + 4 * h + (k & 3)) * TILE_LDS];
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) t += (double)x[k];
+    s = b ? s + t : t;
+  }
+  s += __shfl_xor(s, 32, 64);
+  if (h == 0) o.tsum[TILE * (1 + half) + col] = s;
+}
+
+// Staged half tile (64 rows of block values) -> row sums, stored rows and, with COLS, column
+// sums and the running max (else the caller has formed them in registers).  All 256 threads
+// take part; cross tests store no tile and have no column sums.
+template <bool COLS>
 __device__ inline void emit_half(const BlockOut& o, int half, const float* tl, float& vmax) {
   const int tid = threadIdx.x;
-  if (o.split >= 0) {
-    // cross tests: each row's sums over the x2 columns and over the y2 columns, kept apart
-    // (tsum[r] and tsum[TILE + r]); the tile itself is not stored
-    const int row = tid >> 2, q = tid & 3;
-    const float* src = tl + row * TILE_LDS + q * 32;
-    double s0 = 0.0, s1 = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) {
-      const int col = q * 32 + ((k + q) & 31);
-      const float x = src[(k + q) & 31];
-      if (col < o.split) s0 += (double)x;
-      else s1 += (double)x;
-      vmax = fmaxf(vmax, fabsf(x));
-    }
-    s0 += __shfl_xor(s0, 1, 64);
-    s0 += __shfl_xor(s0, 2, 64);
-    s1 += __shfl_xor(s1, 1, 64);
-    s1 += __shfl_xor(s1, 2, 64);
-    if (q == 0) {
-      o.tsum[half * HALF + row] = s0;
-      o.tsum[TILE + half * HALF + row] = s1;
-    }
-    return;
-  }
-  {
-    const int row = tid >> 2, q = tid & 3;
-    const float* src = tl + row * TILE_LDS + q * 32;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) {
-      const float x = src[(k + q) & 31];
-      s += (double)x;
-      vmax = fmaxf(vmax, fabsf(x));
-    }
-    s += __shfl_xor(s, 1, 64);
-    s += __shfl_xor(s, 2, 64);
-    if (q == 0) o.tsum[half * HALF + row] = s;
-  }
-  {
-    const int col = (tid >> 6) * 32 + (tid & 31), part = (tid >> 5) & 1;
-    const float* src = tl + part * 32 * TILE_LDS + col;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < 32; ++k) s += (double)src[k * TILE_LDS];
-    s += __shfl_xor(s, 32, 64);
-    if (part == 0) o.tsum[TILE * (1 + half) + col] = s;
+  float vm = 0.0f;
+  emit_row(o, half * HALF + (tid >> 2), tid & 3, tl + (tid >> 2) * TILE_LDS + (tid & 3) * 32, vm);
+  if (COLS) vmax = fmaxf(vmax, vm);
+  if (o.split >= 0) return;
+  if (COLS) {
+    const int col = (tid >> 6) * 32 + (tid & 31);
+    emit_col(o, half, col, (tid >> 5) & 1, tl + col);
   }
   if (!o.D) return;  // only the sums are kept
   float4* dst = (float4*)(o.D + half * HALF * TILE);
@@ -164,97 +172,6 @@ __device__ inline void emit_half(const BlockOut& o, int half, const float* tl, f
   }
 }
 
-// Tile epilogue shared by the Gram kernels: one stored tile -> one output (D2 false: the
-// staged values are block values) or, with D2 true, the staged values are squared
-// distances and are turned into the test's own block values and, with has1, into those of
-// the MMD test it feeds (each output's values are formed from the staged copy in place,
-// once per entry, so no second set of values is held in registers).  put(half) writes rows
-// half*64 .. +63 of the tile into tl (row stride TILE_LDS) and is called between barriers;
-// fix(half, first) may then rewrite staged entries, each thread only those of its own
-// transform slots (f = tid + 256 k: row f / 128, column f % 128).  tile_max_bits: two words of
-// LDS.  All 256 threads of the workgroup take part.
-template <bool D2, class Put, class Fix>
-__device__ __attribute__((always_inline)) inline void finish_tile_with(const TileCtx& c, float* tl,
-                                        unsigned int* tile_max_bits, Put put, Fix fix,
-                                        const BlockOut o0, const BlockOut o1, const bool has1) {
-  const int tid = threadIdx.x;
-  float vmax0 = 0.0f, vmax1 = 0.0f;
-  auto stage = [&](int half, bool first) __attribute__((always_inline)) {
-    __syncthreads();
-    put(half);
-    __syncthreads();
-    fix(half, first);
-  };
-  auto transform = [&](int half, int kind, double gamma) {
-#pragma unroll 2
-    for (int k = 0; k < HALF * TILE / 256; ++k) {
-      const int f = tid + 256 * k, r = f >> 7, col = f & (TILE - 1);
-      float* q = tl + r * TILE_LDS + col;
-      *q = block_value_f32(kind, gamma, c, half * HALF + r, col, *q);
-    }
-    __syncthreads();
-  };
-  __syncthreads();  // a previous tile's maxima have been read
-  if (tid < 2) tile_max_bits[tid] = 0u;
-  // the partner's output first: the test's own output may overwrite the staged source
-  // (the super-tile kernels stage from the test's own block tile)
-#pragma nounroll
-  for (int half = 0; half < 2; ++half) {
-    if (D2 && has1) {
-      stage(half, true);
-      transform(half, o1.kind, o1.gamma);
-      emit_half(o1, half, tl, vmax1);
-    }
-    stage(half, !(D2 && has1));
-    if (D2) transform(half, o0.kind, o0.gamma);
-    emit_half(o0, half, tl, vmax0);
-  }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    vmax0 = fmaxf(vmax0, __shfl_xor(vmax0, m, 64));
-    if (D2) vmax1 = fmaxf(vmax1, __shfl_xor(vmax1, m, 64));
-  }
-  // non-negative floats order like their bit patterns
-  if ((tid & 63) == 0) {
-    atomicMax(&tile_max_bits[0], __float_as_uint(vmax0));
-    if (D2 && has1) atomicMax(&tile_max_bits[1], __float_as_uint(vmax1));
-  }
-  __syncthreads();
-  if (tid == 0) {
-    o0.tmax[0] = __uint_as_float(tile_max_bits[0]);
-    o0.tmax[1] = 0.0f;
-    if (D2 && has1) {
-      o1.tmax[0] = __uint_as_float(tile_max_bits[1]);
-      o1.tmax[1] = 0.0f;
-    }
-  }
-}
-
-// 128-tile workgroups: v[mb][nb][e] is the entry of row wm*64 + mb*32 + 8*(e/4) + 4*h + e%4,
-// column wn*64 + nb*32 + lr: the waves with wm == half hold half `half`.
-template <bool DUAL>
-__device__ inline void finish_tile(const TileCtx& c, float* tl, unsigned int* tile_max_bits,
-                                   const f32x16 (&v)[2][2], int wm, int wn, int h, int lr,
-                                   const BlockOut o0, const BlockOut o1, const bool has1) {
-  auto put = [&](int half) {
-    if (wm == half) {
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int r = mb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);  // row within the half
-            tl[r * TILE_LDS + wn * 64 + nb * 32 + lr] = v[mb][nb][e];
-          }
-    }
-  };
-  finish_tile_with<DUAL>(c, tl, tile_max_bits, put, [](int, bool) {}, o0, o1, has1);
-}
-
-// Gram entry -> squared distance.  d^2 = |w_a|^2 + |w_b|^2 - 2 g; pairs with
-// d^2 < 1e-3 (|w_a|^2 + |w_b|^2), where that difference has cancelled most of its
-// digits, are recomputed as a direct FP32 difference of the input rows.
 // Near pairs: a Gram-based d^2 below 1e-3 of the norm sum has lost most of its digits to
 // cancellation; such pairs (off the diagonal, inside the tile) are recomputed as a direct
 // FP32 sum of squared differences of the input rows.
@@ -273,313 +190,130 @@ __device__ inline float direct_d2(const TestDesc& d, const TileCtx& c, int r, in
   }
   return s;
 }
-__device__ inline float refine_d2(const TestDesc& d, const TileCtx& c, int r, int col, float d2,
-                                  float nr, float nc, int* refined) {
-  if (needs_refine(d, c, r, col, d2, nr, nc)) {
-    d2 = direct_d2(d, c, r, col);
-    ++*refined;
-  }
-  return d2;
-}
-__device__ inline float gram_d2(const TestDesc& d, const TileCtx& c, int r, int col, float g,
-                                float nr, float nc, int* refined) {
-  return refine_d2(d, c, r, col, nr + nc - 2.0f * g, nr, nc, refined);
-}
-
 __device__ inline void add_refined(const TestDesc& d, int refined) {
   if (!refined) return;
   atomicAdd(&d.flags[1], refined);
   if (d.pflags) atomicAdd(&d.pflags[1], refined);
 }
 
-// Gram entries of a full-tile workgroup (2 x 2 waves of 64 x 64) -> squared distances
-// (VALUES false) or the test's own block values (VALUES true), in place.
-template <bool VALUES, bool GATHER = false>
-__device__ inline void gram_epilogue(const TestDesc& d, const TileCtx& c, f32x16 (&acc)[2][2],
-                                     int wm, int wn, int h, int lr, float* snorm) {
-  // snorm (LDS): the tile's 128 row norms and 128 column norms, staged once instead of two
-  // global loads per entry
-  const int tid = threadIdx.x;
-  {
-    const float* nrm = (const float*)d.nrm;
-    const int i = tid < TILE ? c.i : c.j, r = tid & (TILE - 1);
-    snorm[tid] = nrm[GATHER ? staged_row(d, i, tid < TILE ? c.rows_i : c.rows_j, r)
-                            : (int64_t)i * TILE + r];
-  }
-  __syncthreads();
-  int refined = 0;
-  for (int mb = 0; mb < 2; ++mb)
-    for (int nb = 0; nb < 2; ++nb) {
-      const int col = wn * 64 + nb * 32 + lr;
-      const float nc = snorm[TILE + col];
-      for (int e = 0; e < 16; ++e) {
-        const int r = wm * 64 + mb * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-        const float d2 = gram_d2(d, c, r, col, acc[mb][nb][e], snorm[r], nc, &refined);
-        acc[mb][nb][e] = VALUES ? block_value_f32(d.kind, d.gamma, c, r, col, d2) : d2;
-      }
+// Staged Gram entries of rows row0 .. row0 + rows - 1 of a tile -> block values of output o, in
+// place, four adjacent columns at a time.  The loop is rolled and its near-pair path stands
+// once: unrolled over a lane's accumulators it was 72 KB of code, whose instruction fetches took
+// longer than the products of a small grid, and rolled over them (one entry at a time through
+// indexed registers, a norm read and up to ten branches each) it took as long as the products of
+// a large one.  edge: the tile has padding or the diagonal.
+template <int THREADS>
+__device__ inline void block_values(const TestDesc& d, const TileCtx& c, const BlockOut& o,
+                                    int row0, int rows, bool edge, float* tl, const float* snorm,
+                                    int& refined) {
+#pragma unroll 1
+  for (int f = threadIdx.x; f < rows * (TILE / 4); f += THREADS) {
+    const int rl = f >> 5, c4 = 4 * (f & 31), r = row0 + rl;
+    float4* q = (float4*)(tl + rl * TILE_LDS + c4);
+    const float4 g = *q, n4 = *(const float4*)(snorm + TILE + c4);
+    const float nv[4] = {n4.x, n4.y, n4.z, n4.w}, nr = snorm[r];
+    float v[4] = {g.x, g.y, g.z, g.w};
+    uint32_t near = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = nr + nv[e] - 2.0f * v[e];
+      if (v[e] < 1e-3f * (nr + nv[e])) near |= 1u << e;
     }
-  add_refined(d, refined);
+    while (near) {
+      const int e = __builtin_ctz(near);
+      near &= near - 1u;
+      const float old = e == 0 ? v[0] : e == 1 ? v[1] : e == 2 ? v[2] : v[3];
+      if (!needs_refine(d, c, r, c4 + e, old, nr, snorm[TILE + c4 + e])) continue;
+      const float x = direct_d2(d, c, r, c4 + e);
+      v[0] = e == 0 ? x : v[0];
+      v[1] = e == 1 ? x : v[1];
+      v[2] = e == 2 ? x : v[2];
+      v[3] = e == 3 ? x : v[3];
+      ++refined;
+    }
+    if (edge) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = block_value_f32(o.kind, o.gamma, c, r, c4 + e, v[e]);
+    } else if (o.kind == KIND_ED) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = sqrtf(fmaxf(v[e], 0.0f));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = expf((float)(-o.gamma) * fmaxf(v[e], 0.0f));
+    }
+    *q = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
-// ------------------------------------------- fp16-pair operands (FP32-accurate) on fp16 MFMA
-// The staged operand holds fp16 pairs (hi, lo) of w 2^e (22 significant bits; see
-// f16_split_exponent).  Each Gram entry is formed as hi_a hi_b + hi_a lo_b + lo_a hi_b
-// (the lo_a lo_b term, 2^-22 of the product, is dropped) with three
-// v_mfma_f32_32x32x16_f16 into one FP32 accumulator: all three products are exact in FP32,
-// so the entry carries the same FP32 accumulation rounding as an FP32 Gram, at the fp16
-// MFMA rate.  The accumulator is scaled back by 2^-2e before the epilogue.
-// 4 waves as 2 x 2, each 64 x 64 = 2 x 2 blocks of 32 x 32; K slices of 32 pairs; the next
-// slice (of both staged planes, hi and lo) is loaded into registers while the current one
-// is multiplied; the LDS holds 40 KB, so three workgroups fit per CU.
+// Correctly rounded square root of a float in [2^-96, 2^126]: the hardware's root s is within
+// one ulp; the neighbour above is nearer when x lies past the midpoint, x - s^2 > s (up - s)
+// (both sides multiples of the squared spacing, so the quarter term drops out), and likewise
+// below.
+__device__ inline float sqrt_rn(float x) {
+  const float s = __builtin_amdgcn_sqrtf(x);
+  const float up = __uint_as_float(__float_as_uint(s) + 1u);
+  const float down = __uint_as_float(__float_as_uint(s) - 1u);
+  const float r = fmaf(-s, s, x);
+  const float v = r > s * (up - s) ? up : s;
+  return r <= -(s * (s - down)) ? down : v;
+}
+
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-constexpr int KS16 = 32;                // pairs per K slice
-constexpr int LDS_ROW_F16 = KS16 + 8;   // halves per LDS row (80 bytes)
 
+// ------------------------------------------------------------------ tiles by an LDS ring
+// F16: the staged operand holds fp16 pairs (hi, lo) of w 2^e (22 significant bits; see
+// f16_split_exponent), and each Gram entry is formed as hi_a hi_b + hi_a lo_b + lo_a hi_b (the
+// lo_a lo_b term, 2^-22 of the product, is dropped) with three v_mfma_f32_32x32x16_f16 into one
+// FP32 accumulator: all three products are exact in FP32, so the entry carries the same FP32
+// accumulation rounding as an FP32 Gram, at the fp16 MFMA rate.  The accumulator is scaled back
+// by 2^-2e before the epilogue.  Else BF16 operands on v_mfma_f32_32x32x16_bf16.
+//
+// The operands go straight from the K-blocked staging into LDS (global_load_lds, one contiguous
+// kilobyte per wave instruction): a stage is two 64-byte chunks of every row (fp16 pairs: 32
+// coordinates; BF16: 64), NBUF stages make the ring, one barrier per stage.  Within a row the
+// four 16-byte pieces of a chunk are stored at slot piece ^ ((row / 4) % 4), so that the 16
+// lanes of a fragment read hit distinct bank groups.  Eight waves (2 x 4 of TR/2 x 32), two on
+// every SIMD per workgroup: one wave's issue, waits and epilogue run under another's products.
+// TR = 128: a stored tile per workgroup; TR = 64: half of one (64 rows x 128 columns).
+//  - Grids of at most one workgroup per CU: the ring takes most of a CU's LDS (NBUF 5 or 6), as
+//    there is no second workgroup to hide the loads' latency; half tiles while they fit.
+//  - Larger grids: NBUF 2; two whole tiles share a CU.
+// Every shape adds an entry's products in the same order (chunk by chunk; hi hi, hi lo, lo hi)
+// and forms values and sums alike, so all agree bit for bit, as does the super-tile kernel.
+//
+// Large grids run the K loop at 1.1 PFLOP/s of fp16 products, the rate of the library's GEMM on
+// this card (power-limited: the clock drops to 1.9 GHz).  Measured (FP32 form), against a
+// kernel of four waves of 64 x 64 with register-staged 32-wide slices: 10 tiles at p = 1000 51 ->
+// 20 us, 136 tiles at p = 512 38 -> 22 us, 256 tiles (cross test) at p = 1000 55 -> 35 us, 528
+// tiles at p = 1024 96 -> 84 us, 7236 tiles at p = 512 (standard test) 461 -> 421 us (by this
+// ring with four waves, three workgroups to a CU: 97 and 465).
+//
 // GATHER: rows staged once in their own order (standard test), read through the row map.
-template <bool DUAL, bool GATHER = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-k_gram_f16x3(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests) {
-  __shared__ __attribute__((aligned(16))) float smem[HALF * TILE_LDS > 2 * TILE * LDS_ROW_F16
-                                                         ? HALF * TILE_LDS
-                                                         : 2 * TILE * LDS_ROW_F16];
-  __shared__ float snorm[2 * TILE];
-  __shared__ unsigned int tile_max_bits[2];
-  const int64_t bid = xcd_grouped(blockIdx.x, gridDim.x);
-  const int ti = find_test(offs, ntests, bid);
-  const TestDesc d = descs[ti];
-  const TileCtx c = tile_ctx(d, bid - offs[ti]);
-  // K-blocked fp16 pairs: tile t starts at t * TILE * 2 p_pad; chunk q (16 coordinates, hi
-  // halves then lo halves) of tile row r at (q * TILE + r) * CHUNK_HALVES
-  const uint16_t* Wa = (const uint16_t*)d.W + (int64_t)c.i * TILE * 2 * d.p_pad;
-  const uint16_t* Wb = (const uint16_t*)d.W + (int64_t)c.j * TILE * 2 * d.p_pad;
-  uint16_t* Ah = (uint16_t*)smem;
-  uint16_t* Al = Ah + TILE * LDS_ROW_F16;
-  uint16_t* Bh = Al + TILE * LDS_ROW_F16;
-  uint16_t* Bl = Bh + TILE * LDS_ROW_F16;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int wm = w >> 1, wn = w & 1, h = lane >> 5, lr = lane & 31;
-  f32x16 acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.0f;
-
-  // per half, operand and slice (two chunks) 128 rows x 4 pieces of 8 halves: thread tid
-  // owns rows (tid >> 2) + 64 s, coordinates c8 .. c8 + 7 of the slice (chunk c8 / 16), hi
-  // ([s][0]) and lo ([s][1])
-  const int lrow = tid >> 2, c8 = (tid & 3) * 8;
-  const int coff = (c8 >> 4) * TILE * CHUNK_HALVES + (c8 & 15);
-  const uint16_t* ga[2];
-  const uint16_t* gb[2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int r = lrow + 64 * s;
-    if (GATHER) {
-      const int64_t ra = staged_row(d, c.i, c.rows_i, r), rb = staged_row(d, c.j, c.rows_j, r);
-      const uint16_t* W = (const uint16_t*)d.W;
-      ga[s] = W + (ra / TILE * 2 * d.p_pad) * TILE + (ra % TILE) * CHUNK_HALVES + coff;
-      gb[s] = W + (rb / TILE * 2 * d.p_pad) * TILE + (rb % TILE) * CHUNK_HALVES + coff;
-    } else {
-      ga[s] = Wa + r * CHUNK_HALVES + coff;
-      gb[s] = Wb + r * CHUNK_HALVES + coff;
-    }
-  }
-  uint4 pa[2][2], pb[2][2];
-  // slice k0 starts at chunk k0 / 16, i.e. 2 k0 TILE halves on
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int pl = 0; pl < 2; ++pl) {
-        pa[s][pl] = gload16(ga[s] + (int64_t)k0 * 2 * TILE + pl * 16);
-        pb[s][pl] = gload16(gb[s] + (int64_t)k0 * 2 * TILE + pl * 16);
-      }
-  };
-  load(0);
-  for (int k0 = 0; k0 < d.p_pad; k0 += KS16) {
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int off = (lrow + 64 * s) * LDS_ROW_F16 + c8;
-      *(uint4*)(Ah + off) = pa[s][0];
-      *(uint4*)(Al + off) = pa[s][1];
-      *(uint4*)(Bh + off) = pb[s][0];
-      *(uint4*)(Bl + off) = pb[s][1];
-    }
-    __syncthreads();
-    if (k0 + KS16 < d.p_pad) load(k0 + KS16);
-#pragma unroll
-    for (int ks = 0; ks < KS16 / 16; ++ks) {
-      f16x8_t ah[2], al[2], bh[2], bl[2];
-      for (int mb = 0; mb < 2; ++mb) {
-        const int off = (wm * 64 + mb * 32 + lr) * LDS_ROW_F16 + 16 * ks + 8 * h;
-        ah[mb] = *(const f16x8_t*)(Ah + off);
-        al[mb] = *(const f16x8_t*)(Al + off);
-      }
-      for (int nb = 0; nb < 2; ++nb) {
-        const int off = (wn * 64 + nb * 32 + lr) * LDS_ROW_F16 + 16 * ks + 8 * h;
-        bh[nb] = *(const f16x8_t*)(Bh + off);
-        bl[nb] = *(const f16x8_t*)(Bl + off);
-      }
-      for (int mb = 0; mb < 2; ++mb)
-        for (int nb = 0; nb < 2; ++nb) {
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[mb], bh[nb], acc[mb][nb], 0, 0, 0);
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[mb], bl[nb], acc[mb][nb], 0, 0, 0);
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al[mb], bh[nb], acc[mb][nb], 0, 0, 0);
-        }
-    }
-  }
-  const float unscale = ldexpf(1.0f, -2 * f16_split_exponent(d));
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int e = 0; e < 16; ++e) acc[a][b][e] *= unscale;
-  // DUAL: launches that hold a test feeding an MMD test keep the squared distances for two
-  // outputs; plain launches turn them into block values at once
-  if (DUAL) {
-    gram_epilogue<false>(d, c, acc, wm, wn, h, lr, snorm);
-    finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
-                      partner_out(d, c), d.pD != nullptr);
-  } else {
-    gram_epilogue<true, GATHER>(d, c, acc, wm, wn, h, lr, snorm);
-    const BlockOut o = own_out(d, c);
-    finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
-  }
-}
-
-// ---------------------------------------------------------------- BF16 MFMA
-// Same arrangement with v_mfma_f32_32x32x16_bf16; pairs whose Gram-based d^2
-// falls below 1e-3 of the norm sum are recomputed from the FP32 input rows.
-template <bool DUAL, bool GATHER = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
-k_gram_bf16(const TestDesc* __restrict__ descs,
-                                                   const int64_t* __restrict__ offs, int ntests) {
-  __shared__ __attribute__((aligned(16))) float smem[HALF * TILE_LDS > TILE * LDS_ROW_BF16 ? HALF * TILE_LDS
-                                                              : TILE * LDS_ROW_BF16];
-  __shared__ float snorm[2 * TILE];
-  __shared__ unsigned int tile_max_bits[2];
-  const int64_t bid = xcd_grouped(blockIdx.x, gridDim.x);
-  const int ti = find_test(offs, ntests, bid);
-  const TestDesc d = descs[ti];
-  const TileCtx c = tile_ctx(d, bid - offs[ti]);
-  // K-blocked operand: tile t starts at t * TILE * p_pad; chunk q (32 coordinates) of tile
-  // row r at (q * TILE + r) * CHUNK_HALVES
-  const uint16_t* Wa = (const uint16_t*)d.W + (int64_t)c.i * TILE * d.p_pad;
-  const uint16_t* Wb = (const uint16_t*)d.W + (int64_t)c.j * TILE * d.p_pad;
-  uint16_t* As = (uint16_t*)smem;
-  uint16_t* Bs = As + TILE * LDS_ROW_BF16;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int wm = w >> 1, wn = w & 1, h = lane >> 5, lr = lane & 31;
-  f32x16 acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.0f;
-
-  // 1024 pieces of 8 bf16 per operand and 64-wide slice (two chunks): thread tid owns rows
-  // (tid >> 3) + 32 s, piece (tid & 7), which lies in chunk (tid & 7) / 4 of the slice; a
-  // wave's load covers 8 rows of both chunks, two contiguous 512-byte runs.  The next slice
-  // is loaded into registers while the current one is multiplied.
-  const int lrow = tid >> 3, c8 = (tid & 7) * 8;
-  const int coff = (c8 >> 5) * TILE * CHUNK_HALVES + (c8 & 31);
-  const uint16_t* ga[4];
-  const uint16_t* gb[4];
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int r = lrow + 32 * s;
-    if (GATHER) {
-      const int64_t ra = staged_row(d, c.i, c.rows_i, r), rb = staged_row(d, c.j, c.rows_j, r);
-      const uint16_t* W = (const uint16_t*)d.W;
-      ga[s] = W + (ra / TILE * d.p_pad) * TILE + (ra % TILE) * CHUNK_HALVES + coff;
-      gb[s] = W + (rb / TILE * d.p_pad) * TILE + (rb % TILE) * CHUNK_HALVES + coff;
-    } else {
-      ga[s] = Wa + r * CHUNK_HALVES + coff;
-      gb[s] = Wb + r * CHUNK_HALVES + coff;
-    }
-  }
-  uint4 pa0 = gload16(ga[0]), pa1 = gload16(ga[1]);
-  uint4 pa2 = gload16(ga[2]), pa3 = gload16(ga[3]);
-  uint4 pb0 = gload16(gb[0]), pb1 = gload16(gb[1]);
-  uint4 pb2 = gload16(gb[2]), pb3 = gload16(gb[3]);
-  for (int k0 = 0; k0 < d.p_pad; k0 += 64) {
-    __syncthreads();
-    uint16_t* la = As + lrow * LDS_ROW_BF16 + c8;
-    uint16_t* lb = Bs + lrow * LDS_ROW_BF16 + c8;
-    *(uint4*)(la) = pa0;
-    *(uint4*)(la + 32 * LDS_ROW_BF16) = pa1;
-    *(uint4*)(la + 64 * LDS_ROW_BF16) = pa2;
-    *(uint4*)(la + 96 * LDS_ROW_BF16) = pa3;
-    *(uint4*)(lb) = pb0;
-    *(uint4*)(lb + 32 * LDS_ROW_BF16) = pb1;
-    *(uint4*)(lb + 64 * LDS_ROW_BF16) = pb2;
-    *(uint4*)(lb + 96 * LDS_ROW_BF16) = pb3;
-    __syncthreads();
-    if (k0 + 64 < d.p_pad) {
-      // slice k0 + 64 starts at chunk (k0 + 64) / 32, i.e. (k0 + 64) * TILE halves on
-      const int64_t ko = (int64_t)(k0 + 64) * TILE;
-      pa0 = gload16(ga[0] + ko);
-      pa1 = gload16(ga[1] + ko);
-      pa2 = gload16(ga[2] + ko);
-      pa3 = gload16(ga[3] + ko);
-      pb0 = gload16(gb[0] + ko);
-      pb1 = gload16(gb[1] + ko);
-      pb2 = gload16(gb[2] + ko);
-      pb3 = gload16(gb[3] + ko);
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      bf16x8 av[2], bv[2];
-      for (int mb = 0; mb < 2; ++mb)
-        av[mb] = *(const bf16x8*)(As + (wm * 64 + mb * 32 + lr) * LDS_ROW_BF16 + 16 * s + 8 * h);
-      for (int nb = 0; nb < 2; ++nb)
-        bv[nb] = *(const bf16x8*)(Bs + (wn * 64 + nb * 32 + lr) * LDS_ROW_BF16 + 16 * s + 8 * h);
-      for (int mb = 0; mb < 2; ++mb)
-        for (int nb = 0; nb < 2; ++nb)
-          acc[mb][nb] =
-              __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[mb], bv[nb], acc[mb][nb], 0, 0, 0);
-    }
-  }
-  // DUAL: launches that hold a test feeding an MMD test keep the squared distances for two
-  // outputs; plain launches turn them into block values at once
-  if (DUAL) {
-    gram_epilogue<false>(d, c, acc, wm, wn, h, lr, snorm);
-    finish_tile<true>(c, smem, tile_max_bits, acc, wm, wn, h, lr, own_out(d, c),
-                      partner_out(d, c), d.pD != nullptr);
-  } else {
-    gram_epilogue<true, GATHER>(d, c, acc, wm, wn, h, lr, snorm);
-    const BlockOut o = own_out(d, c);
-    finish_tile<false>(c, smem, tile_max_bits, acc, wm, wn, h, lr, o, o, false);
-  }
-}
-
-// --------------------------------------------------- small grids: operands by a deep LDS ring
-// Grids of at most one or two workgroups per CU wait on memory and on their own epilogue, not
-// on the matrix cores: with the register-staged kernels above (one slice ahead) a 32-wide slice
-// took 1.5-2.4 us there, against 0.3 us of products.  Here the operands go straight into LDS
-// (global_load_lds), four or five stages ahead: a stage is two 64-byte chunks of every row
-// (fp16 pairs: 32 coordinates; BF16: 64) and the ring takes most of a CU's LDS, so one
-// workgroup fills a CU, with two waves on every SIMD (2 x 4 waves of TR/2 x 32).  TR = 64: half
-// a stored tile (64 rows x 128 columns), which spreads the smallest grids over twice as many
-// CUs; TR = 128: a whole tile.  Chunk layout, swizzle and the order in which each entry's
-// products are added are the super-tile kernel's, and the sums keep the order of the 128-tile
-// kernels, so all shapes agree bit for bit.  Measured (FP32 form, register-staged kernel ->
-// ring): 10 tiles at p = 1000 51 -> 20 us, 256 tiles (cross test) at p = 1000 55 -> 38 us, 136
-// tiles at p = 500 38 -> 25 us.  With one wave per SIMD instead of two: 28, 46 and 33 us.
+// first: the launch's first unit (a list past one dispatch goes in several).
 constexpr int GR_THREADS = 512;
-template <bool F16, int TR>
-__global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __restrict__ descs,
-                                                          const int64_t* __restrict__ offs,
-                                                          int ntests) {
-  constexpr int MB = TR / 64;                    // 32-row blocks per wave
+// WPE: waves per SIMD that the shape's workgroups per CU make.
+// DUAL: a test of the launch may also write its MMD partner's blocks (the loop over both outputs
+// keeps the accumulators live: 43 spilled registers, and 91 instead of 46 us on 1596 tiles at p =
+// 32).
+template <bool F16, int TR, int NBUF, int WPE, bool DUAL, bool GATHER = false>
+__global__ void __launch_bounds__(GR_THREADS) __attribute__((amdgpu_waves_per_eu(WPE)))
+k_gram_ring(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests,
+            int64_t first) {
+  constexpr int THREADS = GR_THREADS, WAVES = THREADS / 64, WN = WAVES / 2;  // 2 x WN waves
+  constexpr int MB = TR / 64;                    // 32-row blocks per wave (32 columns each)
   constexpr int NCH = 2;                         // chunks per stage
+  constexpr bool REGS = TR == TILE;              // finish plain tiles in registers
   constexpr int NSTEP = NCH * (F16 ? 1 : 2);     // K steps of 16 per stage
   constexpr int NPL = F16 ? 2 : 1;               // operand halves per K step (F16: hi, lo)
   constexpr int NF = (TR + TILE) / 16;           // kilobyte loads per chunk
   constexpr int CHP = NF * 64;                   // 16-byte pieces per chunk
   constexpr int BUFP = NCH * CHP;                // pieces per stage
-  constexpr int NBUF = TR == TILE ? 5 : 6;       // 160 or 144 KB
-  constexpr int LOADS = NCH * NF / (GR_THREADS / 64);  // loads per wave and stage
+  constexpr int LOADS = NCH * NF / WAVES;        // loads per wave and stage
   constexpr int EPI = TR * TILE_LDS / 4;         // the epilogue's tile, in pieces
-  static_assert(EPI + 2 * TILE / 4 + 1 <= NBUF * BUFP, "the epilogue fits the ring");
-  __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * BUFP];
-  const int64_t u = blockIdx.x;
+  constexpr int EPIP = EPI + 2 * TILE / 4 + 4;   // with the norms, flags and maxima
+  static_assert(NCH * NF % WAVES == 0, "whole loads per wave");
+  __shared__ __attribute__((aligned(16))) uint4 lds[NBUF * BUFP > EPIP ? NBUF * BUFP : EPIP];
+  const int64_t u = first + xcd_grouped(blockIdx.x, gridDim.x);
   const int64_t bid = TR == TILE ? u : u >> 1;
   const int half = TR == TILE ? 0 : (int)(u & 1);
   const int ti_ = find_test(offs, ntests, bid);
@@ -587,25 +321,40 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
   const TileCtx c = tile_ctx(d, bid - offs[ti_]);
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63,
             h = lane >> 5, lr = lane & 31;
-  const int wm = w >> 2, wn = w & 3;
+  const int wm = w / WN, wn = w % WN;
   const int64_t nch = d.p_pad / (F16 ? 16 : 32);      // chunks per row, even
   const int64_t tstride = nch * TILE * CHUNK_HALVES;  // halves per staged tile
-  const uint32_t lane_src = (uint32_t)(lane >> 2) * CHUNK_HALVES +
-                            (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 8);
+  const uint32_t piece = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) * 8);
+  const uint32_t lane_src = (uint32_t)(lane >> 2) * CHUNK_HALVES + piece;
   const uint16_t* srcA = (const uint16_t*)d.W + c.i * tstride + half * HALF * CHUNK_HALVES + lane_src;
   const uint16_t* srcB = (const uint16_t*)d.W + c.j * tstride + lane_src;
   const int nst = (int)(nch / NCH);
+  // load q of this wave and stage: chunk cc of rows 16 f .. + 15 (the TR rows, then the columns)
+  const uint16_t* grow[GATHER ? LOADS : 1];
+  if (GATHER) {
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) {
+      const int f = (w * LOADS + q) % NF, rr = lane >> 2;
+      const int64_t sr = f < TR / 16 ? staged_row(d, c.i, c.rows_i, half * HALF + f * 16 + rr)
+                                     : staged_row(d, c.j, c.rows_j, (f - TR / 16) * 16 + rr);
+      grow[GATHER ? q : 0] = (const uint16_t*)d.W + sr / TILE * tstride + (sr % TILE) * CHUNK_HALVES + piece;
+    }
+  }
   // the epilogue's norms and scale, loaded ahead of everything else
   float nreg = 0.0f;
-  if (tid < 2 * TILE)
-    nreg = ((const float*)d.nrm)[(int64_t)(tid < TILE ? c.i : c.j) * TILE + (tid & (TILE - 1))];
+  if (tid < 2 * TILE) {
+    const int i = tid < TILE ? c.i : c.j, r = tid & (TILE - 1);
+    nreg = ((const float*)d.nrm)[GATHER ? staged_row(d, i, tid < TILE ? c.rows_i : c.rows_j, r)
+                                        : (int64_t)i * TILE + r];
+  }
   const float unscale = F16 ? ldexpf(1.0f, -2 * f16_split_exponent(d)) : 1.0f;
   auto issue = [&](int st, int buf) {
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
       const int g = w * LOADS + q, cc = g / NF, f = g % NF;
-      const uint16_t* src = f < TR / 16 ? srcA + f * (16 * CHUNK_HALVES)
-                                        : srcB + (f - TR / 16) * (16 * CHUNK_HALVES);
+      const uint16_t* src = GATHER ? grow[GATHER ? q : 0]
+                            : f < TR / 16 ? srcA + f * (16 * CHUNK_HALVES)
+                                          : srcB + (f - TR / 16) * (16 * CHUNK_HALVES);
       __builtin_amdgcn_global_load_lds(
           (const __attribute__((address_space(1))) void*)(src + (int64_t)(st * NCH + cc) *
                                                                     (TILE * CHUNK_HALVES)),
@@ -616,7 +365,7 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
   const int sw = (lane >> 2) & 3;
   const int rd0 = lr * 4 + (h ^ sw);        // piece h       (BF16 first step; F16 hi)
   const int rd1 = lr * 4 + ((2 + h) ^ sw);  // piece 2 + h   (BF16 second step; F16 lo)
-  u32x4 ca[MB * NPL], cb[NPL], na[MB * NPL], nb[NPL];
+  u32x4 ca[MB * NPL], cb[NPL], na[MB * NPL], nb_[NPL];
   auto read = [&](int buf, int ks, u32x4 (&fa)[MB * NPL], u32x4 (&fb)[NPL]) {
     const uint4* base = lds + buf * BUFP + (F16 ? ks : ks >> 1) * CHP;
 #pragma unroll
@@ -658,9 +407,9 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
   __builtin_amdgcn_s_waitcnt(0x0070 | (((N) * LOADS) & 15) | ((((N) * LOADS) >> 4) << 14))
     static_assert((NBUF - 2) * LOADS < 64, "vmcnt");
     if (NBUF > 5 && later >= 4) GR_WAIT(NBUF > 5 ? 4 : 0);
-    else if (later >= 3) GR_WAIT(3);
-    else if (later == 2) GR_WAIT(2);
-    else if (later == 1) GR_WAIT(1);
+    else if (NBUF > 4 && later >= 3) GR_WAIT(NBUF > 4 ? 3 : 0);
+    else if (NBUF > 3 && later >= 2) GR_WAIT(NBUF > 3 ? 2 : 0);
+    else if (later >= 1) GR_WAIT(1);
     else GR_WAIT(0);
 #undef GR_WAIT
     __builtin_amdgcn_s_barrier();
@@ -678,10 +427,10 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
 #pragma unroll
     for (int ks = 0; ks < NSTEP; ++ks) {
       if (ks + 1 < NSTEP) {
-        read(buf, ks + 1, na, nb);
+        read(buf, ks + 1, na, nb_);
       } else if (st + 1 < nst) {
         arrive(st + 1);
-        read(next, 0, na, nb);
+        read(next, 0, na, nb_);
       }
       __builtin_amdgcn_sched_barrier(0);
       mfma();
@@ -689,121 +438,147 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
 #pragma unroll
       for (int k = 0; k < MB * NPL; ++k) ca[k] = na[k];
 #pragma unroll
-      for (int k = 0; k < NPL; ++k) cb[k] = nb[k];
+      for (int k = 0; k < NPL; ++k) cb[k] = nb_[k];
     }
     buf = next;
   }
-  __syncthreads();  // the ring is free for the epilogue
-  // Epilogue: the Gram entries of all TR rows staged at once, block values formed in place,
-  // then the 128-tile kernels' sums and stores (emit_half) with the same additions in the same
-  // order, every LDS read of a sum issued first.
+  // ---- epilogue: block values, sums and maxima of the test's own output and (pD) of the MMD
+  // test it feeds.  REGS: an energy-distance tile without near pairs or row norms outside
+  // [2^-80, 2^99] (every d^2 then lies in sqrt_rn's range) is finished in registers: values,
+  // column sums, maximum; its rows pass through LDS for the row sums and the coalesced store.
+  // Otherwise (and on half tiles, where 80 registers per lane do not hold it) the Gram entries
+  // are staged and turned into values there.
   float* tl = (float*)lds;
   float* snorm = tl + EPI * 4;
-  unsigned int* tile_max_bits = (unsigned int*)(snorm + 2 * TILE);
-  if (tid < 2 * TILE) snorm[tid] = nreg;
-  if (tid == 0) tile_max_bits[0] = 0u;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      tl[(wm * (TR / 2) + mb * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * TILE_LDS + wn * 32 + lr] =
-          acc[mb][e] * unscale;
-  __syncthreads();
-  // Gram entries -> block values, four adjacent columns at a time, in a rolled loop: unrolled
-  // over a lane's accumulators (each with its near-pair path) the kernel was 72 KB of code,
-  // whose instruction fetches took longer than the products of a small grid.
-  int refined = 0;
-#pragma unroll 1
-  for (int f = tid; f < TR * TILE / 4; f += GR_THREADS) {
-    const int rl = f >> 5, c4 = 4 * (f & 31), r = half * HALF + rl;
-    float4* q = (float4*)(tl + rl * TILE_LDS + c4);
-    const float4 g = *q, n4 = *(const float4*)(snorm + TILE + c4);
-    const float gv[4] = {g.x, g.y, g.z, g.w}, nv[4] = {n4.x, n4.y, n4.z, n4.w}, nr = snorm[r];
-    float v[4];
-    uint32_t near = 0u;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = nr + nv[e] - 2.0f * gv[e];
-      if (needs_refine(d, c, r, c4 + e, v[e], nr, nv[e])) near |= 1u << e;
-    }
-    while (near) {
-      const int e = __builtin_ctz(near);
-      near &= near - 1u;
-      const float x = direct_d2(d, c, r, c4 + e);
-      v[0] = e == 0 ? x : v[0];
-      v[1] = e == 1 ? x : v[1];
-      v[2] = e == 2 ? x : v[2];
-      v[3] = e == 3 ? x : v[3];
-      ++refined;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = block_value_f32(d.kind, d.gamma, c, r, c4 + e, v[e]);
-    *q = make_float4(v[0], v[1], v[2], v[3]);
+  uint32_t* misc = (uint32_t*)(snorm + 2 * TILE);  // ok[4], near[8], maxima[2]
+  const int col = wn * 32 + lr, row0 = wm * (TR / 2) + 4 * h;  // row0: in the workgroup's rows
+  float* tcol = tl + row0 * TILE_LDS + col;  // entry (mb, e): row 32 mb + 8 (e / 4) + e % 4 on
+  const bool edge = c.rows_i < TILE || c.rows_j < TILE || c.diag;
+  __syncthreads();  // the ring is free
+  if (tid < 2 * TILE) {
+    snorm[tid] = nreg;
+    const bool pad = (tid & (TILE - 1)) >= (tid < TILE ? c.rows_i : c.rows_j);
+    const uint64_t ok = __ballot(pad || (nreg >= 0x1p-80f && nreg <= 0x1p99f));
+    if (lane == 0) misc[w] = ok == ~0ull ? 1u : 0u;
   }
-  add_refined(d, refined);
-  __syncthreads();
-  const BlockOut o = own_out(d, c);
-  float vmax = 0.0f;
-  if (tid < 4 * TR) {  // row sums: four threads per row
-    const int q = tid & 3, rl = tid >> 2, r = half * HALF + rl;
-    float x[32];
+  if (tid < 2) misc[12 + tid] = 0u;
+  bool fast = REGS && d.kind == KIND_ED;
+  if (REGS && fast) {
+    __syncthreads();  // norms staged
+    // entry k = 32 mb + 8 g + u of this lane is row row0 + k (REGS: half == 0); padding and the
+    // diagonal are never recomputed
+    const int kend = col < c.rows_j ? c.rows_i - row0 : 0, kdiag = c.diag ? col - row0 : -1;
+    const float nc = snorm[TILE + col];
+    bool near = false;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const float4 v = *(const float4*)(tl + rl * TILE_LDS + q * 32 + 4 * k);
-      x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
-    }
-    // emit_half's order: thread q starts at its column q
-    double s0 = 0.0, s1 = 0.0;
-    auto add = [&](int k) {
-      if (o.split >= 0 && q * 32 + k >= o.split) s1 += (double)x[k];
-      else s0 += (double)x[k];
-      vmax = fmaxf(vmax, fabsf(x[k]));
-    };
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      if (k >= q) add(k);
+      for (int g = 0; g < 4; ++g) {
+        const float4 n4 = *(const float4*)(snorm + row0 + mb * 32 + 8 * g);
+        const float nr[4] = {n4.x, n4.y, n4.z, n4.w};
 #pragma unroll
-    for (int k = 3; k < 32; ++k) add(k);
+        for (int u = 0; u < 4; ++u) {
+          const int k = mb * 32 + 8 * g + u;
+          const float s = nr[u] + nc, gv = acc[mb][4 * g + u] * unscale;
+          near |= k < kend && k != kdiag && s - 2.0f * gv < 1e-3f * s;
+        }
+      }
+    const uint64_t anyn = __ballot(near);
+    if (lane == 0) misc[4 + w] = anyn ? 1u : 0u;
+    __syncthreads();
+    fast = misc[0] & misc[1] & misc[2] & misc[3];
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      if (k < q) add(k);
-    s0 += __shfl_xor(s0, 1, 64);
-    s0 += __shfl_xor(s0, 2, 64);
-    if (q == 0) o.tsum[r] = s0;
-    if (o.split >= 0) {
-      s1 += __shfl_xor(s1, 1, 64);
-      s1 += __shfl_xor(s1, 2, 64);
-      if (q == 0) o.tsum[TILE + r] = s1;
-    }
+    for (int k = 0; k < WAVES; ++k) fast = fast && !misc[4 + k];
   }
-  if (o.split < 0) {
-    // column sums of each half: two threads per column in one wave
-    const int t = TR == TILE ? tid : tid - 4 * TR;  // TR = 64: the threads without a row
-    if (t >= 0) {
-      const int hf = t >> 8, col = ((t >> 6) & 3) * 32 + (t & 31), part = (t >> 5) & 1;
-      float x[32];
+  if (REGS && fast && !(DUAL && d.pD)) {
+    const BlockOut o = own_out(d, c);
+    const int kend = col < c.rows_j ? c.rows_i - row0 : 0, kdiag = c.diag ? col - row0 : -1;
+    const float nc = snorm[TILE + col];
+    float vmax = 0.0f;
+    double cs[MB];
 #pragma unroll
-      for (int k = 0; k < 32; ++k) x[k] = tl[(hf * HALF + part * 32 + k) * TILE_LDS + col];
-      double s = 0.0;
+    for (int mb = 0; mb < MB; ++mb) {
+      cs[mb] = 0.0;
 #pragma unroll
-      for (int k = 0; k < 32; ++k) s += (double)x[k];
-      s += __shfl_xor(s, 32, 64);
-      if (part == 0) o.tsum[TILE * (1 + half + hf) + col] = s;
+      for (int g = 0; g < 4; ++g) {
+        const float4 n4 = *(const float4*)(snorm + row0 + mb * 32 + 8 * g);
+        const float nr[4] = {n4.x, n4.y, n4.z, n4.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = mb * 32 + 8 * g + u;
+          const float s = nr[u] + nc, gv = acc[mb][4 * g + u] * unscale;
+          const float x = sqrt_rn(s - 2.0f * gv);
+          const float v = k < kend && k != kdiag ? x : 0.0f;
+          tcol[k * TILE_LDS] = v;
+          vmax = fmaxf(vmax, v);
+          cs[mb] += (double)v;
+        }
+      }
     }
-    float4* dst = (float4*)(o.D + half * HALF * TILE);
+    double s = cs[0] + cs[MB - 1];
+    s += __shfl_xor(s, 32, 64);
+    if (h == 0 && o.split < 0) o.tsum[TILE * (1 + wm) + col] = s;
 #pragma unroll
-    for (int k = 0; k < TR * TILE / 4 / GR_THREADS; ++k) {
-      const int f = tid + GR_THREADS * k;
-      dst[f] = *(const float4*)(tl + (f >> 5) * TILE_LDS + 4 * (f & 31));
+    for (int m = 1; m < 64; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, 64));
+    if (lane == 0) atomicMax(&misc[12], __float_as_uint(vmax));
+    __syncthreads();
+    if (tid == 0) {
+      o.tmax[0] = __uint_as_float(misc[12]);
+      o.tmax[1] = 0.0f;
     }
+    float unused = 0.0f;
+    emit_row(o, tid >> 2, tid & 3, tl + (tid >> 2) * TILE_LDS + (tid & 3) * 32, unused);
+    if (o.D) {
+      float4* dst = (float4*)o.D;
+#pragma unroll
+      for (int k = 0; k < TR * TILE / 4 / THREADS; ++k) {
+        const int f = tid + THREADS * k;
+        dst[f] = *(const float4*)(tl + (f >> 5) * TILE_LDS + 4 * (f & 31));
+      }
+    }
+    return;
   }
+#pragma nounroll
+  for (int out = DUAL && d.pD ? 1 : 0; out >= 0; --out) {
+    const BlockOut o = DUAL && out ? partner_out(d, c) : own_out(d, c);
 #pragma unroll
-  for (int m = 1; m < 64; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, 64));
-  if (lane == 0) atomicMax(tile_max_bits, __float_as_uint(vmax));
-  __syncthreads();
-  if (tid == 0) {
-    o.tmax[half] = __uint_as_float(tile_max_bits[0]);
-    if (TR == TILE) o.tmax[1] = 0.0f;
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        tcol[(mb * 32 + 8 * (e >> 2) + (e & 3)) * TILE_LDS] = acc[mb][e] * unscale;
+    __syncthreads();
+    int refined = 0;
+    block_values<THREADS>(d, c, o, half * HALF, TR, edge, tl, snorm, refined);
+    if (out == 0) add_refined(d, refined);
+    __syncthreads();
+    float vmax = 0.0f;
+    if (tid < 4 * TR)
+      emit_row(o, half * HALF + (tid >> 2), tid & 3, tl + (tid >> 2) * TILE_LDS + (tid & 3) * 32, vmax);
+    if (o.split < 0) {
+      // two threads per column and half (TR = 64: those without a row)
+      const int t = TR == TILE ? tid : tid - 4 * TR;
+      if (t >= 0) {
+        const int hf = t >> 8, cl = ((t >> 6) & 3) * 32 + (t & 31);
+        emit_col(o, half + hf, cl, (t >> 5) & 1, tl + hf * HALF * TILE_LDS + cl);
+      }
+      if (o.D) {
+        float4* dst = (float4*)(o.D + half * HALF * TILE);
+#pragma unroll
+        for (int k = 0; k < TR * TILE / 4 / THREADS; ++k) {
+          const int f = tid + THREADS * k;
+          dst[f] = *(const float4*)(tl + (f >> 5) * TILE_LDS + 4 * (f & 31));
+        }
+      }
+    }
+    // non-negative floats order like their bit patterns
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, 64));
+    if (lane == 0) atomicMax(&misc[12 + out], __float_as_uint(vmax));
+    __syncthreads();  // (and the next output may stage)
+    if (tid == 0) {
+      o.tmax[half] = __uint_as_float(misc[12 + out]);
+      if (TR == TILE) o.tmax[1] = 0.0f;
+    }
   }
 }
 
@@ -820,8 +595,6 @@ __global__ void __launch_bounds__(GR_THREADS) k_gram_ring(const TestDesc* __rest
 // forms the block values, sums and maxima.  A wave whose tile is not stored (the lower
 // tile of a diagonal super tile, a tile past the edge of the grid) loads its share of the
 // operands like the others; its products are discarded.
-constexpr int SUPER = 2 * TILE;
-
 // (Cross tests, which store no block tile, are never planned on this kernel; the cross
 // branch of super_tile keeps the layout consistent with the 128-tile kernels.)
 struct SuperTile {
@@ -1155,7 +928,7 @@ k_gram_finish(const TestDesc* __restrict__ descs,
       }
       __syncthreads();
       float vm = 0.0f;  // one emit call site: the maxima combine afterwards
-      emit_half(o, half, tl, vm);
+      emit_half<true>(o, half, tl, vm);
       if (DUAL && out) vmax1 = fmaxf(vmax1, vm);
       else vmax0 = fmaxf(vmax0, vm);
     }
@@ -1390,12 +1163,33 @@ k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs,
   }
 }
 
-// Largest grids (stored tiles of all tests of the launch) for the ring kernels: one workgroup
-// per CU, of half tiles while two of them per tile still fit.  Past them the ring's workgroups
-// would go in two rounds of one per CU (272 tiles: 2 x 25 us at p = 500), where three
-// register-staged ones share a CU (45 us).
+// Shape of a launch by its grid (stored tiles of all tests): half tiles while two workgroups per
+// tile are at most one per CU; whole tiles with a deep ring up to one per CU (256 tiles at p =
+// 1000: 35 us, half tiles three to a CU 44); whole tiles, two to a CU, beyond (990 tiles at p =
+// 512 / 1024: 69 / 112 us, half tiles 77 / 128; 528 tiles 54 / 84, half tiles 49 / 79, but with
+// the split stream beside them 91 against 104 at p = 1000).
 constexpr int64_t GRAM_RING_MAX_HALVES = 128, GRAM_RING_MAX_TILES = 256;
 
+template <bool F16, int TR, int NBUF, int WPE, bool DUAL, bool GATHER = false>
+static void launch_ring_shape(int64_t blocks, hipStream_t st, const TestDesc* d,
+                              const int64_t* offs, int n) {
+  const int64_t units = TR == TILE ? blocks : 2 * blocks, most = 1 << 22;  // per dispatch
+  for (int64_t first = 0; first < units; first += most)
+    hipLaunchKernelGGL((k_gram_ring<F16, TR, NBUF, WPE, DUAL, GATHER>),
+                       dim3((unsigned)(units - first < most ? units - first : most)),
+                       dim3(GR_THREADS), 0, st, d, offs, n, first);
+}
+template <bool F16, bool DUAL>
+static void launch_ring(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs,
+                        int n) {
+  if (blocks <= GRAM_RING_MAX_HALVES)
+    launch_ring_shape<F16, 64, 6, 2, DUAL>(blocks, st, d, offs, n);
+  else if (blocks <= GRAM_RING_MAX_TILES)
+    launch_ring_shape<F16, 128, 5, 2, DUAL>(blocks, st, d, offs, n);
+  else
+    launch_ring_shape<F16, 128, 2, 4, DUAL>(blocks, st, d, offs, n);
+}
+// dual: some test of the launch also writes its MMD partner's blocks (TestDesc::pD says which)
 void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, const TestDesc* d,
                  const int64_t* offs, int n, bool dual) {
   if (blocks <= 0) return;
@@ -1405,46 +1199,32 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
       hipLaunchKernelGGL(k_gram_super<true>, g, b, 0, st, d, offs, n);
     else if (gop == GOP_BF16)
       hipLaunchKernelGGL(k_gram_super<false>, g, b, 0, st, d, offs, n);
-    return;
-  }
-  if (gop == GOP_F64) {
+  } else if (gop == GOP_F64) {
     // the launch table counts stored tiles
     const int64_t units = blocks * DF_PARTS;
     hipLaunchKernelGGL(k_dist_f64<false>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
                        dim3(DF_THREADS), 0, st, d, offs, n, units);
-  } else if (!dual && blocks <= GRAM_RING_MAX_TILES) {
-    const dim3 rb(GR_THREADS);
-    if (blocks <= GRAM_RING_MAX_HALVES) {
-      const dim3 g2((unsigned)(2 * blocks));
-      if (gop == GOP_F16PAIR) hipLaunchKernelGGL((k_gram_ring<true, 64>), g2, rb, 0, st, d, offs, n);
-      else hipLaunchKernelGGL((k_gram_ring<false, 64>), g2, rb, 0, st, d, offs, n);
-    } else if (gop == GOP_F16PAIR)
-      hipLaunchKernelGGL((k_gram_ring<true, 128>), g, rb, 0, st, d, offs, n);
-    else
-      hipLaunchKernelGGL((k_gram_ring<false, 128>), g, rb, 0, st, d, offs, n);
-  } else if (gop == GOP_F16PAIR && dual)
-    hipLaunchKernelGGL(k_gram_f16x3<true>, g, b, 0, st, d, offs, n);
-  else if (gop == GOP_F16PAIR)
-    hipLaunchKernelGGL(k_gram_f16x3<false>, g, b, 0, st, d, offs, n);
-  else if (dual)
-    hipLaunchKernelGGL(k_gram_bf16<true>, g, b, 0, st, d, offs, n);
-  else
-    hipLaunchKernelGGL(k_gram_bf16<false>, g, b, 0, st, d, offs, n);
+  } else if (gop == GOP_F16PAIR) {
+    if (dual) launch_ring<true, true>(blocks, st, d, offs, n);
+    else launch_ring<true, false>(blocks, st, d, offs, n);
+  } else {
+    if (dual) launch_ring<false, true>(blocks, st, d, offs, n);
+    else launch_ring<false, false>(blocks, st, d, offs, n);
+  }
 }
 
 // Tile sums of recomputations that share one staging (TestDesc::gather): `blocks` stored tiles.
 void launch_gram_sums(int gop, int64_t blocks, hipStream_t st, const TestDesc* d,
                       const int64_t* offs, int n) {
   if (blocks <= 0) return;
-  const dim3 g((unsigned)blocks), b(256);
   const int64_t units = blocks * DF_PARTS;
   if (gop == GOP_F64)
     hipLaunchKernelGGL(k_dist_f64<true>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
                        dim3(DF_THREADS), 0, st, d, offs, n, units);
   else if (gop == GOP_F16PAIR)
-    hipLaunchKernelGGL((k_gram_f16x3<false, true>), g, b, 0, st, d, offs, n);
+    launch_ring_shape<true, 128, 2, 4, false, true>(blocks, st, d, offs, n);
   else
-    hipLaunchKernelGGL((k_gram_bf16<false, true>), g, b, 0, st, d, offs, n);
+    launch_ring_shape<false, 128, 2, 4, false, true>(blocks, st, d, offs, n);
 }
 
 void launch_gram_finish(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs,

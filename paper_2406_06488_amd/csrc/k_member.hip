@@ -97,8 +97,8 @@ __device__ __attribute__((always_inline)) inline void member_walk(
 // MSPL is MEMBER_SPLITS, or MEMBER_SPLITS_WIDE for a launch with more workgroups than the
 // chip holds at once: there the stream is bound by vector-ALU cycles, and a wider
 // workgroup keeps twice as many of the scanning wave's lanes busy.
-// At most 64 VGPRs, so that three of its waves fit on a SIMD beside two of the FP32 form's
-// Gram (160 each), which it runs beside (with 70 the 2000 + 2000 x 1000 test took 3% longer).
+// At most 64 VGPRs, so that a wave of it fits on a SIMD beside four of the Gram's whole tiles
+// (110 each), which it runs beside.
 template <int MSPL>
 __global__ void __launch_bounds__(MTHREADS) __attribute__((amdgpu_waves_per_eu(8)))
 k_member(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests) {

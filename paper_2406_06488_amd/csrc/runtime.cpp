@@ -607,16 +607,13 @@ void enqueue_stages(const TestDesc* D, const int64_t* d_offs, const int64_t* h_o
     if (ev && (ev->mask >> k & 1u)) (void)hipEventRecord(ev->end[k], s);
   };
   if (clear_flags) launch_clear_flags(st, D, nullptr, n);
-  begin(0, st);
-  launch_colpart(total(S_COLPART), st, D, offs(S_COLPART), n);
-  launch_colmean(total(S_COLMEAN), st, D, offs(S_COLMEAN), n);
-  launch_stage(total(S_STAGE), st, D, offs(S_STAGE), n);
-  end(0, st);
-  // Split stream: independent of the data, so it runs beside other stages.  A stream that
-  // fits on the chip at once (up to SPLIT_EARLY_MAX_WG workgroups: each one's walk over the
-  // pooled items is latency-bound) is forked after staging, a short memory-bound stage, and
-  // runs beside the 128-tile block stage, whose grid leaves room on the CUs.  A larger one
-  // (many tests in one launch) keeps every CU's vector ALU busy for its whole duration and
+  // Split stream: independent of the data, so it runs beside other stages.  A stream that fits
+  // on the chip at once (up to SPLIT_EARLY_MAX_WG workgroups: each one's walk over the pooled
+  // items is latency-bound) is forked first: its workgroups have to be on the CUs before the
+  // block stage's, whose tiles leave room for one workgroup of it per CU, while those that find
+  // it there still take a tile per CU (2000 + 2000 x 1000, B = 10000: 439 us; forked after the
+  // staging, 640 workgroups of it took 160 us instead of 112 and the whole test 476).  A larger
+  // one (many tests in one launch) keeps every CU's vector ALU busy for its whole duration and
   // would slow the block stage by about as much as it overlaps, and super-tile workgroups
   // leave it no room; then it is forked after the block stage and runs beside the sums and
   // the centring, which are bound by memory.
@@ -635,6 +632,11 @@ void enqueue_stages(const TestDesc* D, const int64_t* d_offs, const int64_t* h_o
     if (fork) (void)hipEventRecord(fork->done, ms);
   };
   if (!late) split();
+  begin(0, st);
+  launch_colpart(total(S_COLPART), st, D, offs(S_COLPART), n);
+  launch_colmean(total(S_COLMEAN), st, D, offs(S_COLMEAN), n);
+  launch_stage(total(S_STAGE), st, D, offs(S_STAGE), n);
+  end(0, st);
   begin(1, st);
   launch_gram_slots(offs, total, st, D, n, dual);
   end(1, st);
