@@ -11,16 +11,13 @@ using namespace et;
 // ------------------------------------------------- baselines: standard and pre-computation
 namespace et {
 
-// Device result -> host, free the workspaces, wait.
-static etest_status finish_baseline(DevResult* d_res, Batch* b, void* aux, hipStream_t st,
+// Free the workspaces, wait for the result that the last kernel wrote to pinned memory.
+static etest_status finish_baseline(const DevResult* h, Batch* b, void* aux, hipStream_t st,
                                     hipError_t e, const char* what, etest_result* out) {
-  DevResult* h = pinned_results(1);
   if (e == hipSuccess) e = hipGetLastError();
-  if (e == hipSuccess && h) e = hipMemcpyAsync(h, d_res, sizeof(DevResult), hipMemcpyDeviceToHost, st);
   free_batch(b, st, true);
   if (aux) (void)hipFreeAsync(aux, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (!h) return set_error(ETEST_ENOMEM, "pinned result buffer");
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
   return dev_to_result(*h, out);
 }
@@ -46,13 +43,15 @@ static etest_status run_standard(const etest_request& r, hipStream_t st, etest_r
   const int64_t chunk = std::max<int64_t>(
       1, std::min<int64_t>({B + 1, 256, budget / std::max<int64_t>(1, (int64_t)P0.bytes),
                             (1 << 20) / P0.d.ntiles}));
-  size_t aoff[5], asz[5] = {(size_t)(chunk * n * 4), (size_t)(chunk * W * 4),
-                            (size_t)((B + 1) * 8), (size_t)(FLAG_WORDS * 4), sizeof(DevResult)};
+  size_t aoff[4], asz[4] = {(size_t)(chunk * n * 4), (size_t)(chunk * W * 4),
+                            (size_t)((B + 1) * 8), (size_t)(FLAG_WORDS * 4)};
   size_t atotal = 0;
-  for (int k = 0; k < 5; ++k) {
+  for (int k = 0; k < 4; ++k) {
     aoff[k] = atotal;
     atotal += align256(asz[k]);
   }
+  DevResult* res = pinned_results(1);
+  if (!res) return set_error(ETEST_ENOMEM, "pinned result buffer");
   void* aux = nullptr;
   hipError_t e = hipMallocAsync(&aux, atotal, st);
   if (e != hipSuccess || !aux) {
@@ -64,8 +63,9 @@ static etest_status run_standard(const etest_request& r, hipStream_t st, etest_r
   uint32_t* words = (uint32_t*)(a + aoff[1]);
   double* stats = (double*)(a + aoff[2]);
   int32_t* flags = (int32_t*)(a + aoff[3]);
-  DevResult* d_res = (DevResult*)(a + aoff[4]);
   Batch b;
+  sb.desc_by_kernel = true;
+  b.desc_pinned = true;
   s = place_batch(&sb, st, true);
   if (s == ETEST_OK) {
     P0.staged = &sb.descs[0];
@@ -81,7 +81,6 @@ static etest_status run_standard(const etest_request& r, hipStream_t st, etest_r
   {
     auto offs = [&](Slot k) { return sb.d_offs + (size_t)k * 2; };
     auto total = [&](Slot k) { return sb.offs[(size_t)k * 2 + 1]; };
-    launch_clear_flags(st, sb.d_descs, nullptr, 1);
     launch_colpart(total(S_COLPART), st, sb.d_descs, offs(S_COLPART), 1);
     launch_colmean(total(S_COLMEAN), st, sb.d_descs, offs(S_COLMEAN), 1);
     launch_stage(total(S_STAGE), st, sb.d_descs, offs(S_STAGE), 1);
@@ -105,9 +104,9 @@ static etest_status run_standard(const etest_request& r, hipStream_t st, etest_r
     launch_collect(D, m, c0, B, stats, flags, st);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) launch_count(stats, B, flags, r.perm_stats, d_res, st);
+  if (e == hipSuccess) launch_count(stats, B, flags, r.perm_stats, res, st);
   free_batch(&sb, st, true);
-  return finish_baseline(d_res, &b, aux, st, e, "standard test", out);
+  return finish_baseline(res, &b, aux, st, e, "standard test", out);
 }
 
 // Pre-computation test: the pooled Gram (D_WW: upper tiles, or with `dense` the whole
@@ -125,6 +124,9 @@ static etest_status run_precomputed(const etest_request& r, hipStream_t st, etes
   if ((int64_t)b.plans[0].d.ntiles * PC_STRIPS > 2147483647LL / groups)
     return set_error(ETEST_EINVAL, "pre-computation test: tiles x strips x split groups must "
                                    "stay below 2^31");
+  DevResult* res = pinned_results(1);
+  if (!res) return set_error(ETEST_ENOMEM, "pinned result buffer");
+  b.desc_by_kernel = true;
   etest_status s = place_batch(&b, st, true);
   if (s != ETEST_OK) return s;
   const TestDesc& d = b.descs[0];
@@ -135,7 +137,6 @@ static etest_status run_precomputed(const etest_request& r, hipStream_t st, etes
   auto mark = [&](int k, bool begin) {
     if (ev && (ev->mask >> k & 1u)) (void)hipEventRecord(begin ? ev->begin[k] : ev->end[k], st);
   };
-  launch_clear_flags(st, D, nullptr, 1);
   mark(0, true);
   launch_colpart(total(S_COLPART), st, D, offs(S_COLPART), 1);
   launch_colmean(total(S_COLMEAN), st, D, offs(S_COLMEAN), 1);
@@ -152,9 +153,9 @@ static etest_status run_precomputed(const etest_request& r, hipStream_t st, etes
   mark(5, false);
   mark(6, true);
   launch_precomp_stat(D, d.ntiles, r.B, d.part, d.pstat, st);
-  launch_count(d.pstat, r.B, d.flags, r.perm_stats, b.d_results, st);
+  launch_count(d.pstat, r.B, d.flags, r.perm_stats, res, st);
   mark(6, false);
-  etest_status rs = finish_baseline(b.d_results, &b, nullptr, st, hipSuccess, "pre-computation test", out);
+  etest_status rs = finish_baseline(res, &b, nullptr, st, hipSuccess, "pre-computation test", out);
   profile_collect();
   return rs;
 }
@@ -187,15 +188,17 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   // Permutations go in passes whose tables and partial sums take at most 1 GiB.
   const int64_t pass = std::min<int64_t>(
       nperm, std::max<int64_t>(64, ((int64_t)1 << 30) / (4 * ld + 8 * nparts)));
-  enum { H_KX, H_RX, H_RY, H_HS, H_FLAGS, H_PERMS, H_INV, H_PART, H_STATS, H_RES, H_N };
+  enum { H_KX, H_RX, H_RY, H_HS, H_FLAGS, H_PERMS, H_INV, H_PART, H_STATS, H_N };
   size_t sz[H_N] = {(size_t)(n * ld) * el, (size_t)n * 8, (size_t)n * 8, 2 * 8, FLAG_WORDS * 4,
                     (size_t)(pass * ld) * 2, (size_t)(pass * ld) * 2, (size_t)(pass * nparts) * 8,
-                    (size_t)nperm * 8, sizeof(DevResult)};
+                    (size_t)nperm * 8};
   size_t off[H_N], total = 0;
   for (int k = 0; k < H_N; ++k) {
     off[k] = total;
     total += align256(sz[k]);
   }
+  DevResult* res = pinned_results(1);
+  if (!res) return set_error(ETEST_ENOMEM, "pinned result buffer");
   void* aux = nullptr;
   hipError_t e = hipMallocAsync(&aux, total, st);
   if (e != hipSuccess || !aux) {
@@ -203,6 +206,7 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
     return set_error(ETEST_ENOMEM, "HSIC test buffers of " + std::to_string(total) + " bytes");
   }
   char* a = (char*)aux;
+  b.desc_pinned = true;
   etest_status s = place_batch(&b, st, true);
   if (s != ETEST_OK) {
     (void)hipFreeAsync(aux, st);
@@ -216,7 +220,6 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   uint16_t* inv16 = (uint16_t*)(a + off[H_INV]);
   double* part = (double*)(a + off[H_PART]);
   double* stats = (double*)(a + off[H_STATS]);
-  DevResult* d_res = (DevResult*)(a + off[H_RES]);
   const TestDesc* D = b.d_descs;
   auto offs = [&](Slot k) { return b.d_offs + (size_t)k * 3; };
   auto tot = [&](Slot k) { return b.offs[(size_t)k * 3 + 2]; };
@@ -248,9 +251,9 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
     if (last) mark(6, true);
     launch_hsic_stat(part, nparts, n, ld, p16, rxs, rys, m, hs, stats + c0, st);
   }
-  launch_count(stats, B, flags, h.perm_stats, d_res, st);
+  launch_count(stats, B, flags, h.perm_stats, res, st);
   mark(6, false);
-  etest_status rs = finish_baseline(d_res, &b, aux, st, hipSuccess, "HSIC test", out);
+  etest_status rs = finish_baseline(res, &b, aux, st, hipSuccess, "HSIC test", out);
   profile_collect();
   return rs;
 }

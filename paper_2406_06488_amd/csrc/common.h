@@ -144,7 +144,7 @@ struct TestDesc {
   DevResult* result;
   // Asynchronous single-test calls: the caller's result buffer, which the final kernel
   // fills with the result's leading six words (the etest_result fields) beside *result
-  // (NULL: none).
+  // (NULL: none).  Cross tests: the host's pinned buffer of their four statistics and flags.
   double* out6;
   // Shared block stage: an energy-distance test whose Gram also yields the Gaussian-kernel
   // blocks of an MMD test on the same data (pD != nullptr) writes that test's D, tile sums,

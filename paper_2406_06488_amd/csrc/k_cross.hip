@@ -97,10 +97,11 @@ __global__ void __launch_bounds__(CF_THREADS) k_cross_final(const TestDesc* __re
     double z;
     if (sigma > 0.0) z = u / sigma;
     else z = u > 0.0 ? INFINITY : (u < 0.0 ? -INFINITY : 0.0);
-    d.obs[0] = u;
-    d.obs[1] = sigma;
-    d.obs[2] = z;
-    d.obs[3] = 0.5 * erfc(z * 0.70710678118654752440);
+    d.out6[0] = u;
+    d.out6[1] = sigma;
+    d.out6[2] = z;
+    d.out6[3] = 0.5 * erfc(z * 0.70710678118654752440);
+    ((int2*)d.out6)[4] = make_int2(d.flags[0], d.flags[1]);
   }
 }
 

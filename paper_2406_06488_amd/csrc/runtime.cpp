@@ -549,7 +549,7 @@ etest_status place_batch(Batch* b, hipStream_t st, bool stream_ordered) {
   pairing.share_z.resize((size_t)n);
   for (int t = 0; t < n; ++t) {
     TestPlan& P = b->plans[(size_t)t];
-    assign_pointers(P, w + base[(size_t)t], b->d_results + t);
+    assign_pointers(P, w + base[(size_t)t], (b->host_results ? b->host_results : b->d_results) + t);
     b->descs[(size_t)t] = P.d;
     pairing.partner[(size_t)t] = P.partner;
     pairing.share_z[(size_t)t] = P.share_z ? 1 : 0;
@@ -763,7 +763,8 @@ etest_status dev_to_result(const DevResult& r, etest_result* out) {
   return ETEST_OK;
 }
 
-// Pinned staging for result copies (one per thread).
+// Pinned results of calls that wait, written by kernels (one buffer per thread; every device
+// may write it, and its writes bypass the caches).
 DevResult* pinned_results(size_t n) {
   static thread_local DevResult* buf = nullptr;
   static thread_local size_t cap = 0;
@@ -771,7 +772,8 @@ DevResult* pinned_results(size_t n) {
     if (buf) (void)hipHostFree(buf);
     buf = nullptr;
     cap = 0;
-    if (hipHostMalloc((void**)&buf, sizeof(DevResult) * n, hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void**)&buf, sizeof(DevResult) * n,
+                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
       return nullptr;
     cap = n;
   }
@@ -791,23 +793,25 @@ void init_pool_once() {
   });
 }
 
-// Run n tests described by device pointers; waits; fills outs.
+// Run n tests described by device pointers; waits; fills outs.  One test's descriptor goes up
+// as kernel arguments and the results are written to pinned memory by the last kernel (with two
+// pageable copies, a clear kernel and a copy back a test of ten tiles took 126 us instead of 113).
 static etest_status run_device(const etest_request* reqs, int64_t n, hipStream_t st,
                                etest_result* outs, const uint32_t* import_words = nullptr) {
   init_pool_once();
   Batch b;
   etest_status s = build_batch(reqs, n, false, &b);
   if (s != ETEST_OK) return s;
+  DevResult* hr = pinned_results((size_t)n);
+  if (!hr) return set_error(ETEST_ENOMEM, "pinned result buffer");
+  b.host_results = hr;
+  b.desc_by_kernel = n == 1;
   s = place_batch(&b, st, true);
   if (s != ETEST_OK) return s;
   enqueue_batch(b, st, import_words, profile_events(), thread_fork());
   hipError_t e = hipGetLastError();
-  DevResult* hr = pinned_results((size_t)n);
-  if (e == hipSuccess && hr)
-    e = hipMemcpyAsync(hr, b.d_results, sizeof(DevResult) * (size_t)n, hipMemcpyDeviceToHost, st);
   free_batch(&b, st, true);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (!hr) return set_error(ETEST_ENOMEM, "pinned result buffer");
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("run: ") + hipGetErrorString(e));
   profile_collect();
   etest_status worst = ETEST_OK;
@@ -990,11 +994,12 @@ static etest_status graph_entry(const etest_request* reqs, int64_t n, hipStream_
 // This call's pointers, seeds and gammas (and, asynchronous calls, result addresses) into
 // host descriptors for the entry's tables.
 static void fill_descs(const GraphEntry& g, const etest_request* reqs, int64_t n,
-                       const Pairing& pairing, TestDesc* hd, etest_result* d_outs) {
+                       const Pairing& pairing, TestDesc* hd, DevResult* results,
+                       etest_result* d_outs) {
   const Batch& b = g.batch;
   for (int64_t t = 0; t < n; ++t) {
     TestPlan P = make_plan(reqs[t]);
-    assign_pointers(P, (char*)b.ws + b.base[(size_t)t], b.d_results + t);
+    assign_pointers(P, (char*)b.ws + b.base[(size_t)t], results + t);
     if (d_outs) P.d.out6 = (double*)(d_outs + t);
     hd[t] = P.d;
   }
@@ -1012,12 +1017,10 @@ static etest_status run_batch_graph(const etest_request* reqs, int64_t n, hipStr
   TestDesc* hd = pinned_descs((size_t)n);
   DevResult* hr = pinned_results((size_t)n);
   if (!hd || !hr) return set_error(ETEST_ENOMEM, "pinned staging buffer");
-  fill_descs(*hit, reqs, n, pairing, hd, nullptr);
+  fill_descs(*hit, reqs, n, pairing, hd, hr, nullptr);
   HIP_OK(hipMemcpyAsync(b.d_descs, hd, sizeof(TestDesc) * (size_t)n, hipMemcpyHostToDevice, st),
          "descriptor copy");
   HIP_OK(hipGraphLaunch(hit->exec, st), "graph launch");
-  HIP_OK(hipMemcpyAsync(hr, b.d_results, sizeof(DevResult) * (size_t)n, hipMemcpyDeviceToHost, st),
-         "result copy");
   HIP_OK(hipStreamSynchronize(st), "batch");
   etest_status worst = ETEST_OK;
   for (int64_t t = 0; t < n; ++t) {
@@ -1040,7 +1043,7 @@ static etest_status enqueue_batch_graph(const etest_request* reqs, int64_t n, hi
   if (s != ETEST_OK) return s;
   PinnedSlot* slot = pinned_slot(sizeof(TestDesc) * (size_t)n);
   if (!slot) return set_error(ETEST_ENOMEM, "pinned staging slot");
-  fill_descs(*hit, reqs, n, pairing, (TestDesc*)slot->buf, d_outs);
+  fill_descs(*hit, reqs, n, pairing, (TestDesc*)slot->buf, hit->batch.d_results, d_outs);
   HIP_OK(hipMemcpyAsync(hit->batch.d_descs, slot->buf, sizeof(TestDesc) * (size_t)n,
                         hipMemcpyHostToDevice, st),
          "descriptor copy");
@@ -1353,10 +1356,10 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
   const int64_t npad = (int64_t)d.nt * TILE;
   const size_t el_w = (size_t)gram_operand_bytes(d.gop);
   // workspace: descriptor, launch tables, then the buffers the stages index
-  enum { C_DESC, C_OFFS, C_COLPART, C_COLMEAN, C_W, C_NRM, C_TSUM, C_TMAX, C_V, C_OBS, C_FLAGS, C_N };
+  enum { C_DESC, C_OFFS, C_COLPART, C_COLMEAN, C_W, C_NRM, C_TSUM, C_TMAX, C_V, C_FLAGS, C_N };
   size_t sz[C_N];
   sz[C_DESC] = sizeof(TestDesc);
-  sz[C_OFFS] = 5 * 2 * sizeof(int64_t);
+  sz[C_OFFS] = S_COUNT * 2 * sizeof(int64_t);
   sz[C_COLPART] = f64 ? 0 : (size_t)d.nrowchunks * r.p * 8;
   sz[C_COLMEAN] = f64 ? 0 : (size_t)r.p * 8;
   sz[C_W] = (size_t)npad * d.p_pad * el_w;
@@ -1365,13 +1368,17 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
   sz[C_TSUM] = (size_t)d.ntiles * d.tsum_stride * 8;
   sz[C_TMAX] = (size_t)d.ntiles * TMAX_PER_TILE * 4;
   sz[C_V] = (size_t)npad * 8;
-  sz[C_OBS] = 8 * 8;
   sz[C_FLAGS] = FLAG_WORDS * 4;
   size_t off[C_N], total = 0;
   for (int k = 0; k < C_N; ++k) {
     off[k] = total;
     total += align256(sz[k]);
   }
+  // k_cross_final writes the statistics and flags[0..1] into the thread's pinned result
+  struct Back { double stat[4]; int32_t flags[2]; };
+  static_assert(sizeof(Back) <= sizeof(DevResult), "result buffer");
+  const Back* hb = (const Back*)pinned_results(1);
+  if (!hb) return set_error(ETEST_ENOMEM, "pinned result buffer");
   void* ws = nullptr;
   hipError_t e = hipMallocAsync(&ws, total, st);
   if (e != hipSuccess || !ws) {
@@ -1386,28 +1393,23 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
   d.tsum = (double*)(w + off[C_TSUM]);
   d.tmax = (float*)(w + off[C_TMAX]);
   d.rsum = (double*)(w + off[C_V]);
-  d.obs = (double*)(w + off[C_OBS]);
   d.flags = (int32_t*)(w + off[C_FLAGS]);
+  d.out6 = (double*)hb;
   // launch tables [0, workgroups] of the stages (a one-test batch)
   const bool f32like = !f64;
   const int64_t wg[5] = {f32like ? colpart_wgs(d.nrowchunks, r.p) : 0,
                          f32like ? (r.p + 63) / 64 : 0, stage_wgs(npad, d.p_pad), gram_wg, 0};
-  int64_t hoffs[10];
-  for (int k = 0; k < 5; ++k) {
-    hoffs[2 * k] = 0;
-    hoffs[2 * k + 1] = wg[k];
-  }
+  int64_t hoffs[S_COUNT * 2] = {};
+  for (int k = 0; k < 5; ++k) hoffs[2 * k + 1] = wg[k];
   const TestDesc* D = (const TestDesc*)(w + off[C_DESC]);
   const int64_t* O = (const int64_t*)(w + off[C_OFFS]);
-  e = hipMemcpyAsync(w + off[C_DESC], &d, sizeof(TestDesc), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(w + off[C_OFFS], hoffs, sizeof(hoffs), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) {
+  {
     // stage timing as for the permutation tests: 0 staging, 1 blocks, 6 statistic
     const StageEvents* ev = profile_events();
     auto mark = [&](int k, bool begin) {
       if (ev && (ev->mask >> k & 1u)) (void)hipEventRecord(begin ? ev->begin[k] : ev->end[k], st);
     };
-    launch_clear_flags(st, D, nullptr, 1);
+    launch_put_desc(d, hoffs, (TestDesc*)(w + off[C_DESC]), (int64_t*)(w + off[C_OFFS]), st);
     mark(0, true);
     launch_colpart(wg[0], st, D, O, 1);
     launch_colmean(wg[1], st, D, O + 2, 1);
@@ -1421,22 +1423,15 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
     mark(6, false);
     e = hipGetLastError();
   }
-  // obs[0..3] and flags[0..1] back to the host
-  struct Back { double obs[4]; int32_t flags[2]; };
-  static thread_local Back* hb = nullptr;
-  if (!hb && hipHostMalloc((void**)&hb, sizeof(Back), hipHostMallocDefault) != hipSuccess) hb = nullptr;
-  if (e == hipSuccess && hb) e = hipMemcpyAsync(hb->obs, d.obs, 4 * 8, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess && hb) e = hipMemcpyAsync(hb->flags, d.flags, 2 * 4, hipMemcpyDeviceToHost, st);
   (void)hipFreeAsync(ws, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (!hb) return set_error(ETEST_ENOMEM, "pinned result buffer");
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("cross: ") + hipGetErrorString(e));
   profile_collect();
   if (hb->flags[0]) return set_error(ETEST_ENONFINITE, "X or Y contains NaN or Inf");
-  out->statistic = hb->obs[0];
-  out->sigma = hb->obs[1];
-  out->z = hb->obs[2];
-  out->p_value = hb->obs[3];
+  out->statistic = hb->stat[0];
+  out->sigma = hb->stat[1];
+  out->z = hb->stat[2];
+  out->p_value = hb->stat[3];
   out->n_refined = hb->flags[1];
   return ETEST_OK;
 }

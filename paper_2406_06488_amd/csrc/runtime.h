@@ -162,6 +162,9 @@ struct Batch {
   // several tests: descriptors and launch tables go up in one copy from a pinned staging
   // slot (pinned_slot) instead of two copies from pageable host memory
   bool desc_pinned = false;
+  // calls that wait: the tests' last kernels write their results into this pinned host buffer
+  // (pinned_results) instead of d_results, with no copy after the pass
+  DevResult* host_results = nullptr;
   // split stream of MEMBER_SPLITS_WIDE columns per workgroup (build_batch decides)
   bool member_wide = false;
 };
