@@ -11,17 +11,35 @@ namespace et {
 
 constexpr int ROWCHUNK = COLSUM_ROWS;
 
-__device__ inline float load_in_f32(const TestDesc& d, int64_t t, int k) {
-  return pooled_row<float>(d, t)[k];
-}
 __device__ inline double load_in_f64(const TestDesc& d, int64_t t, int k) {
   return pooled_row<double>(d, t)[k];
 }
 
 // Partial column sums over chunks of ROWCHUNK pooled rows (FP64).  All ROWCHUNK loads of a
-// thread are issued before the (fixed-order) sum, so they are in flight together.  Tests
+// thread are issued before the (fixed-order) sum, so they are in flight together; rows past the
+// end and columns past p are read at the last valid place and masked, so that no load stands in
+// a branch, and with p >= 256 the rows' addresses are scalar (a guarded load per row was 13.7 KB
+// of code, which a grid of 52 workgroups spent 4 of its 8 us fetching).  Tests
 // whose Gram reads fp16 pairs also take max |x| over the input (one atomic per workgroup),
 // which sets the scale of those pairs.
+__device__ inline void column_chunk(const TestDesc& d, int64_t t0, int k, float (&v)[ROWCHUNK]) {
+  // pooled_row without a row map (tests with one share another's staging): rows from s1, s2 and
+  // s3 on lie at their own bases
+  const float* X = (const float*)d.X;
+  const float* Y = (const float*)d.Y;
+  const int64_t n = (int64_t)d.nx + d.ny, p = d.p;
+  const int64_t s1 = d.cross ? d.cnx1 : d.nx, s2 = d.cross ? s1 + d.cny1 : n,
+                s3 = d.cross ? s2 + d.cnx2 : n;
+  const float* b1 = Y - s1 * p;
+  const float* b2 = X + (d.cnx1 - s2) * p;
+  const float* b3 = Y + (d.cny1 - s3) * p;
+#pragma unroll
+  for (int r = 0; r < ROWCHUNK; ++r) {
+    const int64_t t = t0 + r < n ? t0 + r : n - 1;
+    const float* base = t < s2 ? (t < s1 ? X : b1) : (t < s3 ? b2 : b3);
+    v[r] = (base + t * p)[k];
+  }
+}
 __global__ void __launch_bounds__(256) k_colpart(const TestDesc* __restrict__ descs,
                                                  const int64_t* __restrict__ offs, int ntests) {
   const int ti = find_test(offs, ntests, blockIdx.x);
@@ -30,28 +48,28 @@ __global__ void __launch_bounds__(256) k_colpart(const TestDesc* __restrict__ de
   const int cpw = colpart_chunks_per_wg(d.p);
   int rc, k;
   bool ok;
+  float v[ROWCHUNK];
   if (cpw > 1) {  // p < 256: row chunks local * cpw + threadIdx.x / p, all p columns
     const int sub = (int)threadIdx.x / d.p;
     k = (int)threadIdx.x % d.p;
     rc = (int)(local * cpw) + sub;
     ok = sub < cpw && rc < d.nrowchunks;
+    column_chunk(d, (int64_t)rc * ROWCHUNK, k, v);
   } else {
     const int ncb = (d.p + 255) / 256;
     rc = (int)(local / ncb);
     k = (int)(local % ncb) * 256 + threadIdx.x;
     ok = k < d.p;
+    column_chunk(d, (int64_t)rc * ROWCHUNK, ok ? k : d.p - 1, v);
   }
-  const int64_t n = (int64_t)d.nx + d.ny;
-  const int64_t t0 = (int64_t)rc * ROWCHUNK;
-  float v[ROWCHUNK];
-#pragma unroll
-  for (int r = 0; r < ROWCHUNK; ++r) v[r] = ok && t0 + r < n ? load_in_f32(d, t0 + r, k) : 0.0f;
+  const int64_t left = ok ? (int64_t)d.nx + d.ny - (int64_t)rc * ROWCHUNK : 0;
   double s = 0.0;
   float mx = 0.0f;
 #pragma unroll
   for (int r = 0; r < ROWCHUNK; ++r) {
-    s += (double)v[r];
-    mx = fmaxf(mx, fabsf(v[r]));  // fmaxf drops NaN; an Inf makes the scale 1 (flagged anyway)
+    const float x = r < left ? v[r] : 0.0f;
+    s += (double)x;
+    mx = fmaxf(mx, fabsf(x));  // fmaxf drops NaN; an Inf makes the scale 1 (flagged anyway)
   }
   if (ok) d.colpart[(int64_t)rc * d.p + k] = s;
   if (d.gop == GOP_F16PAIR) {  // uniform per workgroup: one atomic per workgroup
