@@ -10,7 +10,10 @@
 namespace et {
 
 // One workgroup per 64 split columns: 16 groups of waves each sum every 16th row range,
-// then wave 0 adds the 16 group sums in order.  Every workgroup also evaluates the
+// then wave 0 adds the 16 group sums in order.  A group's loads of its own and the identity
+// column are issued PS_BATCH at a time before any is added: one load after the other, each a
+// trip to a far cache, 136 row ranges took 24 us instead of 11 (16 at a time: the same, and 47
+// instead of 28 us on 256 tests of a few ranges).  Every workgroup also evaluates the
 // identity column B with the same loads in the same order, so all of them hold the
 // threshold bit for bit as the column's own workgroup computes it.  Exceedances are
 // counted with one integer atomic per workgroup; the last workgroup of a test writes the
@@ -23,6 +26,8 @@ __device__ inline double split_statistic(const TestDesc& d, double q) {
   return d.kind == KIND_ED ? -coef * q : coef * q;
 }
 
+constexpr int PS_BATCH = 8;
+
 __global__ void __launch_bounds__(64 * PS_GROUPS) k_pstat(const TestDesc* __restrict__ descs,
                                                           const int64_t* __restrict__ offs,
                                                           int ntests) {
@@ -31,16 +36,29 @@ __global__ void __launch_bounds__(64 * PS_GROUPS) k_pstat(const TestDesc* __rest
   const TestDesc d = descs[ti];
   const int64_t wg = blockIdx.x - offs[ti];
   const int64_t nwg = offs[ti + 1] - offs[ti];
-  const int c = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int c = threadIdx.x & 63, g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t col = wg * 64 + c;
-  double s = 0.0;
-  for (int rk = g; rk < d.n_rowk; rk += PS_GROUPS) s += d.part[(int64_t)rk * d.B_pad + col];
-  red[g][c] = s;
-  if (c == 0) {
-    double sb = 0.0;
-    for (int rk = g; rk < d.n_rowk; rk += PS_GROUPS) sb += d.part[(int64_t)rk * d.B_pad + d.B];
-    red[g][64] = sb;
+  double s = 0.0, sb = 0.0;
+  for (int rk = g; rk < d.n_rowk; rk += PS_GROUPS * PS_BATCH) {
+    double x[PS_BATCH], y[PS_BATCH];
+#pragma unroll
+    for (int u = 0; u < PS_BATCH; ++u) {
+      x[u] = y[u] = 0.0;
+      if (rk + PS_GROUPS * u < d.n_rowk) {
+        const double* row = d.part + (int64_t)(rk + PS_GROUPS * u) * d.B_pad;
+        x[u] = row[col];
+        y[u] = row[d.B];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PS_BATCH; ++u)
+      if (rk + PS_GROUPS * u < d.n_rowk) {
+        s += x[u];
+        sb += y[u];
+      }
   }
+  red[g][c] = s;
+  if (c == 0) red[g][64] = sb;
   __syncthreads();
   if (g != 0) return;
   double q = 0.0, qb = 0.0;
