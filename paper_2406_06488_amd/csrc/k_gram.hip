@@ -966,8 +966,10 @@ k_gram_finish(const TestDesc* __restrict__ descs,
 // (global_load_lds), two rounds ahead; the 16 pieces (two coordinates) of a staged row are
 // stored at slot piece ^ (row % 8), so that the 8 rows of a fragment read lie in distinct
 // banks.  Measured against one 128 x 128 tile per workgroup: 200 + 200 x 1000 (cross test,
-// 4 tiles) 639 -> 48 us, latency-bound before and after; 1000 + 1000 x 500 303 -> 116 us (52
-// us of vector-ALU time); four waves instead of eight took 59 and 107 us.
+// 4 tiles) 639 -> 46 us, latency-bound before and after; 1000 + 1000 x 500 303 -> 112 us (52
+// us of vector-ALU time; four waves instead of eight took 107); 504 tiles of 90 + 33 rows, p =
+// 25 (standard test) 45 -> 65 us, where a part's fixed cost (partial sums through LDS, root or
+// exponential) is most of it, but the whole test 175 -> 165.
 constexpr int DF_THREADS = 512;
 constexpr int DF_ROWS = 32, DF_COLS = 64;      // entries of one workgroup
 constexpr int DF_K = 32;                       // coordinates per round (4 per wave)
@@ -975,19 +977,20 @@ constexpr int DF_NBUF = 3;
 constexpr int DF_BUF = (DF_ROWS + DF_COLS) * DF_K;  // doubles per buffer
 constexpr int DF_PARTS = (TILE / DF_ROWS) * (TILE / DF_COLS);
 
-// Block values, stored entries and sums of the rows lr + 8 w of a 32 x 64 part: v[b] is the
-// squared distance of entry (r0 + lr + 8 w, c0 + lc + 8 b).  Column sums of the wave's 8
-// rows go to cs[w].  Cross tests keep the row sums over the x2 columns and over the y2
-// columns apart and store no tile.
+// Block values, stored entries and sums of the rows lr + 8 (w % 4) and columns lc + 8 b +
+// 32 (w / 4) of a 32 x 64 part: v[b] is the squared distance of that entry.  The sums of the
+// row's 32 columns go to rs[0][w / 4] (cross tests: x2 columns there, y2 columns to rs[1]), the
+// column sums of the wave's 8 rows to cs[w % 4].  Cross tests store no tile.
 __device__ inline void dist_emit_f64(const TestDesc& d, const TileCtx& c, int r0, int c0, int w,
-                                     int lane, const double (&v)[8], double (*cs)[64]) {
-  const int lr = lane >> 3, lc = lane & 7, ch = c0 / 64;
+                                     int lane, const double (&v)[4], double (*rs)[2][32],
+                                     double (*cs)[64]) {
+  const int lr = lane >> 3, lc = lane & 7, hc = w >> 2;
   const int split = d.cross ? cross_split(d, c.j) : -1;
-  const int r = r0 + 8 * w + lr;
-  double s0 = 0.0, s1 = 0.0, col[8];
+  const int r = r0 + 8 * (w & 3) + lr;
+  double s0 = 0.0, s1 = 0.0, col[4];
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int cc = c0 + lc + 8 * b;
+  for (int b = 0; b < 4; ++b) {
+    const int cc = c0 + lc + 8 * b + 32 * hc;
     double x;
     if (r >= c.rows_i || cc >= c.rows_j) x = 0.0;
     else if (c.diag && r == cc) x = d.kind == KIND_ED ? 0.0 : 1.0;
@@ -1002,17 +1005,16 @@ __device__ inline void dist_emit_f64(const TestDesc& d, const TileCtx& c, int r0
     s0 += __shfl_xor(s0, m, 64);
     s1 += __shfl_xor(s1, m, 64);
   }
-  double* ts = d.tsum + (int64_t)c.t * d.tsum_stride;
   if (lc == 0) {
-    ts[ch * TILE + r] = s0;
-    if (split >= 0) ts[(2 + ch) * TILE + r] = s1;
+    rs[0][hc][8 * (w & 3) + lr] = s0;
+    if (split >= 0) rs[1][hc][8 * (w & 3) + lr] = s1;
   }
   if (split >= 0) return;
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {  // over the wave's 8 rows
+  for (int b = 0; b < 4; ++b) {  // over the wave's 8 rows
 #pragma unroll
     for (int m = 8; m < 64; m <<= 1) col[b] += __shfl_xor(col[b], m, 64);
-    if (lr == 0) cs[w][lc + 8 * b] = col[b];
+    if (lr == 0) cs[w & 3][lc + 8 * b + 32 * hc] = col[b];
   }
 }
 
@@ -1026,8 +1028,25 @@ __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int pa
   const int lr = lane >> 3, lc = lane & 7;  // entries (lr + 8 a, lc + 8 b), a < 4, b < 8
   const double* Wa = (const double*)d.W + ((int64_t)c.i * TILE + r0) * d.p_pad;
   const double* Wb = (const double*)d.W + ((int64_t)c.j * TILE + c0) * d.p_pad;
-  // a part that holds only padding has no coordinates to add (its entries are 0)
-  const int nk = r0 < c.rows_i && c0 < c.rows_j ? d.p_pad : 0;
+  double* ts = d.tsum + (int64_t)c.t * d.tsum_stride;
+  // a part that holds only padding: its entries are 0
+  if (r0 >= c.rows_i || c0 >= c.rows_j) {
+    if (tid < DF_ROWS) {
+      ts[ch * TILE + r0 + tid] = 0.0;
+      if (d.cross) ts[(2 + ch) * TILE + r0 + tid] = 0.0;
+    }
+    if (d.cross) return;
+    if (tid < DF_COLS) ts[(2 + rq) * TILE + c0 + tid] = 0.0;
+    if (d.D)
+#pragma unroll
+      for (int q = 0; q < DF_ROWS * DF_COLS / 2 / DF_THREADS; ++q) {
+        const int e = 2 * (tid + DF_THREADS * q);
+        *(double2*)((double*)d.D + (int64_t)c.t * TILE * TILE + (r0 + e / DF_COLS) * TILE + c0 +
+                    e % DF_COLS) = make_double2(0.0, 0.0);
+      }
+    return;
+  }
+  const int nk = d.p_pad;
   // Load f = NLD w + q of a round moves staged rows 4 f .. + 3 (the 32 rows, then the 64
   // columns); this lane fills slot lane % 16 of row 4 f + lane / 16.
   const int row4 = lane >> 4;
@@ -1098,69 +1117,74 @@ __device__ inline void dist_part_f64(const TestDesc& d, const TileCtx& c, int pa
       if (k == 1) __builtin_amdgcn_sched_barrier(0);  // at most two coordinates' reads ahead
     }
   }
-  // The waves' partial sums meet in LDS: waves 4..7 hand theirs to waves 0..3, which then
-  // finish row group a = w (rows lr + 8 w) each and hand their other three groups over.
+  // The waves' partial sums meet in LDS: waves 4..7 hand theirs to waves 0..3 (up to 16
+  // coordinates they have none); then every wave finishes the rows lr + 8 (w % 4) of half of the
+  // columns, from what waves 0..3 hand over.
   __syncthreads();
-  if (w >= 4) {
+  if (nk > 16) {
+    if (w >= 4) {
 #pragma unroll
-    for (int o = 0; o < 32; ++o) sm[((w - 4) * 32 + o) * 64 + lane] = acc[o >> 3][o & 7];
-  }
-  __syncthreads();
-  if (w < 4) {
-#pragma unroll
-    for (int o = 0; o < 32; ++o) acc[o >> 3][o & 7] += sm[(w * 32 + o) * 64 + lane];
-  }
-  __syncthreads();
-  // slot of (source wave q, group a != q)
-  auto slot = [&](int q, int a) { return sm + ((q * 3 + (a < q ? a : a - 1)) * 8) * 64 + lane; };
-  double v[8];  // this wave's own part of its group, then the sums
-#pragma unroll
-  for (int b = 0; b < 8; ++b) v[b] = 0.0;
-  if (w < 4) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-      if (a != w) {
-#pragma unroll
-        for (int b = 0; b < 8; ++b) slot(w, a)[b * 64] = acc[a][b];
-      } else {
-#pragma unroll
-        for (int b = 0; b < 8; ++b) v[b] = acc[a][b];
-      }
-  }
-  __syncthreads();
-  double (*cs)[DF_COLS] = (double (*)[DF_COLS])(sm + 4 * 3 * 8 * 64);
-  if (w < 4) {
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      double s = 0.0;  // in the order of the waves, whichever of them adds
-#pragma unroll
-      for (int q = 0; q < 4; ++q) s += q == w ? v[b] : slot(q, w)[b * 64];
-      v[b] = s;
+      for (int o = 0; o < 32; ++o) sm[((w - 4) * 32 + o) * 64 + lane] = acc[o >> 3][o & 7];
     }
-    dist_emit_f64(d, c, r0, c0, w, lane, v, cs);
+    __syncthreads();
+    if (w < 4) {
+#pragma unroll
+      for (int o = 0; o < 32; ++o) {
+        acc[o >> 3][o & 7] += sm[(w * 32 + o) * 64 + lane];
+        if (o % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // at most eight reads ahead
+      }
+    }
+    __syncthreads();
+  }
+  if (w < 4) {
+#pragma unroll
+    for (int o = 0; o < 32; ++o) sm[(w * 32 + o) * 64 + lane] = acc[o >> 3][o & 7];
   }
   __syncthreads();
+  double v[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const int o = 8 * (w & 3) + 4 * (w >> 2) + b;
+    v[b] = 0.0;  // in the order of the waves
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[b] += sm[(q * 32 + o) * 64 + lane];
+  }
+  double (*rs)[2][32] = (double (*)[2][32])(sm + 4 * 32 * 64);
+  double (*cs)[DF_COLS] = (double (*)[DF_COLS])(sm + 4 * 32 * 64 + 2 * 2 * 32);
+  dist_emit_f64(d, c, r0, c0, w, lane, v, rs, cs);
+  __syncthreads();
+  if (tid < DF_ROWS) {
+    ts[ch * TILE + r0 + tid] = rs[0][0][tid] + rs[0][1][tid];
+    if (d.cross) ts[(2 + ch) * TILE + r0 + tid] = rs[1][0][tid] + rs[1][1][tid];
+  }
   if (!d.cross && tid < DF_COLS)
-    (d.tsum + (int64_t)c.t * d.tsum_stride)[(2 + rq) * TILE + c0 + tid] =
-        (cs[0][tid] + cs[1][tid]) + (cs[2][tid] + cs[3][tid]);
+    ts[(2 + rq) * TILE + c0 + tid] = (cs[0][tid] + cs[1][tid]) + (cs[2][tid] + cs[3][tid]);
 }
 
-// DF_PARTS units per stored tile; a grid smaller than the `units` of all tests (one dispatch
-// holds fewer than 2^32 work-items) strides over them.
+// DF_PARTS units per stored tile.  first: the dispatch's first unit (one dispatch holds fewer than
+// 2^32 work-items; a loop over units in the kernel had the constants of exp and sqrt hoisted out
+// of it and 27 registers spilled).
 template <bool GATHER>
 __global__ void __launch_bounds__(DF_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 k_dist_f64(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs, int ntests,
-           int64_t units) {
+           int64_t first) {
   __shared__ __attribute__((aligned(16))) double sm[DF_NBUF * DF_BUF];
-  static_assert(4 * 32 * 64 <= DF_NBUF * DF_BUF, "the partial sums fit the operand buffers");
-  for (int64_t g = blockIdx.x; g < units; g += gridDim.x) {
-    const int64_t u = xcd_grouped(g, units);
-    const int64_t bid = u / DF_PARTS;
-    const int ti = find_test(offs, ntests, bid);
-    const TestDesc& d = descs[ti];
-    dist_part_f64<GATHER>(d, tile_ctx(d, bid - offs[ti]), (int)(u % DF_PARTS), sm);
-    __syncthreads();  // the next unit's loads reuse the buffers
-  }
+  static_assert(4 * 32 * 64 + 2 * 2 * 32 + 4 * DF_COLS <= DF_NBUF * DF_BUF,
+                "the partial sums fit the operand buffers");
+  const int64_t u = first + xcd_grouped(blockIdx.x, gridDim.x);
+  const int64_t bid = u / DF_PARTS;
+  const int ti = find_test(offs, ntests, bid);
+  const TestDesc& d = descs[ti];
+  dist_part_f64<GATHER>(d, tile_ctx(d, bid - offs[ti]), (int)(u % DF_PARTS), sm);
+}
+template <bool GATHER>
+static void launch_dist_f64(int64_t blocks, hipStream_t st, const TestDesc* d, const int64_t* offs,
+                            int n) {
+  const int64_t units = blocks * DF_PARTS, most = 1 << 22;  // per dispatch
+  for (int64_t first = 0; first < units; first += most)
+    hipLaunchKernelGGL(k_dist_f64<GATHER>,
+                       dim3((unsigned)(units - first < most ? units - first : most)),
+                       dim3(DF_THREADS), 0, st, d, offs, n, first);
 }
 
 // Shape of a launch by its grid (stored tiles of all tests): half tiles while two workgroups per
@@ -1200,10 +1224,7 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
     else if (gop == GOP_BF16)
       hipLaunchKernelGGL(k_gram_super<false>, g, b, 0, st, d, offs, n);
   } else if (gop == GOP_F64) {
-    // the launch table counts stored tiles
-    const int64_t units = blocks * DF_PARTS;
-    hipLaunchKernelGGL(k_dist_f64<false>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
-                       dim3(DF_THREADS), 0, st, d, offs, n, units);
+    launch_dist_f64<false>(blocks, st, d, offs, n);
   } else if (gop == GOP_F16PAIR) {
     if (dual) launch_ring<true, true>(blocks, st, d, offs, n);
     else launch_ring<true, false>(blocks, st, d, offs, n);
@@ -1217,10 +1238,8 @@ void launch_gram(int gop, bool super_tiles, int64_t blocks, hipStream_t st, cons
 void launch_gram_sums(int gop, int64_t blocks, hipStream_t st, const TestDesc* d,
                       const int64_t* offs, int n) {
   if (blocks <= 0) return;
-  const int64_t units = blocks * DF_PARTS;
   if (gop == GOP_F64)
-    hipLaunchKernelGGL(k_dist_f64<true>, dim3((unsigned)(units < (1 << 22) ? units : (1 << 22))),
-                       dim3(DF_THREADS), 0, st, d, offs, n, units);
+    launch_dist_f64<true>(blocks, st, d, offs, n);
   else if (gop == GOP_F16PAIR)
     launch_ring_shape<true, 128, 2, 4, false, true>(blocks, st, d, offs, n);
   else
