@@ -698,6 +698,25 @@ static const Fork* thread_fork() {
   return state == 1 ? &f : nullptr;
 }
 
+// The fork to run a pass with, or NULL: on the tests' own stream.  Forking costs an event record
+// and a wait on either stream, about 15 us of an eager pass and 8 us of a graph's, which a walk
+// over few tiles does not take.  Eager, 200 splits: 400 rows 109 us forked, 94 not; 1200 rows 115
+// and 112; 1600 rows 119 and 122 (10000 splits: 116 / 104, 156 / 155, 193 / 194).  As a graph: 400
+// rows 102 and 95, 800 rows 105 and 106, 1200 rows 109 and 114.  Split streams that follow the
+// block stage (split_late) are always forked.
+constexpr int32_t FORK_MIN_TILES = 11, FORK_MIN_TILES_GRAPH = 6;
+const Fork* batch_fork(const Batch& b, bool graph) {
+  int32_t nt = 0;
+  int64_t member = 0, super = 0;
+  for (const TestPlan& P : b.plans) {
+    nt = std::max(nt, P.d.nt);
+    member += P.wg[S_MEMBER];
+    super += P.wg[S_GRAM_F32S] + P.wg[S_GRAM_BF16S];
+  }
+  if (nt < (graph ? FORK_MIN_TILES_GRAPH : FORK_MIN_TILES) && !split_late(member, super)) return nullptr;
+  return thread_fork();
+}
+
 // ------------------------------------------------------------------ stage timing
 // Each enqueued pass takes its own set of stage events, so passes enqueued back to back
 // without a wait in between (the asynchronous entry points) are all timed; the sets are
@@ -808,7 +827,7 @@ static etest_status run_device(const etest_request* reqs, int64_t n, hipStream_t
   b.desc_by_kernel = n == 1;
   s = place_batch(&b, st, true);
   if (s != ETEST_OK) return s;
-  enqueue_batch(b, st, import_words, profile_events(), thread_fork());
+  enqueue_batch(b, st, import_words, profile_events(), batch_fork(b, false));
   hipError_t e = hipGetLastError();
   free_batch(&b, st, true);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -973,7 +992,7 @@ static etest_status graph_entry(const etest_request* reqs, int64_t n, hipStream_
   HIP_OK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "capture stream");
   hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    enqueue_batch(g.batch, cap, nullptr, nullptr, thread_fork());
+    enqueue_batch(g.batch, cap, nullptr, nullptr, batch_fork(g.batch, true));
     e = hipStreamEndCapture(cap, &g.graph);
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
@@ -1184,7 +1203,7 @@ static etest_status enqueue_async(const etest_request* req, int kind, etest_resu
   b.plans[0].d.out6 = (double*)d_out;
   s = place_batch(&b, st, true);
   if (s != ETEST_OK) return s;
-  enqueue_batch(b, st, nullptr, profile_events(), thread_fork());
+  enqueue_batch(b, st, nullptr, profile_events(), batch_fork(b, false));
   free_batch(&b, st, true);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("enqueue: ") + hipGetErrorString(e));
@@ -1210,7 +1229,7 @@ static etest_status enqueue_batch_async(const etest_request* reqs, int64_t n,
   for (int64_t t = 0; t < n; ++t) b.plans[(size_t)t].d.out6 = (double*)(d_outs + t);
   s = place_batch(&b, st, true);
   if (s != ETEST_OK) return s;
-  enqueue_batch(b, st, nullptr, profile_events(), thread_fork());
+  enqueue_batch(b, st, nullptr, profile_events(), batch_fork(b, false));
   free_batch(&b, st, true);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("enqueue: ") + hipGetErrorString(e));

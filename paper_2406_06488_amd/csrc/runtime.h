@@ -225,6 +225,7 @@ void enqueue_stages(const TestDesc* D, const int64_t* d_offs, const int64_t* h_o
 // Enqueue every stage.  import_words: caller splits for a single test (or null).
 void enqueue_batch(const Batch& b, hipStream_t st, const uint32_t* import_words = nullptr,
                    const StageEvents* events = nullptr, const Fork* fork = nullptr);
+const Fork* batch_fork(const Batch& b, bool graph);  // the calling thread's, or none
 void free_batch(Batch* b, hipStream_t st, bool stream_ordered);
 etest_status dev_to_result(const DevResult& r, etest_result* out);
 
