@@ -275,8 +275,10 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 // lanes of a fragment read hit distinct bank groups.  Eight waves (2 x 4 of TR/2 x 32), two on
 // every SIMD per workgroup: one wave's issue, waits and epilogue run under another's products.
 // TR = 128: a stored tile per workgroup; TR = 64: half of one (64 rows x 128 columns).
-//  - Grids of at most one workgroup per CU: the ring takes most of a CU's LDS (NBUF 5 or 6), as
-//    there is no second workgroup to hide the loads' latency; half tiles while they fit.
+//  - Grids of at most one workgroup per CU: a deep ring (NBUF 4 or 6), as there is no second
+//    workgroup to hide the loads' latency, which leaves LDS for the split stream's workgroups
+//    (16 KB each) beside it; half tiles while they fit.  (Whole tiles with NBUF 5: 35 instead of
+//    36 us alone, but no room beside: FP32 MMD 344 + 2213 x 816 175 -> 162 us with 4.)
 //  - Larger grids: NBUF 2; two whole tiles share a CU.
 // Every shape adds an entry's products in the same order (chunk by chunk; hi hi, hi lo, lo hi)
 // and forms values and sums alike, so all agree bit for bit, as does the super-tile kernel.
@@ -284,7 +286,7 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 // Large grids run the K loop at 1.1 PFLOP/s of fp16 products, the rate of the library's GEMM on
 // this card (power-limited: the clock drops to 1.9 GHz).  Measured (FP32 form), against a
 // kernel of four waves of 64 x 64 with register-staged 32-wide slices: 10 tiles at p = 1000 51 ->
-// 20 us, 136 tiles at p = 512 38 -> 22 us, 256 tiles (cross test) at p = 1000 55 -> 35 us, 528
+// 20 us, 136 tiles at p = 512 38 -> 22 us, 256 tiles (cross test) at p = 1000 55 -> 36 us, 528
 // tiles at p = 1024 96 -> 84 us, 7236 tiles at p = 512 (standard test) 461 -> 421 us (by this
 // ring with four waves, three workgroups to a CU: 97 and 465).
 //
@@ -1189,7 +1191,7 @@ static void launch_dist_f64(int64_t blocks, hipStream_t st, const TestDesc* d, c
 
 // Shape of a launch by its grid (stored tiles of all tests): half tiles while two workgroups per
 // tile are at most one per CU; whole tiles with a deep ring up to one per CU (256 tiles at p =
-// 1000: 35 us, half tiles three to a CU 44); whole tiles, two to a CU, beyond (990 tiles at p =
+// 1000: 36 us, half tiles three to a CU 44); whole tiles, two to a CU, beyond (990 tiles at p =
 // 512 / 1024: 69 / 112 us, half tiles 77 / 128; 528 tiles 54 / 84, half tiles 49 / 79, but with
 // the split stream beside them 91 against 104 at p = 1000).
 constexpr int64_t GRAM_RING_MAX_HALVES = 128, GRAM_RING_MAX_TILES = 256;
@@ -1209,7 +1211,7 @@ static void launch_ring(int64_t blocks, hipStream_t st, const TestDesc* d, const
   if (blocks <= GRAM_RING_MAX_HALVES)
     launch_ring_shape<F16, 64, 6, 2, DUAL>(blocks, st, d, offs, n);
   else if (blocks <= GRAM_RING_MAX_TILES)
-    launch_ring_shape<F16, 128, 5, 2, DUAL>(blocks, st, d, offs, n);
+    launch_ring_shape<F16, 128, 4, 2, DUAL>(blocks, st, d, offs, n);
   else
     launch_ring_shape<F16, 128, 2, 4, DUAL>(blocks, st, d, offs, n);
 }
