@@ -242,7 +242,9 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 //
 // Measured at n = 2000 and 201 permutations: 1007 us with one workgroup per permutation and
 // 8 rows (a row of Lt staged for each of them, every entry read), 416 us in this form without
-// the reads one permutation ahead and with the pairs' ownership tested per entry, 201 us now.
+// the reads one permutation ahead and with the pairs' ownership tested per entry, 201 us with it
+// tested row by row on the scalar unit, 155 us now (LDS 65% busy, vector ALU 60%).  Four rows
+// interleaved, so that one 16-byte read gathers them all: 314 us, 54 LDS cycles per read.
 constexpr int HT_THREADS = 512;
 constexpr int HT_COLS = 256;   // columns per slice
 constexpr int HT_BATCH = 4;    // permutations per wave whose sums are combined together
@@ -319,41 +321,40 @@ k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n
   }
   __syncthreads();
   const int c0 = sl * HT_COLS, j0 = c0 + 4 * lane;
-  const T* kcol = kx + j0;
   // this unit's permutations [b0, b1); wave w takes batches of HT_BATCH
   const int per = ((nperm + nps - 1) / nps + HT_BATCH - 1) / HT_BATCH * HT_BATCH;
   const int b0 = ps * per, b1 = min(nperm, b0 + per);
   constexpr int STEP = HT_BATCH * (HT_THREADS / 64);
   struct Tables {
     ushort4 pj[HT_BATCH];
-    uint32_t iv[HT_BATCH][G / 2];
+    uint16_t i;  // lane q G + g: the row of Kt that meets row l0 + g of S in permutation q
   };
+  const int tq = lane / G % HT_BATCH, tg = lane % G;
   auto tables = [&](int bb, Tables& t) {
 #pragma unroll
-    for (int q = 0; q < HT_BATCH; ++q) {
-      const int64_t b = min(bb + q, nperm - 1);
-      t.pj[q] = *(const ushort4*)(p16 + b * ld + j0);
-      const uint32_t* ip = (const uint32_t*)(inv16 + b * ld + l0);
-#pragma unroll
-      for (int g = 0; g < G / 2; ++g) t.iv[q][g] = ip[g];
-    }
+    for (int q = 0; q < HT_BATCH; ++q)
+      t.pj[q] = *(const ushort4*)(p16 + (int64_t)min(bb + q, nperm - 1) * ld + j0);
+    t.i = inv16[(int64_t)min(bb + tq, nperm - 1) * ld + l0 + tg];
   };
-  // rows of Kt of permutation q, those that own no pair of the slice left out: bit g of the
-  // result; their loads go to row 0 (always the same line)
-  auto rows = [&](const Tables& t, int q, T (&kv)[G][4]) {
-    uint32_t on = 0;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int i = __builtin_amdgcn_readfirstlane((int)((t.iv[q][g / 2] >> (16 * (g & 1))) & 0xFFFFu));
-      int d0 = c0 - i;  // cyclic distance of the slice's first column
-      d0 += d0 < 0 ? n : 0;
-      const bool a = i < n && ((i / HT_COLS) == sl || 2 * d0 <= n);
-      on |= a ? 1u << g : 0u;
-      load4(kcol + (int64_t)(a ? i : 0) * ld, kv[g]);
-    }
-    return on;
+  // the batch's rows of Kt, all in one step over the lanes: bit q G + g of the result tells that
+  // the row owns a pair of the slice, off its place; the others' loads go to row 0 (always the
+  // same line).  (Row by row on the scalar unit this was 14 instructions each, two thirds of the
+  // scalar unit's time.)
+  auto choose = [&](const Tables& t, uint32_t& off) {
+    const int i = t.i;
+    int d0 = c0 - i;  // cyclic distance of the slice's first column
+    d0 += d0 < 0 ? n : 0;
+    const bool a = i < n && ((i / HT_COLS) == sl || 2 * d0 <= n);
+    off = (a ? (uint32_t)i : 0u) * (uint32_t)(ld * sizeof(T));
+    return (uint32_t)__ballot(a);
   };
-  auto terms = [&](const Tables& t, int q, uint32_t on, const T (&kv)[G][4]) {
+  auto rows = [&](uint32_t off, int q, T (&kv)[G][4]) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+      load4((const T*)((const char*)kx + (uint32_t)__builtin_amdgcn_readlane(off, q * G + g)) + j0, kv[g]);
+  };
+  auto terms = [&](const Tables& t, int q, uint32_t all, const T (&kv)[G][4]) {
+    const uint32_t on = all >> (q * G);
     const int pk[4] = {t.pj[q].x, t.pj[q].y, t.pj[q].z, t.pj[q].w};
     double a = 0.0;
 #pragma unroll
@@ -366,24 +367,27 @@ k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n
   };
   Tables t, tn;
   T ka[G][4], kb[G][4];
-  uint32_t oa = 0, ob = 0;
+  uint32_t off = 0, on = 0;
   int bb = b0 + w * HT_BATCH;
   if (bb < b1) {
     tables(bb, t);
-    oa = rows(t, 0, ka);
+    on = choose(t, off);
+    rows(off, 0, ka);
   }
-  static_assert(HT_BATCH == 4, "the batch is written out");
+  static_assert(HT_BATCH == 4 && HT_BATCH * G <= 32, "the batch is written out, its rows are bits");
   for (; bb < b1; bb += STEP) {
     double acc[HT_BATCH];
     tables(min(bb + STEP, nperm - 1), tn);
-    ob = rows(t, 1, kb);
-    acc[0] = terms(t, 0, oa, ka);
-    oa = rows(t, 2, ka);
-    acc[1] = terms(t, 1, ob, kb);
-    ob = rows(t, 3, kb);
-    acc[2] = terms(t, 2, oa, ka);
-    oa = rows(tn, 0, ka);
-    acc[3] = terms(t, 3, ob, kb);
+    rows(off, 1, kb);
+    acc[0] = terms(t, 0, on, ka);
+    rows(off, 2, ka);
+    acc[1] = terms(t, 1, on, kb);
+    rows(off, 3, kb);
+    acc[2] = terms(t, 2, on, ka);
+    const uint32_t cur = on;
+    on = choose(tn, off);
+    rows(off, 0, ka);
+    acc[3] = terms(t, 3, cur, kb);
     t = tn;
     // sums over the lanes, the four permutations together: each step sends half of the
     // values still held, so lanes 16 k .. + 15 end with permutation (k >> 1) + 2 (k & 1)
@@ -477,10 +481,11 @@ void launch_hsic_terms(bool f64, const TestDesc* d, const void* kx, int64_t n, i
                        hipStream_t st) {
   const int64_t g = f64 ? HT_G<double> : HT_G<float>;
   const int nsl = (int)((n + HT_COLS - 1) / HT_COLS), ngrp = (int)((n + g - 1) / g);
-  // permutation ranges per (slice, row group): enough units for four rounds of the chip's
-  // 512 resident workgroups, but at least one batch for each of a workgroup's waves
+  // permutation ranges per (slice, row group): enough units for three rounds of the chip's
+  // 512 resident workgroups, but at least one batch for each of a workgroup's waves; each range
+  // stages the rows again (n = 2000: 2000 units in one range 155 us, 4000 in two 169)
   int nps = 1;
-  while (nps < 64 && (int64_t)nsl * ngrp * nps < 2048 &&
+  while (nps < 64 && (int64_t)nsl * ngrp * nps < 1536 &&
          nperm >= 2 * nps * HT_BATCH * (HT_THREADS / 64))
     nps *= 2;
   const int64_t units = (int64_t)nsl * ngrp * nps;
