@@ -256,32 +256,41 @@ __global__ void __launch_bounds__(PERM_THREADS) k_perm_mfma(const TestDesc* __re
 
 // FP64: v_mfma_f64_16x16x4f64, whose products with the split bits (0.0 or 1.0) are exact.
 // The work units are those of 32-row strips (unit rks = row unit rks / PC_STRIPS, strip
-// rks % PC_STRIPS), so that even a test of two tiles spreads over several CUs; a workgroup
-// covers the 256 columns of a chunk, each wave 64 of them: 2 row blocks x 4 column blocks of
+// rks % PC_STRIPS), so that even a test of two tiles spreads over several CUs; workgroup
+// (unit, quarter) covers 64 of the 256 columns of a chunk, each wave 16 of them: 2 row blocks of
 // 16 x 16.  The centred tile is stored in the order the A operand is read (k_center.hip), so
 // a wave loads its fragments straight from memory, 32 columns ahead of the products, and the
 // four waves of the workgroup meet in the L1: no LDS and no barrier.  Bound by the FP64 MFMA
 // rate on large tests, by one unit's chain on small ones.  Measured against one thread per
-// split and an FMA per entry: 1000 + 1000 rows, B = 200: 208 -> 31 us; 100 + 100 rows, B =
-// 1000: 71 -> 14 us.
+// split and an FMA per entry: 1000 + 1000 rows, B = 200: 208 -> 29 us; 100 + 100 rows, B =
+// 1000: 71 -> 6.5 us; with whole units of 256 columns per workgroup, 64 per wave: 33 and 13.3,
+// and 1500 + 1500 rows, B = 1000: 287, now 187 (units of several chunks, two per CU).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __global__ void __launch_bounds__(256) k_perm_f64(const TestDesc* __restrict__ descs,
                                                   const int64_t* __restrict__ offs, int ntests,
-                                                  const int32_t* __restrict__ pcr) {
-  const int ti = find_test(offs, ntests, blockIdx.x);
+                                                  const int32_t* __restrict__ pcr, int64_t units,
+                                                  int quarter) {
+  // the quarters of eight units, one per XCD, follow each other: each XCD reads its unit's tiles
+  // once from memory (quarter >= 0: a dispatch of that quarter alone)
+  const int64_t g = blockIdx.x;
+  const int64_t unit = quarter < 0 ? g / (4 * NUM_XCD) * NUM_XCD + g % NUM_XCD : g;
+  const int qr = quarter < 0 ? (int)(g / NUM_XCD % 4) : quarter;
+  if (unit >= units) return;
+  const int ti = find_test(offs, ntests, unit);
   const TestDesc& d = descs[ti];
   const int pc0 = pcr ? pcr[2 * ti] : 0;
   const int pcn = pcr ? pcr[2 * ti + 1] : (int)(d.B_pad / NP);
   const int ncr = (pcn + d.cc - 1) / d.cc;
-  const int64_t local = blockIdx.x - offs[ti];
+  const int64_t local = unit - offs[ti];
   const int rks = (int)(local / ncr);
   const int cr = (int)(local % ncr);
   const int h = rks % PC_STRIPS;
   int i, j0, j1;
   rowk_coords(d, rks / PC_STRIPS, &i, &j0, &j1);
   const int cb = pc0 + cr * d.cc, ce = min(pc0 + pcn, cb + d.cc);
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, cl = lane & 15, kq = lane >> 4;
+  const int lane = threadIdx.x & 63, cl = lane & 15, kq = lane >> 4;
+  const int cg = qr * 4 + (threadIdx.x >> 6);  // column group of the chunk
   const int64_t BP = d.B_pad;
   // fragments of row blocks 2 h and 2 h + 1 of tile (i, j0); successive j are adjacent tiles
   const double2* A0 = (const double2*)((const double*)d.planes +
@@ -289,39 +298,32 @@ __global__ void __launch_bounds__(256) k_perm_f64(const TestDesc* __restrict__ d
                       2 * h * 16 * 64 + lane;
   const int steps = (j1 - j0) * TILE_WORDS;  // of 32 columns: one membership word each
   for (int c = cb; c < ce; ++c) {
-    const int64_t col = (int64_t)c * NP + w * 64 + cl;  // of column block 0
+    const int64_t col = (int64_t)c * NP + cg * 16 + cl;
     const uint32_t* Zj = d.Z + (int64_t)j0 * TILE_WORDS * BP + col;
-    f64x4 acc[2][4];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) acc[rb][nb] = f64x4{0.0, 0.0, 0.0, 0.0};
+    f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
     double2 a[2][4], an[2][4];
-    uint32_t z[4], zn[4];
-    auto load = [&](int s, double2 (&x)[2][4], uint32_t (&y)[4]) {
+    uint32_t z, zn;
+    auto load = [&](int s, double2 (&x)[2][4], uint32_t& y) {
       const double2* A = A0 + (int64_t)(s >> 2) * (TILE * TILE / 2) + (s & 3) * 4 * 64;
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp) x[rb][kp] = A[(rb * 16 + kp) * 64];
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) y[nb] = Zj[(int64_t)s * BP + 16 * nb];
+      y = Zj[(int64_t)s * BP];
     };
-    auto multiply = [&](const double2 (&x)[2][4], const uint32_t (&y)[4]) {
+    auto multiply = [&](const double2 (&x)[2][4], uint32_t y) {
       // columns 8 kp + 2 kq + e of the step: bit 8 kp + e of the shifted word
 #pragma unroll
       for (int kp = 0; kp < 4; ++kp)
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 2; ++e) {
+          const int bit = __builtin_amdgcn_sbfe((int)(y >> (2 * kq)), 8 * kp + e, 1);
+          const double b = __hiloint2double(bit & 0x3FF00000, 0);
 #pragma unroll
-          for (int nb = 0; nb < 4; ++nb) {
-            const int bit = __builtin_amdgcn_sbfe((int)(y[nb] >> (2 * kq)), 8 * kp + e, 1);
-            const double b = __hiloint2double(bit & 0x3FF00000, 0);
-#pragma unroll
-            for (int rb = 0; rb < 2; ++rb)
-              acc[rb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e ? x[rb][kp].y : x[rb][kp].x, b,
-                                                                 acc[rb][nb], 0, 0, 0);
-          }
+          for (int rb = 0; rb < 2; ++rb)
+            acc[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(e ? x[rb][kp].y : x[rb][kp].x, b,
+                                                           acc[rb], 0, 0, 0);
+        }
     };
     load(0, a, z);
     for (int s = 0; s < steps; s += 2) {  // steps is a multiple of 4
@@ -331,21 +333,15 @@ __global__ void __launch_bounds__(256) k_perm_f64(const TestDesc* __restrict__ d
       multiply(an, zn);
     }
     // fold the row weights: element e of an accumulator is row kq + 4 e of its row block
-    double q[4];
+    const uint32_t zi = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col] >> kq;
+    double f = 0.0;
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      const uint32_t zi = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col + 16 * nb] >> kq;
-      double f = 0.0;
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f += (zi >> (16 * rb + 4 * e)) & 1u ? acc[rb][nb][e] : 0.0;
-      f += __shfl_xor(f, 16, 64);
-      f += __shfl_xor(f, 32, 64);
-      q[nb] = f;
-    }
-    const double mine = kq == 0 ? q[0] : kq == 1 ? q[1] : kq == 2 ? q[2] : q[3];
-    d.part[(int64_t)rks * BP + col + 16 * kq] = mine;
+      for (int e = 0; e < 4; ++e) f += (zi >> (16 * rb + 4 * e)) & 1u ? acc[rb][e] : 0.0;
+    f += __shfl_xor(f, 16, 64);
+    f += __shfl_xor(f, 32, 64);
+    if (kq == 0) d.part[(int64_t)rks * BP + col] = f;
   }
 }
 
@@ -354,7 +350,15 @@ void launch_perm(int variant, int64_t blocks, hipStream_t st, const TestDesc* d,
   if (blocks <= 0) return;
   const dim3 g((unsigned)blocks), b(256);
   switch (variant) {
-    case 0: hipLaunchKernelGGL(k_perm_f64, g, b, 0, st, d, offs, ntests, pcr); break;
+    case 0:
+      // all quarters in one dispatch while it holds fewer than 2^32 work-items
+      if (blocks <= 1 << 20)
+        hipLaunchKernelGGL(k_perm_f64, dim3((unsigned)((blocks + NUM_XCD - 1) / NUM_XCD * 4 * NUM_XCD)),
+                           b, 0, st, d, offs, ntests, pcr, blocks, -1);
+      else
+        for (int q = 0; q < 4; ++q)
+          hipLaunchKernelGGL(k_perm_f64, g, b, 0, st, d, offs, ntests, pcr, blocks, q);
+      break;
     case 2: hipLaunchKernelGGL(k_perm_mfma<2>, g, dim3(PERM_THREADS), 0, st, d, offs, ntests, pcr); break;
     case 3: hipLaunchKernelGGL(k_perm_mfma<3>, g, dim3(PERM_THREADS), 0, st, d, offs, ntests, pcr); break;
     default: break;
