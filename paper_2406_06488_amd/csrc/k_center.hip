@@ -41,6 +41,13 @@ __device__ inline uint32_t pack_h2(_Float16 a, _Float16 b) {
   return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
 }
 
+// Four values, at most 2^8 in size, to fp8 E4M3: the hardware's conversion, which up to 448 gives
+// f32_to_e4m3's codes (all 2.3e9 floats compared; a zero keeps its sign).
+__device__ inline uint32_t pack_e4m3(const float* x) {
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(
+      x[2], x[3], __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], 0, false), true);
+}
+
 // One workgroup per half tile (rows 64 rh .. + 63: fragment row blocks 2 rh and 2 rh + 1),
 // so that the grid has twice as many workgroups as stored tiles in flight; on grids
 // planned with one workgroup per tile (past 2^22 tiles) a workgroup takes both halves.
@@ -99,7 +106,7 @@ __global__ void __launch_bounds__(256) k_center_split(const TestDesc* __restrict
                           raw[it][1].x, raw[it][1].y, raw[it][1].z, raw[it][1].w};
       const double ca = crow[r];
       _Float16 hi[8], lo[8];
-      uint32_t lo8[8];
+      float lo8[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int col = c0l + e;
@@ -110,7 +117,7 @@ __global__ void __launch_bounds__(256) k_center_split(const TestDesc* __restrict
         // absorbs, since it is formed from the exact FP64 remainder x - hi
         hi[e] = (_Float16)to_f32(x);
         const double rem = x - (double)(float)hi[e];
-        if (f8lo) lo8[e] = f32_to_e4m3(to_f32(rem * 32.0));
+        if (f8lo) lo8[e] = to_f32(rem * 32.0);
         else lo[e] = (_Float16)to_f32(rem * 2048.0);
       }
       uint4 w;
@@ -124,8 +131,8 @@ __global__ void __launch_bounds__(256) k_center_split(const TestDesc* __restrict
         const int64_t off = ((int64_t)((mb * 2 + kb) * 2 + hf) * 64 + (lane & 31) + 32 * g) * 16 +
                             (c0l & 15);
         uint2 b;
-        b.x = lo8[0] | (lo8[1] << 8) | (lo8[2] << 16) | (lo8[3] << 24);
-        b.y = lo8[4] | (lo8[5] << 8) | (lo8[6] << 16) | (lo8[7] << 24);
+        b.x = pack_e4m3(lo8);
+        b.y = pack_e4m3(lo8 + 4);
         *(uint2*)(Plo + off) = b;
       } else {
         w.x = pack_h2(lo[0], lo[1]); w.y = pack_h2(lo[2], lo[3]);
