@@ -74,15 +74,30 @@ struct Neu {
   __device__ double value() const { return s + c; }
 };
 
-// One workgroup per test: S_XX, S_YY, S_XY and the observed statistic.
+// One workgroup per test: S_XX, S_YY, S_XY and the observed statistic.  Bound by latency: all
+// loads first, then one barrier to hand the partial sums to a wave per sum (and one for the
+// tiles' maxima), one for the results; with a barrier per level of the combining trees three tiles
+// took 4.4 us, now 3.1, 528 tiles 7.8, now 6.5, and 256 tests 51, now 36.
 __global__ void __launch_bounds__(256) k_observed(const TestDesc* __restrict__ descs,
                                                   const int64_t* __restrict__ sel, int ntests) {
-  __shared__ double red[3][256][2];
+  __shared__ double red[3][256][2], sum[3];
+  __shared__ float mx[256];
   if (sel && sel[blockIdx.x + 1] == sel[blockIdx.x]) return;
   const TestDesc d = descs[blockIdx.x];
   const int tid = threadIdx.x;
   Neu sxx{0, 0}, syy{0, 0}, sxy{0, 0};
   const int64_t xend = (int64_t)d.tx * TILE, npad = (int64_t)d.nt * TILE;
+  float m = 0.0f;
+  if (d.prec != PREC_F64) {
+    const int nmax = d.ntiles * TMAX_PER_TILE;
+    for (int base = tid; base < nmax; base += 256 * OBS_BATCH) {
+      float v[OBS_BATCH];
+#pragma unroll
+      for (int u = 0; u < OBS_BATCH; ++u) v[u] = base + 256 * u < nmax ? d.tmax[base + 256 * u] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < OBS_BATCH; ++u) m = fmaxf(m, v[u]);
+    }
+  }
   // The loads of OBS_BATCH positions are issued together before any of them is added (the
   // row sums were just written by other XCDs, so each load waits on a far cache); the
   // additions keep the order pos = tid, tid + 256, ... .
@@ -108,55 +123,50 @@ __global__ void __launch_bounds__(256) k_observed(const TestDesc* __restrict__ d
   red[0][tid][0] = sxx.s; red[0][tid][1] = sxx.c;
   red[1][tid][0] = syy.s; red[1][tid][1] = syy.c;
   red[2][tid][0] = sxy.s; red[2][tid][1] = sxy.c;
-  // pairwise combination of the compensated partials (fixed tree: reproducible)
-  for (int st = 128; st > 0; st >>= 1) {
-    __syncthreads();
-    if (tid < st)
-      for (int a = 0; a < 3; ++a) {
-        Neu u{red[a][tid][0], red[a][tid][1] + red[a][tid + st][1]};
-        u.add(red[a][tid + st][0]);
-        red[a][tid][0] = u.s;
-        red[a][tid][1] = u.c;
-      }
-  }
+  mx[tid] = m;
   __syncthreads();
-  if (tid < 3) d.obs[tid] = red[tid][0][0] + red[tid][0][1];
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if (w < 3) {
+    // pairwise combination of the compensated partials (fixed tree: reproducible)
+    auto at = [&](int k) { return Neu{red[w][lane + 64 * k][0], red[w][lane + 64 * k][1]}; };
+    auto join = [](Neu& u, double s, double c) {
+      u.c += c;
+      u.add(s);
+    };
+    Neu u = at(0), v = at(1);
+    const Neu u2 = at(2), v2 = at(3);
+    join(u, u2.s, u2.c);
+    join(v, v2.s, v2.c);
+    join(u, v.s, v.c);
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1) {
+      const double us = __shfl_down(u.s, st, 64), uc = __shfl_down(u.c, st, 64);
+      join(u, us, uc);
+    }
+    if (lane == 0) d.obs[w] = sum[w] = u.s + u.c;
+  } else if (d.prec != PREC_F64) {
+    // Scale of the fp16 planes of the FP32 / BF16 forms: a centred entry
+    // D - c_a - c_b + c0 (all of them within [0, max D] for distances and kernel values)
+    // is at most 4 max|D| in size; scaling by 2^e with 4 max|D| 2^e <= 2^14 keeps every
+    // plane value inside the fp16 range.
+    m = fmaxf(fmaxf(mx[lane], mx[lane + 64]), fmaxf(mx[lane + 128], mx[lane + 192]));
+#pragma unroll
+    for (int st = 1; st < 64; st <<= 1) m = fmaxf(m, __shfl_xor(m, st, 64));
+    if (lane == 0) {
+      const double bound = 4.0 * (double)m;
+      int e = 0;
+      if (bound > 0.0) e = 14 - (int)ceil(log2(bound));
+      e = e < -120 ? -120 : (e > 120 ? 120 : e);
+      d.obs[5] = ldexp(1.0, e);
+    }
+  }
   __syncthreads();
   if (tid == 0) {
     const double nx = d.nx, ny = d.ny;
-    const double txx = d.obs[0] / (nx * nx), tyy = d.obs[1] / (ny * ny);
-    const double txy = 2.0 * d.obs[2] / (nx * ny);
+    const double txx = sum[0] / (nx * nx), tyy = sum[1] / (ny * ny);
+    const double txy = 2.0 * sum[2] / (nx * ny);
     d.obs[3] = d.kind == KIND_ED ? (txy - txx) - tyy : (txx + tyy) - txy;
-    d.obs[4] = d.obs[0] + d.obs[1] + 2.0 * d.obs[2];  // R = sum of all pooled row sums
-  }
-  // Scale of the fp16 planes of the FP32 / BF16 forms: a centred entry
-  // D - c_a - c_b + c0 (all of them within [0, max D] for distances and kernel values)
-  // is at most 4 max|D| in size; scaling by 2^e with 4 max|D| 2^e <= 2^14 keeps every
-  // plane value inside the fp16 range.
-  __shared__ float mx[256];
-  float m = 0.0f;
-  if (d.prec != PREC_F64) {
-    const int nmax = d.ntiles * TMAX_PER_TILE;
-    for (int base = tid; base < nmax; base += 256 * OBS_BATCH) {
-      float v[OBS_BATCH];
-#pragma unroll
-      for (int u = 0; u < OBS_BATCH; ++u) v[u] = base + 256 * u < nmax ? d.tmax[base + 256 * u] : 0.0f;
-#pragma unroll
-      for (int u = 0; u < OBS_BATCH; ++u) m = fmaxf(m, v[u]);
-    }
-  }
-  mx[tid] = m;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) mx[tid] = fmaxf(mx[tid], mx[tid + s]);
-    __syncthreads();
-  }
-  if (tid == 0) {
-    const double bound = 4.0 * (double)mx[0];
-    int e = 0;
-    if (bound > 0.0) e = 14 - (int)ceil(log2(bound));
-    e = e < -120 ? -120 : (e > 120 ? 120 : e);
-    d.obs[5] = ldexp(1.0, e);
+    d.obs[4] = sum[0] + sum[1] + 2.0 * sum[2];  // R = sum of all pooled row sums
   }
 }
 
