@@ -7,6 +7,8 @@
 // efficient test does: p = (1 + #{b < B : stat*_b >= stat_B}) / (1 + B).
 #include "common.h"
 
+#include <algorithm>
+
 namespace et {
 
 // ------------------------------------------------------------------ standard test
@@ -136,15 +138,16 @@ __global__ void __launch_bounds__(1024) k_count(const double* __restrict__ stats
 // With the dense pooled matrix (Alg. 5 as printed: every tile of the nt x nt grid, D_YX
 // included) every tile holds both orders of its pairs and takes the diagonal-tile rule: the
 // X*X*, Y*Y* and X*Y* sub-blocks are read entry by entry and the Y*X* entries are skipped.
-// Padding entries are 0.  One wave per (tile, 32-row strip, 64 splits): every entry of the
-// strip is multiplied by each split's column bit as 0.0 or 1.0, which adds it exactly or leaves
-// the sum as it is, and added in FP64 -- on v_mfma_f64_16x16x4f64, 2 row blocks x 4 column
-// blocks of 16 x 16; s_y is the row's total less s_x.  No centring and no quadratic form: this
+// Padding entries are 0.  One workgroup per (tile, 32-row strip, 64 splits), 16 splits per wave:
+// every entry of the strip is multiplied by each split's column bit as 0.0 or 1.0, which adds it exactly or leaves
+// the sum as it is, and added in FP64 -- on v_mfma_f64_16x16x4f64, 2 row blocks of 16 x 16; s_y
+// is the row's total less s_x.  No centring and no quadratic form: this
 // is the per-split extraction of Alg. 5.  The lanes read their entries straight from the
-// stored tile (four adjacent columns each, FP32 entries converted once) and the waves of a
-// workgroup, 64 splits each, meet in the L1.  Bound by the FP64 MFMA rate; 211 us on the vector
-// ALU (one FMA per entry and split, one wave per SIMD) -> 34 us for 1000 + 1000 rows and 201
-// splits.
+// stored tile (four adjacent columns each, FP32 entries converted) and the waves of a workgroup
+// meet in the L1, the workgroups of a strip in one XCD's L2.  Bound by the FP64 MFMA rate; 211 us
+// on the vector ALU (one FMA per entry and split, one wave per SIMD) -> 28 us for 1000 + 1000
+// rows and 201 splits (34 with 64 splits per wave, where two rounds of the chip were one and a
+// bit).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // four adjacent entries
@@ -159,13 +162,12 @@ __device__ inline void load4(const double* p, double (&v)[4]) {
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ descs,
-                                                 double* __restrict__ part, int64_t sg) {
+                                                 double* __restrict__ part, int64_t sg,
+                                                 int64_t first) {
   const TestDesc& d = descs[0];
-  const int64_t sg4 = (sg + 3) / 4;  // groups of 64 split columns, four per workgroup
   const int64_t id = xcd_grouped(blockIdx.x, gridDim.x);
-  const int64_t g = (id % sg4) * 4 + (threadIdx.x >> 6);
-  const int64_t u = id / sg4;  // strip u: tile u / PC_STRIPS, rows 32 (u % PC_STRIPS) ..
-  if (g >= sg) return;
+  const int64_t g = id % sg;           // group of 64 split columns
+  const int64_t u = first + id / sg;  // strip u: tile u / PC_STRIPS, rows 32 (u % PC_STRIPS) ..
   const int t = (int)(u / PC_STRIPS), h = (int)(u % PC_STRIPS);
   int i, j;
   if (d.dense) {
@@ -175,40 +177,33 @@ __global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ de
     tile_coords(t, d.nt, &i, &j);
   }
   const int lane = threadIdx.x & 63, cl = lane & 15, kq = lane >> 4;
-  const int64_t BP = d.B_pad, col = g * 64 + cl;  // of column block 0; Z columns past B are 0
+  const int64_t BP = d.B_pad, col = g * 64 + (threadIdx.x >> 6) * 16 + cl;  // Z columns past B are 0
   // the strip's rows cl and 16 + cl, columns 4 kq .. + 3 of every 16
   const T* src = (const T*)d.D + (int64_t)t * TILE * TILE + (h * PC_ROWS + cl) * TILE + 4 * kq;
   const uint32_t* Zj = d.Z + (int64_t)j * TILE_WORDS * BP + col;
-  f64x4 acc[2][4];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) acc[rb][nb] = f64x4{0.0, 0.0, 0.0, 0.0};
+  f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
   // steps of 32 columns (one membership word), the next step's entries loaded ahead
   double a[2][2][4], an[2][2][4];
-  uint32_t z[4], zn[4];
-  auto load = [&](int s, double (&x)[2][2][4], uint32_t (&y)[4]) {
+  uint32_t z, zn;
+  auto load = [&](int s, double (&x)[2][2][4], uint32_t& y) {
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
       for (int q = 0; q < 2; ++q) load4(src + rb * 16 * TILE + 32 * s + 16 * q, x[rb][q]);
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) y[nb] = Zj[(int64_t)s * BP + 16 * nb];
+    y = Zj[(int64_t)s * BP];
   };
-  auto multiply = [&](const double (&x)[2][2][4], const uint32_t (&y)[4]) {
+  auto multiply = [&](const double (&x)[2][2][4], uint32_t y) {
     // column 16 q + 4 kq + e of the step: bit 16 q + e of the shifted word
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e) {
+        const int bit = __builtin_amdgcn_sbfe((int)(y >> (4 * kq)), 16 * q + e, 1);
+        const double b = __hiloint2double(bit & 0x3FF00000, 0);
 #pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-          const int bit = __builtin_amdgcn_sbfe((int)(y[nb] >> (4 * kq)), 16 * q + e, 1);
-          const double b = __hiloint2double(bit & 0x3FF00000, 0);
-#pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
-            acc[rb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rb][q][e], b, acc[rb][nb], 0, 0, 0);
-        }
+        for (int rb = 0; rb < 2; ++rb)
+          acc[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rb][q][e], b, acc[rb], 0, 0, 0);
+      }
   };
   load(0, a, z);
 #pragma unroll 1
@@ -230,36 +225,28 @@ __global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ de
     }
   // a tile holding both orders of its pairs: a diagonal tile, or any tile of the dense matrix
   const bool both_orders = d.dense || i == j;
-  double w[4][3];
+  const uint32_t zr = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col] >> kq;
+  double wxx = 0.0, wyy = 0.0, wxy = 0.0;
 #pragma unroll
-  for (int nb = 0; nb < 4; ++nb) {
-    const uint32_t zr = d.Z[(int64_t)(i * TILE_WORDS + h) * BP + col + 16 * nb] >> kq;
-    double wxx = 0.0, wyy = 0.0, wxy = 0.0;
+  for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double sx = acc[rb][nb][e], sy = tot[rb][e] - sx;
-        const bool member = (zr >> (16 * rb + 4 * e)) & 1u;
-        wxx += member ? sx : 0.0;
-        wyy += member ? 0.0 : sy;
-        wxy += member ? sy : both_orders ? 0.0 : sx;
-      }
-    const double scale = both_orders ? 1.0 : 2.0;
-    w[nb][0] = scale * wxx;
-    w[nb][1] = scale * wyy;
-    w[nb][2] = wxy;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      w[nb][k] += __shfl_xor(w[nb][k], 16, 64);
-      w[nb][k] += __shfl_xor(w[nb][k], 32, 64);
+    for (int e = 0; e < 4; ++e) {
+      const double sx = acc[rb][e], sy = tot[rb][e] - sx;
+      const bool member = (zr >> (16 * rb + 4 * e)) & 1u;
+      wxx += member ? sx : 0.0;
+      wyy += member ? 0.0 : sy;
+      wxy += member ? sy : both_orders ? 0.0 : sx;
     }
-  }
-  const int64_t s = col + 16 * kq;  // this lane writes column block kq
-  if (s <= d.B) {
+  const double scale = both_orders ? 1.0 : 2.0;
+  double w[3] = {scale * wxx, scale * wyy, wxy};
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      part[(u * 3 + k) * BP + s] = kq == 0 ? w[0][k] : kq == 1 ? w[1][k] : kq == 2 ? w[2][k] : w[3][k];
+  for (int k = 0; k < 3; ++k) {
+    w[k] += __shfl_xor(w[k], 16, 64);
+    w[k] += __shfl_xor(w[k], 32, 64);
+  }
+  if (kq == 0 && col <= d.B) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) part[(u * 3 + k) * BP + col] = w[k];
   }
 }
 
@@ -335,10 +322,14 @@ void launch_count(const double* stats, int64_t B, const int32_t* flags, double* 
 // Strip sums of every split column: ntiles * PC_STRIPS strips x ceil((B + 1) / 64) groups.
 void launch_precomp(bool f64, const TestDesc* d, int64_t ntiles, int64_t B, double* part,
                     hipStream_t st) {
-  const int64_t sg = (B + 1 + 63) / 64;
-  const dim3 grid((unsigned)(ntiles * PC_STRIPS * ((sg + 3) / 4)));
-  if (f64) hipLaunchKernelGGL(k_precomp<double>, grid, dim3(256), 0, st, d, part, sg);
-  else hipLaunchKernelGGL(k_precomp<float>, grid, dim3(256), 0, st, d, part, sg);
+  const int64_t sg = (B + 1 + 63) / 64, strips = ntiles * PC_STRIPS;
+  // several dispatches of at most 2^23 workgroups
+  const int64_t most = ((int64_t)1 << 23) / sg > 0 ? ((int64_t)1 << 23) / sg : 1;
+  for (int64_t first = 0; first < strips; first += most) {
+    const dim3 grid((unsigned)(std::min(most, strips - first) * sg));
+    if (f64) hipLaunchKernelGGL(k_precomp<double>, grid, dim3(256), 0, st, d, part, sg, first);
+    else hipLaunchKernelGGL(k_precomp<float>, grid, dim3(256), 0, st, d, part, sg, first);
+  }
 }
 void launch_precomp_stat(const TestDesc* d, int64_t ntiles, int64_t B, const double* part,
                          double* stats, hipStream_t st) {
