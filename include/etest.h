@@ -187,10 +187,11 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
    (arguments), ENONFINITE (NaN / Inf input; perm_stats untouched), ENOMEM, EDEVICE. */
 
 /* Standard permutation test (Alg. 4): for each of the B drawn splits and the identity
-   split, X* and Y* are staged from the pooled rows in index order (x* items first) and the
-   three blocks and the statistic, eq. (1) or (2), are recomputed from them.  The B + 1
-   recomputations run as batched passes of up to 256 tests (each pass one launch per stage,
-   within a 4 GiB workspace).  Cost: (B + 1) times the blocks of one test. */
+   split, the three blocks of X* and Y* (pooled rows in index order, x* items first) and the
+   statistic, eq. (1) or (2), are recomputed.  The pooled rows are staged once; the B + 1
+   recomputations read them through their splits' row maps, in batched passes of up to 256
+   tests (each pass one launch per stage, within a 4 GiB workspace), and keep only their
+   blocks' sums.  Cost: (B + 1) times the blocks of one test. */
 etest_status etest_standard(const etest_request* req, void* stream, etest_result* out);
 
 /* Pre-computation permutation test (Alg. 5): the distance (kernel) matrix of the pooled

@@ -123,14 +123,14 @@ static int64_t super_tiles(int64_t nt) {
 // workgroup holds a CU alone, so that the grid takes whole rounds of 256, and a second pass turns
 // its raw Gram into block values.  In units of a stored tile's time per coordinate on 128-tile
 // workgroups (FP32 form 0.11 ns, BF16 0.044 ns, whole card), measured between n = 8000 and 16000,
-// p = 500 and 16384: a super tile's four take 0.82 (BF16 0.68) each, the second pass as long as
+// p = 500 and 16384: a super tile's four take 0.80 (BF16 0.68) each, the second pass as long as
 // 240 (BF16 600) coordinates (26 ns).  BF16, super / 128-tile, whole test of 100 splits: n =
 // 8000, p = 4096 730 / 657 us (528 super tiles: three rounds), n = 16000, p = 4096 1783 / 1925;
 // FP32 form, n = 16000, p = 500 1178 / 1034 us, p = 4096 3710 / 4026.
 static bool super_pays(int prec, int64_t p, int64_t nt) {
   const bool bf16 = prec == ETEST_PREC_BF16_REFINED;
   const int64_t slots = (super_tiles(nt) + 255) / 256 * 1024, tiles = nt * (nt + 1) / 2;
-  return slots * (bf16 ? 68 : 82) / 100 * p + tiles * (bf16 ? 600 : 240) < tiles * p;
+  return slots * (bf16 ? 68 : 80) / 100 * p + tiles * (bf16 ? 600 : 240) < tiles * p;
 }
 static int gram_shape(const etest_request& r, int64_t nt) {
   if (r.prec == ETEST_PREC_F64) return GSHAPE_TILE;
