@@ -44,7 +44,8 @@ METRIC = "permuted statistics/sec and Gram TFLOP/s vs plain FP32; serving p50/p9
 # (hi hi + hi lo + lo hi): its peak in algorithmic flops is the fp16 peak over three.
 PEAK = {"hbm_GBs": 8000.0, "bf16_TF": 2500.0, "fp16_TF": 2500.0, "fp32_TF": 157.3,
         "f16x3_TF": 2500.0 / 3,
-        "fp64_TF": 78.6}
+        "fp64_TF": 78.6,
+        "lds_GBs": 256 * 128 * 2.4}  # 128 bytes per clock and CU
 
 
 def log(*a):
@@ -704,27 +705,27 @@ def run_hsic(args):
         elapsed, live, prof, res = timed(step, args.steps, args.warmup)
         stage = per_launch(prof)
         terms_ms = per_launch(live)["resampling"]
-        entries = (B + 1) * n * n
+        entries = (B + 1) * n * (n - 1) // 2  # unordered pairs, each gathered once
         rows[str(n)] = {"ms_per_test": 1e3 * elapsed / args.steps, "p_value": res["p_value"],
                         "statistic": res["statistic"],
                         "stage_ms": {k: round(v, 5) for k, v in stage.items()},
                         "terms_ms_live": terms_ms,
-                        "terms_gather_GBs": entries * 8 / (terms_ms * 1e-3) / 1e9}
+                        "terms_gather_GBs": entries * 4 / (terms_ms * 1e-3) / 1e9}
         log("hsic n", n, rows[str(n)])
         if head is None:
             head = (n, elapsed, terms_ms, entries, X, Y)
     n, elapsed, terms_ms, entries, X, Y = head
-    achieved = entries * 8 / (terms_ms * 1e-3) / 1e9
+    achieved = entries * 4 / (terms_ms * 1e-3) / 1e9
     line = base_line(args, "hsic_f32_n2000_p500_B200", args.steps / elapsed, elapsed, args.steps,
                      "f32", {"n": n, "p": p, "q": p, "B": B, "kernel": "gaussian, gamma = 1/p"})
     line.update({"metric": "HSIC permutation tests/s (n = 2000, p = q = 500, B = 200)",
                  "unit": "tests/s", "sizes": rows,
-                 "roofline": {"bound": "hbm", "kernel": "k_hsic_terms<float>",
-                              "achieved": achieved, "peak": PEAK["hbm_GBs"], "unit": "GB/s",
-                              "algorithmic": "8 bytes (one Kt and one gathered Lt entry) per "
-                                             "entry and permutation: (B+1) n^2 x 8 = %.4g per "
-                                             "launch" % (entries * 8),
-                              "frac": achieved / PEAK["hbm_GBs"],
+                 "roofline": {"bound": "lds", "kernel": "k_hsic_terms<float>",
+                              "achieved": achieved, "peak": PEAK["lds_GBs"], "unit": "GB/s",
+                              "algorithmic": "4 bytes gathered from LDS per unordered pair and "
+                                             "permutation: (B+1) n (n-1) / 2 x 4 = %.4g per "
+                                             "launch" % (entries * 4),
+                              "frac": achieved / PEAK["lds_GBs"],
                               "traffic": measured_traffic("k_hsic_terms<float>",
                                                           "hsic_f32_n2000_p500_B200")}})
     if not args.no_cpu_baseline:
