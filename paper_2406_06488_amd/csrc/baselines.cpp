@@ -13,11 +13,12 @@ namespace et {
 
 // Free the workspaces, wait for the result that the last kernel wrote to pinned memory.
 static etest_status finish_baseline(const DevResult* h, Batch* b, void* aux, hipStream_t st,
-                                    hipError_t e, const char* what, etest_result* out) {
+                                    hipError_t e, const char* what, etest_result* out,
+                                    const Fork* fork = nullptr) {
   if (e == hipSuccess) e = hipGetLastError();
   free_batch(b, st, true);
   if (aux) (void)hipFreeAsync(aux, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  e = finish_stream(st, e, fork);
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
   return dev_to_result(*h, out);
 }
@@ -76,6 +77,7 @@ static etest_status run_standard(const etest_request& r, hipStream_t st, etest_r
   }
   if (s != ETEST_OK) {
     (void)hipFreeAsync(aux, st);
+    (void)finish_stream(st, hipSuccess);
     return s;
   }
   {
@@ -128,7 +130,10 @@ static etest_status run_precomputed(const etest_request& r, hipStream_t st, etes
   if (!res) return set_error(ETEST_ENOMEM, "pinned result buffer");
   b.desc_by_kernel = true;
   etest_status s = place_batch(&b, st, true);
-  if (s != ETEST_OK) return s;
+  if (s != ETEST_OK) {
+    (void)finish_stream(st, hipSuccess);
+    return s;
+  }
   const TestDesc& d = b.descs[0];
   const TestDesc* D = b.d_descs;
   auto offs = [&](Slot k) { return b.d_offs + (size_t)k * 2; };
@@ -166,7 +171,8 @@ static etest_status run_precomputed(const etest_request& r, hipStream_t st, etes
   launch_precomp_stat(D, d.ntiles, r.B, d.part, d.pstat, st);
   launch_count(d.pstat, r.B, d.flags, r.perm_stats, res, st);
   mark(6, false);
-  etest_status rs = finish_baseline(res, &b, nullptr, st, hipSuccess, "pre-computation test", out);
+  etest_status rs = finish_baseline(res, &b, nullptr, st, hipSuccess, "pre-computation test", out,
+                                    fork);
   profile_collect();
   return rs;
 }
@@ -221,6 +227,7 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   etest_status s = place_batch(&b, st, true);
   if (s != ETEST_OK) {
     (void)hipFreeAsync(aux, st);
+    (void)finish_stream(st, hipSuccess);
     return s;
   }
   double* rxs = (double*)(a + off[H_RX]);
@@ -280,7 +287,7 @@ static etest_status run_hsic(const etest_hsic_request& h, hipStream_t st, etest_
   }
   launch_count(stats, B, flags, h.perm_stats, res, st);
   mark(6, false);
-  etest_status rs = finish_baseline(res, &b, aux, st, hipSuccess, "HSIC test", out);
+  etest_status rs = finish_baseline(res, &b, aux, st, hipSuccess, "HSIC test", out, fork);
   profile_collect();
   return rs;
 }
@@ -326,8 +333,7 @@ etest_status etest_permutations(int64_t n, uint64_t seed, int64_t b0, int64_t co
   if (b0 < 0 || count < 0 || !perms) return set_error(ETEST_EINVAL, "bad range or NULL perms");
   hipStream_t st = (hipStream_t)stream;
   launch_permgen(n, seed, b0, count, count, perms, st);
-  HIP_OK(hipGetLastError(), "permutations launch");
-  HIP_OK(hipStreamSynchronize(st), "permutations");
+  HIP_OK(finish_stream(st, hipGetLastError()), "permutations");
   return ETEST_OK;
 }
 

@@ -717,6 +717,13 @@ const Fork* batch_fork(const Batch& b, bool graph) {
   return thread_fork();
 }
 
+hipError_t finish_stream(hipStream_t st, hipError_t e, const Fork* fork) {
+  const hipError_t w = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = w;
+  if (e != hipSuccess && fork) (void)hipStreamSynchronize(fork->aux);
+  return e;
+}
+
 // ------------------------------------------------------------------ stage timing
 // Each enqueued pass takes its own set of stage events, so passes enqueued back to back
 // without a wait in between (the asynchronous entry points) are all timed; the sets are
@@ -826,11 +833,15 @@ static etest_status run_device(const etest_request* reqs, int64_t n, hipStream_t
   b.host_results = hr;
   b.desc_by_kernel = n == 1;
   s = place_batch(&b, st, true);
-  if (s != ETEST_OK) return s;
-  enqueue_batch(b, st, import_words, profile_events(), batch_fork(b, false));
+  if (s != ETEST_OK) {
+    (void)finish_stream(st, hipSuccess);
+    return s;
+  }
+  const Fork* fork = batch_fork(b, false);
+  enqueue_batch(b, st, import_words, profile_events(), fork);
   hipError_t e = hipGetLastError();
   free_batch(&b, st, true);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  e = finish_stream(st, e, fork);
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("run: ") + hipGetErrorString(e));
   profile_collect();
   etest_status worst = ETEST_OK;
@@ -1037,10 +1048,9 @@ static etest_status run_batch_graph(const etest_request* reqs, int64_t n, hipStr
   DevResult* hr = pinned_results((size_t)n);
   if (!hd || !hr) return set_error(ETEST_ENOMEM, "pinned staging buffer");
   fill_descs(*hit, reqs, n, pairing, hd, hr, nullptr);
-  HIP_OK(hipMemcpyAsync(b.d_descs, hd, sizeof(TestDesc) * (size_t)n, hipMemcpyHostToDevice, st),
-         "descriptor copy");
-  HIP_OK(hipGraphLaunch(hit->exec, st), "graph launch");
-  HIP_OK(hipStreamSynchronize(st), "batch");
+  hipError_t e = hipMemcpyAsync(b.d_descs, hd, sizeof(TestDesc) * (size_t)n, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipGraphLaunch(hit->exec, st);
+  HIP_OK(finish_stream(st, e), "batch");
   etest_status worst = ETEST_OK;
   for (int64_t t = 0; t < n; ++t) {
     etest_result tmp;
@@ -1283,8 +1293,7 @@ etest_status etest_membership(int64_t nx, int64_t ny, uint64_t seed, int64_t b0,
   if (b0 < 0 || count < 0 || !words) return set_error(ETEST_EINVAL, "bad range or NULL words");
   hipStream_t st = (hipStream_t)stream;
   launch_member_public(nx, ny, seed, b0, count, words, st);
-  HIP_OK(hipGetLastError(), "membership launch");
-  HIP_OK(hipStreamSynchronize(st), "membership");
+  HIP_OK(finish_stream(st, hipGetLastError()), "membership");
   return ETEST_OK;
 }
 
@@ -1299,7 +1308,10 @@ etest_status etest_blocks(const etest_request* req, void* dxx, void* dyy, void* 
   etest_status s = build_batch(&r, 1, false, &b);
   if (s != ETEST_OK) return s;
   s = place_batch(&b, st, true);
-  if (s != ETEST_OK) return s;
+  if (s != ETEST_OK) {
+    (void)finish_stream(st, hipSuccess);
+    return s;
+  }
   enqueue_batch(b, st);
   int32_t flag = 0;
   hipError_t e = hipGetLastError();
@@ -1312,7 +1324,7 @@ etest_status etest_blocks(const etest_request* req, void* dxx, void* dyy, void* 
     e = hipGetLastError();
   }
   free_batch(&b, st, true);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  e = finish_stream(st, e);
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("blocks: ") + hipGetErrorString(e));
   if (flag) return set_error(ETEST_ENONFINITE, "X or Y contains NaN or Inf");
   return ETEST_OK;
@@ -1443,7 +1455,7 @@ etest_status etest_cross(const etest_request* req, void* stream, etest_cross_res
     e = hipGetLastError();
   }
   (void)hipFreeAsync(ws, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  e = finish_stream(st, e);
   if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("cross: ") + hipGetErrorString(e));
   profile_collect();
   if (hb->flags[0]) return set_error(ETEST_ENONFINITE, "X or Y contains NaN or Inf");

@@ -226,6 +226,10 @@ void enqueue_stages(const TestDesc* D, const int64_t* d_offs, const int64_t* h_o
 void enqueue_batch(const Batch& b, hipStream_t st, const uint32_t* import_words = nullptr,
                    const StageEvents* events = nullptr, const Fork* fork = nullptr);
 const Fork* batch_fork(const Batch& b, bool graph);  // the calling thread's, or none
+// End of a call that waits: waits for its stream whatever e, the error so far, is (and for the
+// forked stream, should the error have kept it from being joined), so that no kernel of the call
+// is left reading the caller's buffers or writing the thread's pinned result.
+hipError_t finish_stream(hipStream_t st, hipError_t e, const Fork* fork = nullptr);
 void free_batch(Batch* b, hipStream_t st, bool stream_ordered);
 etest_status dev_to_result(const DevResult& r, etest_result* out);
 

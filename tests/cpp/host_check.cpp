@@ -1,0 +1,118 @@
+// Host runtime checked without a device, one check per argument (see fake_hip.h).
+#include <functional>
+
+#include "fake_hip.h"
+
+using namespace et;
+
+static char sample[8];  // stands for device inputs, which only kernels read
+
+static etest_request request(int prec, int64_t n, int64_t B, int kind = ETEST_ED) {
+  etest_request r{};
+  r.kind = kind;
+  r.prec = prec;
+  r.nx = r.ny = n;
+  r.p = 20;
+  r.B = B;
+  r.gamma = 0.1;
+  r.X = r.Y = sample;
+  return r;
+}
+
+// Every call that waits, on stream st: 1600 pooled rows, so that the split stream is forked.
+struct Call {
+  std::string name;
+  std::function<etest_status(hipStream_t)> run;
+};
+static std::vector<Call> waiting_calls() {
+  static std::vector<char> words(1 << 16);
+  std::vector<Call> v;
+  for (int prec : {ETEST_PREC_F64, ETEST_PREC_F32, ETEST_PREC_BF16_REFINED}) {
+    const std::string p = " prec " + std::to_string(prec);
+    const etest_request r = request(prec, 800, 300), small = request(prec, 100, 20);
+    auto one = [&](const char* name, etest_status (*f)(const etest_request*, void*, etest_result*)) {
+      v.push_back({name + p, [=](hipStream_t st) { etest_result o; return f(&r, st, &o); }});
+    };
+    one("run", etest_run);
+    one("precomputed", etest_precomputed);
+    one("precomputed_dense", etest_precomputed_dense);
+    one("standard", etest_standard);
+    v.push_back({"cross" + p, [=](hipStream_t st) { etest_cross_result o; return etest_cross(&r, st, &o); }});
+    v.push_back({"blocks" + p, [=](hipStream_t st) {
+      return etest_blocks(&small, words.data(), words.data(), words.data(), st);
+    }});
+    v.push_back({"from_membership" + p, [=](hipStream_t st) {
+      etest_result o;
+      return etest_perm_stats_from_membership(&r, (uint32_t*)words.data(), 40, (double*)words.data(), st, &o);
+    }});
+    v.push_back({"batch" + p, [=](hipStream_t st) {
+      const etest_request q[2] = {r, small};
+      etest_result o[2];
+      return etest_batch(q, 2, st, o);
+    }});
+    v.push_back({"timed batch" + p, [=](hipStream_t st) {
+      const etest_request q[2] = {r, small};
+      etest_result o[2];
+      etest_profile_enable(1);
+      const etest_status s = etest_batch(q, 2, st, o);
+      etest_profile_enable(0);
+      return s;
+    }});
+  }
+  for (int prec : {ETEST_PREC_F64, ETEST_PREC_F32})
+    v.push_back({"hsic prec " + std::to_string(prec), [=](hipStream_t st) {
+      etest_hsic_request h{};
+      h.prec = prec;
+      h.n = 1600;
+      h.p = h.q = 20;
+      h.B = 50;
+      h.gamma_x = h.gamma_y = 0.1;
+      h.X = h.Y = sample;
+      etest_result o;
+      return etest_hsic(&h, st, &o);
+    }});
+  v.push_back({"membership", [=](hipStream_t st) {
+    return etest_membership(100, 100, 1, 0, 10, (uint32_t*)words.data(), st);
+  }});
+  v.push_back({"permutations", [=](hipStream_t st) {
+    return etest_permutations(100, 1, 0, 10, (int32_t*)words.data(), st);
+  }});
+  return v;
+}
+
+// Runs f once with each of its fallible HIP calls failing in turn, then as it is.
+static void each_failure(const Call& c, hipStream_t st, const std::function<void(int64_t, etest_status)>& f) {
+  for (int64_t k = 1;; ++k) {
+    fake::calls = 0;
+    fake::fail_at = k;
+    fake::last = hipSuccess;
+    const etest_status s = c.run(st);
+    const bool reached = fake::calls >= k;
+    fake::fail_at = -1;
+    f(reached ? k : 0, s);
+    hipDeviceSynchronize();
+    if (!reached) return;
+  }
+}
+
+// A call that waits leaves nothing in flight, also where it fails: its kernels read the
+// caller's buffers and write the thread's pinned result, which the next call uses.
+static void check_failed_calls_wait() {
+  hipStream_t st;
+  hipStreamCreateWithFlags(&st, 0);
+  for (const Call& c : waiting_calls())
+    each_failure(c, st, [&](int64_t k, etest_status s) {
+      CHECK(fake::in_flight() == 0, "%s: %d launches in flight, failure %d, status %d", c.name.c_str(),
+            fake::in_flight(), (int)k, (int)s);
+      CHECK(k > 0 || s == ETEST_OK, "%s: status %d: %s", c.name.c_str(), (int)s, etest_last_error());
+    });
+}
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> checks = {
+      {"failed_calls_wait", check_failed_calls_wait},
+  };
+  for (int k = 1; k < argc; ++k) checks.at(argv[k])();
+  if (!fake::failures) std::printf("ok\n");
+  return fake::failures ? 1 : 0;
+}
