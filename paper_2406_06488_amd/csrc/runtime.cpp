@@ -566,7 +566,10 @@ etest_status place_batch(Batch* b, hipStream_t st, bool stream_ordered) {
   } else if (b->desc_pinned) {
     // descriptors and launch tables are adjacent on the device: one copy of both
     PinnedSlot* slot = pinned_slot(desc_bytes + offs_bytes);
-    if (!slot) return set_error(ETEST_ENOMEM, "pinned staging slot");
+    if (!slot) {
+      free_batch(b, st, stream_ordered);
+      return set_error(ETEST_ENOMEM, "pinned staging slot");
+    }
     char* h = (char*)slot->buf;
     std::memcpy(h, b->descs.data(), sizeof(TestDesc) * (size_t)n);
     std::memcpy(h + desc_bytes, b->offs.data(), sizeof(int64_t) * b->offs.size());
@@ -580,7 +583,10 @@ etest_status place_batch(Batch* b, hipStream_t st, bool stream_ordered) {
       e = hipMemcpyAsync(b->d_offs, b->offs.data(), sizeof(int64_t) * b->offs.size(),
                          hipMemcpyHostToDevice, st);
   }
-  if (e != hipSuccess) return set_error(ETEST_EDEVICE, std::string("descriptor copy: ") + hipGetErrorString(e));
+  if (e != hipSuccess) {
+    free_batch(b, st, stream_ordered);
+    return set_error(ETEST_EDEVICE, std::string("descriptor copy: ") + hipGetErrorString(e));
+  }
   return ETEST_OK;
 }
 
@@ -994,20 +1000,17 @@ static etest_status graph_entry(const etest_request* reqs, int64_t n, hipStream_
   if (s != ETEST_OK) return s;
   // Workspace and tables are placed before capture; the graph holds kernels only.
   s = place_batch(&g.batch, st, false);
-  if (s != ETEST_OK) {
-    free_batch(&g.batch, nullptr, false);
-    return s;
-  }
-  HIP_OK(hipStreamSynchronize(st), "descriptor copy");
+  if (s != ETEST_OK) return s;
+  hipError_t e = hipStreamSynchronize(st);
   hipStream_t cap = nullptr;
-  HIP_OK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "capture stream");
-  hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     enqueue_batch(g.batch, cap, nullptr, nullptr, batch_fork(g.batch, true));
     e = hipStreamEndCapture(cap, &g.graph);
   }
   if (e == hipSuccess) e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
-  (void)hipStreamDestroy(cap);
+  if (cap) (void)hipStreamDestroy(cap);
   if (e != hipSuccess) {
     destroy_entry(g);
     return set_error(ETEST_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));

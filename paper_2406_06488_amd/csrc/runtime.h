@@ -190,7 +190,7 @@ void init_pool_once();
 // Build plans + layout (host only).  extra_perm: allocate internal perm-stat
 // outputs for tests whose request has perm_stats == NULL but the caller wants them.
 etest_status build_batch(const etest_request* reqs, int64_t n, bool internal_perm, Batch* b);
-// Allocate the workspace on `st`, copy descriptors.
+// Allocate the workspace on `st`, copy descriptors.  It holds no workspace after a failure.
 etest_status place_batch(Batch* b, hipStream_t st, bool stream_ordered);
 // Optional stage events: begin[k] / end[k] bracket stage k on the stream it runs on.
 constexpr int NSTAGE = 7;

@@ -108,9 +108,36 @@ static void check_failed_calls_wait() {
     });
 }
 
+// A call that fails frees its workspaces; up to four graphs keep theirs.
+static void check_failed_calls_free() {
+  hipStream_t st;
+  hipStreamCreateWithFlags(&st, 0);
+  std::vector<Call> calls = waiting_calls();
+  for (int64_t n : {100, 800})
+    calls.push_back({"async", [=](hipStream_t s) {
+      const etest_request r = request(ETEST_PREC_F32, n, 100);
+      etest_result o;
+      return ed_test_async(&r, &o, s);
+    }});
+  calls.push_back({"async batch", [=](hipStream_t s) {
+    const etest_request q[2] = {request(ETEST_PREC_F32, 100, 20), request(ETEST_PREC_F64, 800, 20)};
+    etest_result o[2];
+    return etest_batch_async(q, 2, s, o);
+  }});
+  for (const Call& c : calls)
+    each_failure(c, st, [&](int64_t k, etest_status s) {
+      CHECK(fake::ordered.empty(), "%s: %d workspaces kept, failure %d, status %d", c.name.c_str(),
+            (int)fake::ordered.size(), (int)k, (int)s);
+      // and one per (device, stream) of the asynchronous calls
+      CHECK(fake::plain.size() <= 5, "%s: %d held, failure %d, status %d", c.name.c_str(),
+            (int)fake::plain.size(), (int)k, (int)s);
+    });
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"failed_calls_wait", check_failed_calls_wait},
+      {"failed_calls_free", check_failed_calls_free},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");
