@@ -690,18 +690,25 @@ void enqueue_batch(const Batch& b, hipStream_t st, const uint32_t* import_words,
 // microseconds per record between the kernels of a pass.
 constexpr unsigned kFenceFree = hipEventDisableSystemFence;
 
-// Per-thread auxiliary stream and fork/join events.
+// Auxiliary stream and fork/join events of the calling thread on the current device (a stream
+// runs on the device it was made on, and an event is recorded on streams of its own device only).
 static const Fork* thread_fork() {
-  static thread_local Fork f;
-  static thread_local int state = 0;  // 0 untried, 1 ready, -1 unavailable
-  if (state == 0) {
-    state = -1;
-    if (hipStreamCreateWithFlags(&f.aux, hipStreamNonBlocking) == hipSuccess &&
-        hipEventCreateWithFlags(&f.start, kFenceFree | hipEventDisableTiming) == hipSuccess &&
-        hipEventCreateWithFlags(&f.done, kFenceFree | hipEventDisableTiming) == hipSuccess)
-      state = 1;
-  }
-  return state == 1 ? &f : nullptr;
+  struct DeviceFork {
+    int dev;
+    bool ready;
+    Fork f;
+  };
+  static thread_local std::list<DeviceFork> forks;  // (entries do not move)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  for (const DeviceFork& d : forks)
+    if (d.dev == dev) return d.ready ? &d.f : nullptr;
+  forks.push_back(DeviceFork{dev, false, {}});
+  DeviceFork& d = forks.back();
+  d.ready = hipStreamCreateWithFlags(&d.f.aux, hipStreamNonBlocking) == hipSuccess &&
+            hipEventCreateWithFlags(&d.f.start, kFenceFree | hipEventDisableTiming) == hipSuccess &&
+            hipEventCreateWithFlags(&d.f.done, kFenceFree | hipEventDisableTiming) == hipSuccess;
+  return d.ready ? &d.f : nullptr;
 }
 
 // The fork to run a pass with, or NULL: on the tests' own stream.  Forking costs an event record

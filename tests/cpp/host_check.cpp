@@ -134,10 +134,30 @@ static void check_failed_calls_free() {
     });
 }
 
+// One thread, two devices in turn, the null stream of each: every launch, record and replay is
+// on the current device, and no call fails for having run on the other one before.
+static void check_two_devices(const std::set<std::string>& names) {
+  for (int pass = 0; pass < 3; ++pass) {
+    fake::device = pass % 2;
+    for (const Call& c : waiting_calls()) {
+      if (!names.count(c.name.substr(0, c.name.find(" prec")))) continue;
+      const etest_status s = c.run(nullptr);
+      CHECK(s == ETEST_OK, "%s on device %d: %s", c.name.c_str(), fake::device, etest_last_error());
+      CHECK(fake::other_device == 0, "%s on device %d used the other", c.name.c_str(), fake::device);
+      fake::other_device = 0;
+      hipDeviceSynchronize();
+    }
+  }
+}
+static void check_fork_of_two_devices() {
+  check_two_devices({"run", "from_membership", "precomputed", "precomputed_dense", "cross", "blocks"});
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"failed_calls_wait", check_failed_calls_wait},
       {"failed_calls_free", check_failed_calls_free},
+      {"fork_of_two_devices", check_fork_of_two_devices},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");
