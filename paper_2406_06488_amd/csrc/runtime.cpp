@@ -484,13 +484,14 @@ static hipError_t stream_workspace(hipStream_t st, size_t total, void** out,
   return hipSuccess;
 }
 
-// Pinned staging for the descriptor tables of asynchronous batches: a small ring per host
-// thread.  A slot is handed out again only once the copy from it has run (an event recorded
-// after the copy), so a caller can run a few calls ahead of the device.
+// Pinned staging for the descriptor tables of batches: a small ring per host thread.  A slot
+// is handed out again only once the copy from it has run (an event recorded after the copy, on
+// the device it was made on), so a caller can run a few calls ahead of the device.
 struct PinnedSlot {
   void* buf = nullptr;
   size_t cap = 0;
   hipEvent_t done = nullptr;
+  int dev = 0;  // the event's device
   bool used = false;
 };
 constexpr int PINNED_SLOTS = 4;
@@ -509,9 +510,16 @@ static PinnedSlot* pinned_slot(size_t bytes) {
     if (hipHostMalloc(&s.buf, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
     s.cap = bytes;
   }
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  if (s.done && s.dev != dev) {
+    (void)hipEventDestroy(s.done);
+    s.done = nullptr;
+  }
   if (!s.done && hipEventCreateWithFlags(&s.done, hipEventDisableSystemFence |
                                                       hipEventDisableTiming) != hipSuccess)
     return nullptr;
+  s.dev = dev;
   return &s;
 }
 

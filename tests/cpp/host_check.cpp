@@ -153,11 +153,14 @@ static void check_fork_of_two_devices() {
   check_two_devices({"run", "from_membership", "precomputed", "precomputed_dense", "cross", "blocks"});
 }
 
+static void check_staging_of_two_devices() { check_two_devices({"standard", "hsic"}); }
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"failed_calls_wait", check_failed_calls_wait},
       {"failed_calls_free", check_failed_calls_free},
       {"fork_of_two_devices", check_fork_of_two_devices},
+      {"staging_of_two_devices", check_staging_of_two_devices},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");
