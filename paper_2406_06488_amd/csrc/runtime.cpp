@@ -959,6 +959,7 @@ struct GraphEntry {
   std::vector<ShapeKey> key;
   uint64_t tune_gen = 0;  // tuning rules the captured work shapes came from
   hipStream_t stream = nullptr;  // calls on one stream share the entry's workspace in order
+  int dev = 0;                   // (the null stream stands for one on every device)
   Batch batch;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -968,19 +969,23 @@ static std::list<GraphEntry> g_graphs;
 static const size_t kGraphCacheMax = 4;
 
 static bool same_shapes(const GraphEntry& g, const etest_request* b, int64_t n, uint64_t gen,
-                        const Pairing& pg, hipStream_t st) {
-  if (g.stream != st || g.tune_gen != gen || (int64_t)g.key.size() != n) return false;
+                        const Pairing& pg, hipStream_t st, int dev) {
+  if (g.stream != st || g.dev != dev || g.tune_gen != gen || (int64_t)g.key.size() != n) return false;
   for (int64_t t = 0; t < n; ++t)
     if (!(g.key[(size_t)t] == shape_of(b[t], pg, t))) return false;
   return true;
 }
 
 static void destroy_entry(GraphEntry& g) {
+  int dev = g.dev;
+  (void)hipGetDevice(&dev);
+  if (dev != g.dev) (void)hipSetDevice(g.dev);
   // an asynchronous replay of it may still be queued
   (void)hipDeviceSynchronize();
   if (g.exec) (void)hipGraphExecDestroy(g.exec);
   if (g.graph) (void)hipGraphDestroy(g.graph);
   free_batch(&g.batch, nullptr, false);
+  if (dev != g.dev) (void)hipSetDevice(dev);
 }
 
 static TestDesc* pinned_descs(size_t n) {
@@ -1001,8 +1006,10 @@ static TestDesc* pinned_descs(size_t n) {
 static etest_status graph_entry(const etest_request* reqs, int64_t n, hipStream_t st,
                                 const Pairing& pairing, GraphEntry** out) {
   const uint64_t gen = tune_generation();
+  int dev = 0;
+  HIP_OK(hipGetDevice(&dev), "no device");
   for (auto it = g_graphs.begin(); it != g_graphs.end(); ++it)
-    if (same_shapes(*it, reqs, n, gen, pairing, st)) {
+    if (same_shapes(*it, reqs, n, gen, pairing, st, dev)) {
       g_graphs.splice(g_graphs.begin(), g_graphs, it);
       *out = &g_graphs.front();
       return ETEST_OK;
@@ -1011,6 +1018,7 @@ static etest_status graph_entry(const etest_request* reqs, int64_t n, hipStream_
   for (int64_t t = 0; t < n; ++t) g.key.push_back(shape_of(reqs[t], pairing, t));
   g.tune_gen = gen;
   g.stream = st;
+  g.dev = dev;
   etest_status s = build_batch(reqs, n, false, &g.batch);
   if (s != ETEST_OK) return s;
   // Workspace and tables are placed before capture; the graph holds kernels only.

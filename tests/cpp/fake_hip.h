@@ -25,6 +25,7 @@ struct Event {
 };
 struct Graph {
   int dev = 0;
+  Stream* on = nullptr;  // of its last replay
 };
 inline int device = 0;
 inline hipError_t last = hipSuccess;
@@ -34,6 +35,7 @@ inline std::set<Stream*> streams;
 inline std::map<int, Stream*> null_streams;
 inline std::map<void*, size_t> ordered, plain, pinned;  // hipMallocAsync, hipMalloc, hipHostMalloc
 inline int other_device = 0;  // launches, records and replays refused as another device's
+inline int destroyed_in_flight = 0;  // graphs
 
 inline hipError_t fail(hipError_t e) { return last = e; }
 inline bool inject() { return ++calls == fail_at; }
@@ -130,8 +132,10 @@ hipError_t hipStreamSynchronize(hipStream_t st) {
   s->joined.clear();
   return fake::inject() ? fake::fail(hipErrorUnknown) : hipSuccess;
 }
+hipError_t hipSetDevice(int d) { fake::device = d; return hipSuccess; }
 hipError_t hipDeviceSynchronize() {
-  for (fake::Stream* s : fake::streams) s->work = 0;
+  for (fake::Stream* s : fake::streams)
+    if (s->dev == fake::device) s->work = 0;
   return hipSuccess;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
@@ -163,11 +167,17 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*,
 hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t st) {
   if (fake::inject()) return fake::fail(hipErrorOutOfMemory);
   if (((fake::Graph*)x)->dev != fake::device) ++fake::other_device;
+  ((fake::Graph*)x)->on = fake::stream(st);
   ++fake::stream(st)->work;
   return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t g) { delete (fake::Graph*)g; return hipSuccess; }
-hipError_t hipGraphExecDestroy(hipGraphExec_t x) { delete (fake::Graph*)x; return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t x) {
+  fake::Stream* on = ((fake::Graph*)x)->on;
+  if (on && on->work) ++fake::destroyed_in_flight;
+  delete (fake::Graph*)x;
+  return hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
   auto* ev = new fake::Event;
   ev->dev = fake::device;

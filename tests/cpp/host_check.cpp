@@ -154,6 +154,17 @@ static void check_fork_of_two_devices() {
 }
 
 static void check_staging_of_two_devices() { check_two_devices({"standard", "hsic"}); }
+static void check_graphs_of_two_devices() {
+  check_two_devices({"batch"});
+  // graphs in flight on one device, put out of the cache by calls on the other
+  for (int k = 0; k < 8; ++k) {
+    fake::device = k / 4;
+    const etest_request r = request(ETEST_PREC_F32, 50 + k, 20);
+    etest_result o;
+    CHECK(etest_batch_async(&r, 1, nullptr, &o) == ETEST_OK, "async batch %d", k);
+  }
+  CHECK(fake::destroyed_in_flight == 0, "%d graphs destroyed in flight", fake::destroyed_in_flight);
+}
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
@@ -161,6 +172,7 @@ int main(int argc, char** argv) {
       {"failed_calls_free", check_failed_calls_free},
       {"fork_of_two_devices", check_fork_of_two_devices},
       {"staging_of_two_devices", check_staging_of_two_devices},
+      {"graphs_of_two_devices", check_graphs_of_two_devices},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");
