@@ -761,11 +761,16 @@ static thread_local Profile g_prof;
 const StageEvents* profile_events() {
   if (!g_prof.on) return nullptr;
   StageEvents* ev = nullptr;
-  if (!g_prof.spare.empty()) {
-    ev = g_prof.spare.back();
-    g_prof.spare.pop_back();
-  } else {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  for (size_t k = g_prof.spare.size(); k-- > 0 && !ev;)
+    if (g_prof.spare[k]->dev == dev) {
+      ev = g_prof.spare[k];
+      g_prof.spare.erase(g_prof.spare.begin() + (std::ptrdiff_t)k);
+    }
+  if (!ev) {
     ev = new StageEvents;
+    ev->dev = dev;
     for (int k = 0; k < NSTAGE; ++k)
       if (hipEventCreateWithFlags(&ev->begin[k], kFenceFree) != hipSuccess ||
           hipEventCreateWithFlags(&ev->end[k], kFenceFree) != hipSuccess) {

@@ -197,6 +197,7 @@ constexpr int NSTAGE = 7;
 struct StageEvents {
   hipEvent_t begin[NSTAGE], end[NSTAGE];
   uint32_t mask = 0;  // stages (bit k = stage k) whose events are recorded
+  int dev = 0;        // the events' device
 };
 
 // Stage events of one pass while stage timing is on (else null), and their collection once

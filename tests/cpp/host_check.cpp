@@ -165,6 +165,7 @@ static void check_graphs_of_two_devices() {
   }
   CHECK(fake::destroyed_in_flight == 0, "%d graphs destroyed in flight", fake::destroyed_in_flight);
 }
+static void check_timing_of_two_devices() { check_two_devices({"timed batch"}); }
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
@@ -173,6 +174,7 @@ int main(int argc, char** argv) {
       {"fork_of_two_devices", check_fork_of_two_devices},
       {"staging_of_two_devices", check_staging_of_two_devices},
       {"graphs_of_two_devices", check_graphs_of_two_devices},
+      {"timing_of_two_devices", check_timing_of_two_devices},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");
