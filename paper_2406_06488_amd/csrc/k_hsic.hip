@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(1024) k_permgen(int64_t n, uint64_t seed, int6
 // here holds those weights of Kt: a pair of different tiles belongs to the row i from which j
 // lies at most n / 2 ahead, cyclically (at exactly n / 2: to the smaller of the two), so that
 // every range of columns carries the same work; its other entry is 0.  FP32 entries are
-// scaled by 2^100 (see HT_SCALE).  Row-major, n rows of stride ld; columns from n on are 0.
+// scaled by 2^127 (see HT_SCALE).  Row-major, n rows of stride ld; columns from n on are 0.
 template <typename T>
 __device__ inline T hsic_weight(T v, int64_t i, int64_t j, int64_t n) {
   int64_t dl = j - i;
@@ -103,7 +103,7 @@ __device__ inline T hsic_weight(T v, int64_t i, int64_t j, int64_t n) {
   T w;
   if (i / TILE == j / TILE) w = i == j ? (T)0 : (T)0.5;
   else w = 2 * dl < n || (2 * dl == n && j > i) ? (T)1 : (T)0;
-  if (sizeof(T) == 4) w *= (T)0x1p100;
+  if (sizeof(T) == 4) w *= (T)0x1p127;
   return j < n ? v * w : (T)0;
 }
 
@@ -234,8 +234,10 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 //
 // FP32 form: S has one bit more than an FP32 value and no sign, so it is staged as 8 exponent
 // and 24 mantissa bits: bits 28..59 of the FP64 value S 2^-896, which two shifts restore.
-// Kt carries 2^100, so that no product above 2^-226 of the unit leaves FP64's normal range;
-// the sums are scaled back by 2^796.
+// Kt carries 2^127.  A product is then an integer times 2^-1068 (entries are integers times
+// 2^-149, halves of them times 2^-150), which FP64 holds exactly from its normal range, products
+// of 2^-253, down through its subnormals (multiples of 2^-1074); the sums are scaled back by
+// 2^769.
 //
 // Units are slice-major and every XCD takes a contiguous run of them: the Kt entries of one
 // slice (2 MB at n = 2000) stay in its L2 across all permutations (95% of the reads hit).
@@ -248,7 +250,7 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 constexpr int HT_THREADS = 512;
 constexpr int HT_COLS = 256;   // columns per slice
 constexpr int HT_BATCH = 4;    // permutations per wave whose sums are combined together
-constexpr int HT_SCALE = 796;  // FP32 form: the sums' exponent offset, 896 - 100
+constexpr int HT_SCALE = 769;  // FP32 form: the sums' exponent offset, 896 - 127
 template <typename T>
 constexpr int HT_G = 32 / sizeof(T);  // rows of S per workgroup
 
