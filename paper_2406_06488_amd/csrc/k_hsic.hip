@@ -228,9 +228,10 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 // ahead) while the lanes gather S[l][pi_j] from LDS.  Rows that own no pair of the slice are
 // skipped.  So each row of S is staged once per slice instead of once per permutation, and
 // half of the pairs' entries are never touched.  The products of two FP32 entries are exact
-// in FP64; a lane adds at most 4 G of them before the wave's tree, and the tree sums
-// (part[b][slice][group]) are added with compensation.  Bound by the gathers (random LDS
-// banks).
+// in FP64; a lane adds CH of a row's four, then adds such chains, and the wave its lanes, with
+// compensation (the three terms of the estimator cancel to a small fraction of their size), and
+// so are the waves' sums (part[b][slice][group]).  Bound by the gathers (random LDS banks) and,
+// in the FP32 form, as much by the vector ALU.
 //
 // FP32 form: S has one bit more than an FP32 value and no sign, so it is staged as 8 exponent
 // and 24 mantissa bits: bits 28..59 of the FP64 value S 2^-896, which two shifts restore.
@@ -245,8 +246,11 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 // Measured at n = 2000 and 201 permutations: 1007 us with one workgroup per permutation and
 // 8 rows (a row of Lt staged for each of them, every entry read), 416 us in this form without
 // the reads one permutation ahead and with the pairs' ownership tested per entry, 201 us with it
-// tested row by row on the scalar unit, 155 us now (LDS 65% busy, vector ALU 60%).  Four rows
-// interleaved, so that one 16-byte read gathers them all: 314 us, 54 LDS cycles per read.
+// tested row by row on the scalar unit, 155 us with them chosen over the lanes but every sum of a
+// wave by plain additions (LDS 65% busy, vector ALU 60%), 179 us now.  Whole tests, plain / now:
+// that one 286 / 303 us, n = 4096 1000 / 1111 (1147 with the lanes' sums by ds_bpermute); FP64
+// form 1780 / 1795.  Four rows interleaved, so that one 16-byte read gathers them all: 314 us, 54
+// LDS cycles per read.
 constexpr int HT_THREADS = 512;
 constexpr int HT_COLS = 256;   // columns per slice
 constexpr int HT_BATCH = 4;    // permutations per wave whose sums are combined together
@@ -273,8 +277,61 @@ __device__ inline double stage_sum(double a, double b) { return a + b; }
 __device__ inline double staged(uint32_t u) { return __hiloint2double((int)(u >> 4), (int)(u << 28)); }
 __device__ inline double staged(double v) { return v; }
 
-// NC: columns of a staged row (a power of two, at least the tiles' columns)
-template <typename T, int NC>
+// A sum and the roundings it has left behind (the error-free sum of two numbers, whatever their
+// order).
+struct Pair {
+  double s = 0.0, c = 0.0;
+  __device__ void add(double x) {
+    const double t = s + x, b = t - s;
+    c += (s - (t - b)) + (x - b);
+    s = t;
+  }
+  __device__ void add(const Pair& x) {
+    c += x.c;
+    add(x.s);
+  }
+};
+// Two sums over the lanes become one: lanes 0 .. 31 (row 16 even) hold a's, the others b's, each
+// with the other half's (the other row's) share added.
+template <int LANES>
+__device__ inline Pair join(const Pair& a, const Pair& b) {
+  auto exchange = [](double& x, double& y) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x), v = __builtin_bit_cast(uint64_t, y);
+    uint32_t p[2] = {(uint32_t)u, (uint32_t)(u >> 32)}, q[2] = {(uint32_t)v, (uint32_t)(v >> 32)};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const auto r = LANES == 32 ? __builtin_amdgcn_permlane32_swap(p[k], q[k], false, false)
+                                 : __builtin_amdgcn_permlane16_swap(p[k], q[k], false, false);
+      p[k] = r[0];
+      q[k] = r[1];
+    }
+    x = __builtin_bit_cast(double, (uint64_t)p[1] << 32 | p[0]);
+    y = __builtin_bit_cast(double, (uint64_t)q[1] << 32 | q[0]);
+  };
+  Pair x = a, y = b;
+  exchange(x.s, y.s);
+  exchange(x.c, y.c);
+  x.add(y);
+  return x;
+}
+// the value of the lane N places on, cyclically within 16
+template <int N>
+__device__ inline double rotated(double x) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x120 + N, 0xf, 0xf, true),
+                 hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x120 + N, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+template <int N>
+__device__ inline void add_rotated(Pair& a) {
+  Pair x;
+  x.s = rotated<N>(a.s);
+  x.c = rotated<N>(a.c);
+  a.add(x);
+}
+// NC: columns of a staged row (a power of two, at least the tiles' columns).  CH: products of
+// a row that a lane adds before a compensated step.
+template <typename T, int NC, int CH>
 __global__ void __launch_bounds__(HT_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n, int ld,
              const uint16_t* __restrict__ p16, const uint16_t* __restrict__ inv16, int nperm,
@@ -358,12 +415,19 @@ k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n
   auto terms = [&](const Tables& t, int q, uint32_t all, const T (&kv)[G][4]) {
     const uint32_t on = all >> (q * G);
     const int pk[4] = {t.pj[q].x, t.pj[q].y, t.pj[q].z, t.pj[q].w};
-    double a = 0.0;
+    Pair a;
 #pragma unroll
     for (int g = 0; g < G; ++g)
       if (on >> g & 1u) {
+        double x = 0.0;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a = fma((double)kv[g][e], staged(lt[g][pk[e]]), a);
+        for (int e = 0; e < 4; ++e) {
+          x = fma((double)kv[g][e], staged(lt[g][pk[e]]), x);
+          if ((e + 1) % CH == 0) {
+            a.add(x);
+            x = 0.0;
+          }
+        }
       }
     return a;
   };
@@ -378,7 +442,7 @@ k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n
   }
   static_assert(HT_BATCH == 4 && HT_BATCH * G <= 32, "the batch is written out, its rows are bits");
   for (; bb < b1; bb += STEP) {
-    double acc[HT_BATCH];
+    Pair acc[HT_BATCH];
     tables(min(bb + STEP, nperm - 1), tn);
     rows(off, 1, kb);
     acc[0] = terms(t, 0, on, ka);
@@ -391,16 +455,15 @@ k_hsic_terms(const TestDesc* __restrict__ descs, const T* __restrict__ kx, int n
     rows(off, 0, ka);
     acc[3] = terms(t, 3, cur, kb);
     t = tn;
-    // sums over the lanes, the four permutations together: each step sends half of the
-    // values still held, so lanes 16 k .. + 15 end with permutation (k >> 1) + 2 (k & 1)
+    // sums over the lanes, the four permutations together: lanes 16 k .. + 15 end with
+    // permutation (k >> 1) + 2 (k & 1)
     const bool hi5 = lane & 32, hi4 = lane & 16;
-    double x0 = hi5 ? acc[1] : acc[0], x1 = hi5 ? acc[3] : acc[2];
-    x0 += __shfl_xor(hi5 ? acc[0] : acc[1], 32, 64);
-    x1 += __shfl_xor(hi5 ? acc[2] : acc[3], 32, 64);
-    double x = hi4 ? x1 : x0;
-    x += __shfl_xor(hi4 ? x0 : x1, 16, 64);
-#pragma unroll
-    for (int m = 8; m > 0; m >>= 1) x += __shfl_xor(x, m, 64);
+    Pair sum = join<16>(join<32>(acc[0], acc[1]), join<32>(acc[2], acc[3]));
+    add_rotated<8>(sum);
+    add_rotated<4>(sum);
+    add_rotated<2>(sum);
+    add_rotated<1>(sum);
+    double x = sum.s + sum.c;
     if (sizeof(T) == 4) x = ldexp(x, HT_SCALE);
     const int b = bb + (hi5 ? 1 : 0) + (hi4 ? 2 : 0);
     if ((lane & 15) == 0 && b < b1) part[((int64_t)b * nsl + sl) * ngrp + grp] = x;
@@ -485,7 +548,7 @@ void launch_hsic_terms(bool f64, const TestDesc* d, const void* kx, int64_t n, i
   const int nsl = (int)((n + HT_COLS - 1) / HT_COLS), ngrp = (int)((n + g - 1) / g);
   // permutation ranges per (slice, row group): enough units for three rounds of the chip's
   // 512 resident workgroups, but at least one batch for each of a workgroup's waves; each range
-  // stages the rows again (n = 2000: 2000 units in one range 155 us, 4000 in two 169)
+  // stages the rows again (n = 2000, plain additions: 2000 units in one range 155 us, 4000 in two 169)
   int nps = 1;
   while (nps < 64 && (int64_t)nsl * ngrp * nps < 1536 &&
          nperm >= 2 * nps * HT_BATCH * (HT_THREADS / 64))
@@ -498,10 +561,14 @@ void launch_hsic_terms(bool f64, const TestDesc* d, const void* kx, int64_t n, i
   };
   auto pick = [&](auto* x) {
     typedef std::remove_const_t<std::remove_pointer_t<decltype(x)>> T;
-    if (n <= 512) go(k_hsic_terms<T, 512>, x);
-    else if (n <= 1024) go(k_hsic_terms<T, 1024>, x);
-    else if (n <= 2048) go(k_hsic_terms<T, 2048>, x);
-    else go(k_hsic_terms<T, HSIC_NMAX>, x);
+    // a chain of plain additions has at most n / 256 products, rounded up: as the number of
+    // chains grows with n^2, its roundings stay below those of the partial sums
+    if (n <= 256) go(k_hsic_terms<T, 512, 1>, x);
+    else if (n <= 512) go(k_hsic_terms<T, 512, 2>, x);
+    else if (n <= 768) go(k_hsic_terms<T, 1024, 2>, x);
+    else if (n <= 1024) go(k_hsic_terms<T, 1024, 4>, x);
+    else if (n <= 2048) go(k_hsic_terms<T, 2048, 4>, x);
+    else go(k_hsic_terms<T, HSIC_NMAX, 4>, x);
   };
   if (f64) pick((const double*)kx);
   else pick((const float*)kx);
