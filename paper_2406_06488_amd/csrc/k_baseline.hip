@@ -192,7 +192,10 @@ __global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ de
       for (int q = 0; q < 2; ++q) load4(src + rb * 16 * TILE + 32 * s + 16 * q, x[rb][q]);
     y = Zj[(int64_t)s * BP];
   };
-  auto multiply = [&](const double (&x)[2][2][4], uint32_t y) {
+  // a step's products in a chain of their own, which loses less to a large entry than one over
+  // the tile's 128 columns would; the chains of the four steps are added in pairs
+  auto multiply = [&](const double (&x)[2][2][4], uint32_t y, f64x4 (&sum)[2]) {
+    sum[0] = sum[1] = f64x4{0.0, 0.0, 0.0, 0.0};
     // column 16 q + 4 kq + e of the step: bit 16 q + e of the shifted word
 #pragma unroll
     for (int q = 0; q < 2; ++q)
@@ -202,16 +205,19 @@ __global__ void __launch_bounds__(256) k_precomp(const TestDesc* __restrict__ de
         const double b = __hiloint2double(bit & 0x3FF00000, 0);
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
-          acc[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rb][q][e], b, acc[rb], 0, 0, 0);
+          sum[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[rb][q][e], b, sum[rb], 0, 0, 0);
       }
   };
   load(0, a, z);
 #pragma unroll 1
   for (int s = 0; s < TILE_WORDS; s += 2) {
+    f64x4 u[2], v[2];
     load(s + 1, an, zn);
-    multiply(a, z);
+    multiply(a, z, u);
     if (s + 2 < TILE_WORDS) load(s + 2, a, z);
-    multiply(an, zn);
+    multiply(an, zn, v);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) acc[rb] += u[rb] + v[rb];
   }
   // element e of an accumulator is row 16 rb + kq + 4 e of the strip, whose total the Gram left
   const double* ts = d.tsum + (int64_t)t * d.tsum_stride + h * PC_ROWS + kq;
