@@ -167,6 +167,60 @@ static void check_graphs_of_two_devices() {
 }
 static void check_timing_of_two_devices() { check_two_devices({"timed batch"}); }
 
+// What every mode's kernels write lies in the plan's buffers: tile sums (6 TILE doubles a tile in
+// the FP64 form, 3 TILE else, at the descriptor's stride), the buffers a mode leaves out, and the
+// rows that a recomputation of the standard test reads from another plan.
+static void check_plan_buffers() {
+  const int64_t sizes[][3] = {{1, 1, 1}, {128, 128, 20}, {129, 300, 33}, {700, 90, 500}, {5000, 4000, 64}};
+  for (int prec : {ETEST_PREC_F64, ETEST_PREC_F32, ETEST_PREC_BF16_REFINED})
+    for (const auto& z : sizes)
+      for (int mode = PLAN_EFFICIENT; mode <= PLAN_SUMS; ++mode) {
+        const bool f64 = prec == ETEST_PREC_F64;
+        etest_request r = request(prec, z[0], mode == PLAN_STAGE || mode == PLAN_SUMS ? 0 : 300);
+        r.ny = z[1];
+        r.p = z[2];
+        TestPlan stage = make_plan(r, 0, PLAN_STAGE), P = make_plan(r, 0, mode);
+        char* at = (char*)(uintptr_t)(1 << 20);
+        assign_pointers(stage, at + ((size_t)1 << 40), nullptr);
+        if (mode == PLAN_SUMS) P.staged = &stage.d;
+        assign_pointers(P, at, nullptr);
+        const TestDesc& d = P.d;
+        char what[96];
+        std::snprintf(what, sizeof what, "prec %d mode %d, %d + %d x %d", prec, mode, d.nx, d.ny, d.p);
+        auto inside = [&](const void* p, size_t bytes, int buf) {
+          const size_t o = (size_t)((const char*)p - at);
+          return o >= P.off[buf] && o + bytes <= P.off[buf] + P.size[buf];
+        };
+        const size_t tile = f64 ? 8 : 4, npad = (size_t)d.nt * TILE;
+        const size_t rows = npad * d.p_pad * gram_operand_bytes(d.gop);
+        int64_t gram = 0, stagers = 0;
+        for (int k : GRAM_SLOTS)
+          if (k != S_GRAM_FIN) gram += P.wg[k];
+        for (int k : {S_COLPART, S_COLMEAN, S_STAGE}) stagers += P.wg[k];
+        CHECK((gram > 0) == (mode != PLAN_STAGE) && (stagers > 0) == (mode != PLAN_SUMS), "%s", what);
+        if (mode == PLAN_SUMS) {
+          CHECK(d.D == nullptr && d.W == stage.d.W && d.nrm == stage.d.nrm, "%s", what);
+          CHECK(d.gather == 1 && d.gshape == GSHAPE_TILE && gram == d.ntiles, "%s", what);
+          CHECK(P.size[B_D] + P.size[B_W] + P.size[B_NRM] + P.size[B_COLPART] + P.size[B_PLANES] == 0, "%s", what);
+        } else {
+          CHECK(d.gather == 0 && inside(d.W, rows, B_W) && inside(d.nrm, npad * tile, B_NRM), "%s", what);
+          CHECK(f64 || (inside(d.colpart, (size_t)d.nrowchunks * d.p * 8, B_COLPART) &&
+                        inside(d.colmean, (size_t)d.p * 8, B_COLMEAN)), "%s", what);
+        }
+        CHECK(inside(d.flags, FLAG_WORDS * 4, B_FLAGS), "%s", what);
+        if (mode == PLAN_STAGE) {
+          CHECK(P.size[B_D] + P.size[B_TSUM] + P.size[B_PLANES] == 0 && P.wg[S_ROWSUM] == 0, "%s", what);
+          continue;
+        }
+        const size_t sums = ((size_t)(d.ntiles - 1) * d.tsum_stride + (f64 ? 6 : 3) * TILE) * 8;
+        CHECK(d.tsum_stride >= (f64 ? 6 : 3) * TILE, "%s: stride %d", what, (int)d.tsum_stride);
+        CHECK(inside(d.tsum, sums, f64 && mode == PLAN_EFFICIENT ? B_PLANES : B_TSUM), "%s: tile sums", what);
+        CHECK(inside(d.tmax, (size_t)d.ntiles * TMAX_PER_TILE * 4, B_TMAX), "%s", what);
+        if (mode != PLAN_SUMS) CHECK(inside(d.D, (size_t)d.ntiles * TILE * TILE * tile, B_D), "%s", what);
+        if (P.wg[S_ROWSUM]) CHECK(inside(d.rsum, npad * 16, B_RSUM) && inside(d.obs, 64, B_OBS), "%s", what);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {
       {"failed_calls_wait", check_failed_calls_wait},
@@ -175,6 +229,7 @@ int main(int argc, char** argv) {
       {"staging_of_two_devices", check_staging_of_two_devices},
       {"graphs_of_two_devices", check_graphs_of_two_devices},
       {"timing_of_two_devices", check_timing_of_two_devices},
+      {"plan_buffers", check_plan_buffers},
   };
   for (int k = 1; k < argc; ++k) checks.at(argv[k])();
   if (!fake::failures) std::printf("ok\n");

@@ -25,7 +25,8 @@ def host_check(tmp_path_factory):
 
 @pytest.mark.parametrize("check", ["failed_calls_wait", "failed_calls_free",
                                    "fork_of_two_devices", "staging_of_two_devices",
-                                   "graphs_of_two_devices", "timing_of_two_devices"])
+                                   "graphs_of_two_devices", "timing_of_two_devices",
+                                   "plan_buffers"])
 def test_host_runtime(host_check, check):
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
     out = subprocess.run([host_check, check], capture_output=True, text=True, env=env, timeout=120)
