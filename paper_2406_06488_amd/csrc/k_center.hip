@@ -25,7 +25,7 @@
 // FP64 form: one FP64 tile in the order v_mfma_f64_16x16x4f64 reads its A operand: fragment
 // (rb, kp) holds rows 16 rb .. and columns 8 kp .., lane row%16 + 16 * ((col%8)/2) holding
 // two adjacent columns (one for each of two instructions).
-#include "common.h"
+#include "e4m3.h"
 
 namespace et {
 
@@ -39,13 +39,6 @@ __device__ inline float to_f32(double x) {
 
 __device__ inline uint32_t pack_h2(_Float16 a, _Float16 b) {
   return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
-}
-
-// Four values, at most 2^8 in size, to fp8 E4M3: the hardware's conversion, which up to 448 gives
-// f32_to_e4m3's codes (all 2.3e9 floats compared; a zero keeps its sign).
-__device__ inline uint32_t pack_e4m3(const float* x) {
-  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(
-      x[2], x[3], __builtin_amdgcn_cvt_pk_fp8_f32(x[0], x[1], 0, false), true);
 }
 
 // One workgroup per half tile (rows 64 rh .. + 63: fragment row blocks 2 rh and 2 rh + 1),
