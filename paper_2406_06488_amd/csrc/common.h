@@ -70,8 +70,9 @@ __host__ __device__ inline int gram_operands(int prec, int64_t p) {
   return prec == PREC_F64 ? GOP_F64
          : (prec == PREC_F32 || p < BF16_PAIR_MAX_P) ? GOP_F16PAIR : GOP_BF16;
 }
-// Gram workgroup shapes: one stored 128 x 128 tile per workgroup (four waves of 64 x 64),
-// or one 2 x 2 block of stored tiles (a 256 x 256 super tile: four waves, one tile each).
+// Gram workgroup shapes: one stored 128 x 128 tile per workgroup (or half of one on small grids;
+// eight waves), or one 2 x 2 block of stored tiles (a 256 x 256 super tile: four waves, one tile
+// each).
 enum { GSHAPE_TILE = 0, GSHAPE_SUPER = 1 };
 // K-slice width of each Gram kernel: staged rows are padded to a multiple of it.
 __host__ __device__ inline int gram_k_slice(int gop) {
@@ -162,9 +163,8 @@ struct TestDesc {
   // Dense pooled matrix (the pre-computation test as the paper prints it): every tile
   // (i, j) of the nt x nt grid, row-major (tile i * nt + j), both orders of every pair.
   int32_t dense;
-  // Standard permutation test: staging position t reads pooled item rowmap[t] (x* items in
-  // increasing order, then y* items), so one split's X* and Y* are staged without copying
-  // the data; NULL reads the items in their own order.
+  // Standard permutation test: position t of a recomputation is pooled item rowmap[t] (x* items
+  // in increasing order, then y* items); NULL: the items in their own order.
   const int32_t* rowmap;
   // Standard permutation test, recomputations: W and nrm hold the pooled rows staged once, in
   // their own order; the Gram reads position t's row through the row map (staged_row) and
@@ -172,8 +172,8 @@ struct TestDesc {
   int32_t gather;
 };
 
-// Input row t of the pooled sample, in staging order: x rows then y rows (through the
-// row map when there is one); for a cross test x1, y1, x2, y2.
+// Input row of position t of the pooled sample: x rows then y rows (through the row map when
+// there is one: the near pairs of a recomputation); for a cross test x1, y1, x2, y2.
 template <typename T>
 __device__ inline const T* pooled_row(const TestDesc& d, int64_t t) {
   const T* X = (const T*)d.X;
@@ -305,7 +305,8 @@ __host__ __device__ inline void rowk_coords(const TestDesc& d, int u, int* pi, i
 
 // FP32 -> fp8 E4M3 in the OCP layout the gfx950 fp8 MFMA reads (bias 7, no infinities,
 // 0x7F / 0xFF are NaN, largest finite 448): round to nearest even, saturating at +-448;
-// subnormals (multiples of 2^-9) kept.  Finite inputs only; zero of either sign -> 0.
+// subnormals (multiples of 2^-9) kept.  Finite inputs only; zero of either sign -> 0.  The
+// format's definition in code: the tests hold the kernels' conversion (pack_e4m3) to it.
 __host__ __device__ inline uint32_t f32_to_e4m3(float x) {
   const uint32_t sign = (__builtin_bit_cast(uint32_t, x) >> 24) & 0x80u;
   const float a = __builtin_fabsf(x);

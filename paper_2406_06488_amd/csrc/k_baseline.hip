@@ -13,7 +13,8 @@ namespace et {
 
 // ------------------------------------------------------------------ standard test
 // Row map of split b: pooled items of x* in increasing order, then those of y* -- the
-// index sets i*_x, i*_y of Alg. 4 -- so that staging through the map reads X* and Y*.
+// index sets i*_x, i*_y of Alg. 4 -- so that the Gram reads X* and Y* through the map from rows
+// that were staged once.
 // One workgroup per split; maps k >= count are the identity (the observed split).
 // Every member word holds exactly nx members (selection sampling); the index guards keep
 // the writes inside the map whatever the words hold.
@@ -139,8 +140,8 @@ __global__ void __launch_bounds__(1024) k_count(const double* __restrict__ stats
 // included) every tile holds both orders of its pairs and takes the diagonal-tile rule: the
 // X*X*, Y*Y* and X*Y* sub-blocks are read entry by entry and the Y*X* entries are skipped.
 // Padding entries are 0.  One workgroup per (tile, 32-row strip, 64 splits), 16 splits per wave:
-// every entry of the strip is multiplied by each split's column bit as 0.0 or 1.0, which adds it exactly or leaves
-// the sum as it is, and added in FP64 -- on v_mfma_f64_16x16x4f64, 2 row blocks of 16 x 16; s_y
+// every entry of the strip is multiplied by each split's column bit as 0.0 or 1.0, which adds the
+// entry or leaves the sum as it is, and added in FP64 -- on v_mfma_f64_16x16x4f64, 2 row blocks of 16 x 16; s_y
 // is the row's total less s_x.  No centring and no quadratic form: this
 // is the per-split extraction of Alg. 5.  The lanes read their entries straight from the
 // stored tile (four adjacent columns each, FP32 entries converted) and the waves of a workgroup

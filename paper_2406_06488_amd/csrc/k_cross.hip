@@ -28,6 +28,10 @@ struct Csum {  // compensated FP64 sum (Neumaier)
 };
 }  // namespace
 
+// CF_WGS: one workgroup per x-side tile up to 16, then several tiles each.  Whole cross tests with
+// 1 / 16 / 32 workgroups, FP32 form, p = 50: 100 + 100 rows (one tile) 52 / 52 / 53 us, 2000 +
+// 2000 96 / 58 / 58, 4000 + 4000 162 / 81 / 78, 6000 + 6000 304 / 122 / 118; FP64 44 / 44 / 44,
+// 116 / 77 / 77, 328 / 190 / 185, 645 / 362 / 356.
 constexpr int CF_THREADS = 1024, CF_WGS = 16, CF_BATCH = 4;
 
 // Workgroup-wide sums of two values (every thread returns them).

@@ -1,10 +1,9 @@
-// Block stage: every stored tile (i <= j) of the pooled tile grid is one
-// workgroup.  FP32 / BF16 forms: Gram tile G = W_i W_j^T on MFMA, epilogue
-// d^2 = |w_a|^2 + |w_b|^2 - 2 g (clamped at 0), then D = sqrt(d^2) (energy
-// distance, Alg. 3) or K = exp(-gamma d^2) (Gaussian kernel).  The BF16 form
-// recomputes pairs with d^2 < 1e-3 (|w_a|^2 + |w_b|^2) as a direct FP32
-// difference of the input rows.  The FP64 form evaluates Alg. 3 as written
-// (sum of squared differences) on the vector ALU.
+// Block stage: the stored tiles (i <= j) of the pooled tile grid.  FP32 / BF16 forms: Gram tile G
+// = W_i W_j^T on MFMA, a workgroup per half tile, tile or 2 x 2 tiles; epilogue d^2 = |w_a|^2 +
+// |w_b|^2 - 2 g (clamped at 0), then D = sqrt(d^2) (energy distance, Alg. 3) or K = exp(-gamma
+// d^2) (Gaussian kernel); pairs with d^2 < 1e-3 (|w_a|^2 + |w_b|^2) are recomputed as a direct FP32
+// difference of the input rows.  The FP64 form evaluates Alg. 3 as written (sum of squared
+// differences) on the vector ALU, a workgroup per 32 x 64 part of a tile.
 //
 // Every stored tile also yields FP64 row sums and column sums, from which the
 // observed statistic (eq. 1 / eq. 2) and the double-centring constants follow.
@@ -149,21 +148,13 @@ __device__ inline void emit_col(const BlockOut& o, int half, int col, int h, con
   if (h == 0) o.tsum[TILE * (1 + half) + col] = s;
 }
 
-// Staged half tile (64 rows of block values) -> row sums, stored rows and, with COLS, column
-// sums and the running max (else the caller has formed them in registers).  All 256 threads
-// take part; cross tests store no tile and have no column sums.
-template <bool COLS>
+// Staged half tile (64 rows of block values) of a stored tile -> row sums, column sums, running
+// max and stored rows.  All 256 threads take part.
 __device__ inline void emit_half(const BlockOut& o, int half, const float* tl, float& vmax) {
   const int tid = threadIdx.x;
-  float vm = 0.0f;
-  emit_row(o, half * HALF + (tid >> 2), tid & 3, tl + (tid >> 2) * TILE_LDS + (tid & 3) * 32, vm);
-  if (COLS) vmax = fmaxf(vmax, vm);
-  if (o.split >= 0) return;
-  if (COLS) {
-    const int col = (tid >> 6) * 32 + (tid & 31);
-    emit_col(o, half, col, (tid >> 5) & 1, tl + col);
-  }
-  if (!o.D) return;  // only the sums are kept
+  emit_row(o, half * HALF + (tid >> 2), tid & 3, tl + (tid >> 2) * TILE_LDS + (tid & 3) * 32, vmax);
+  const int col = (tid >> 6) * 32 + (tid & 31);
+  emit_col(o, half, col, (tid >> 5) & 1, tl + col);
   float4* dst = (float4*)(o.D + half * HALF * TILE);
 #pragma unroll
   for (int k = 0; k < HALF * TILE / 4 / 256; ++k) {
@@ -283,12 +274,14 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 // Every shape adds an entry's products in the same order (chunk by chunk; hi hi, hi lo, lo hi)
 // and forms values and sums alike, so all agree bit for bit, as does the super-tile kernel.
 //
-// Large grids run the K loop at 1.1 PFLOP/s of fp16 products, the rate of the library's GEMM on
-// this card (power-limited: the clock drops to 1.9 GHz).  Measured (FP32 form), against a
-// kernel of four waves of 64 x 64 with register-staged 32-wide slices: 10 tiles at p = 1000 51 ->
-// 20 us, 136 tiles at p = 512 38 -> 22 us, 256 tiles (cross test) at p = 1000 55 -> 36 us, 528
-// tiles at p = 1024 96 -> 84 us, 7236 tiles at p = 512 (standard test) 461 -> 421 us (by this
-// ring with four waves, three workgroups to a CU: 97 and 465).
+// The FP32 form's fp16 products run at 625 TFLOP/s at p = 1024 and 782 at p = 8192 on 528 tiles,
+// whose last 16 make a second round of the 512 resident workgroups, and at 868 and 1000 on 2080
+// tiles (85, 544, 241 and 1698 us; the library's 8192^3 product: 1111).  A launch of 528 tiles at p
+// = 1000 keeps the matrix cores 25% busy.  Measured (FP32 form), against a kernel of four waves of
+// 64 x 64 with register-staged 32-wide slices: 10 tiles at p = 1000 51 -> 20 us, 136 tiles at p =
+// 512 38 -> 22 us, 256 tiles (cross test) at p = 1000 55 -> 36 us, 528 tiles at p = 1024 96 -> 84
+// us, 7236 tiles at p = 512 (standard test) 461 -> 421 us (by this ring with four waves, three
+// workgroups to a CU: 97 and 465).
 //
 // GATHER: rows staged once in their own order (standard test), read through the row map.
 // first: the launch's first unit (a list past one dispatch goes in several).
@@ -448,8 +441,8 @@ k_gram_ring(const TestDesc* __restrict__ descs, const int64_t* __restrict__ offs
   // test it feeds.  REGS: an energy-distance tile without near pairs or row norms outside
   // [2^-80, 2^99] (every d^2 then lies in sqrt_rn's range) is finished in registers: values,
   // column sums, maximum; its rows pass through LDS for the row sums and the coalesced store.
-  // Otherwise (and on half tiles, where 80 registers per lane do not hold it) the Gram entries
-  // are staged and turned into values there.
+  // Otherwise (and on half tiles, where the 64 rows of a column's sum lie in two waves) the Gram
+  // entries are staged and turned into values there.
   float* tl = (float*)lds;
   float* snorm = tl + EPI * 4;
   uint32_t* misc = (uint32_t*)(snorm + 2 * TILE);  // ok[4], near[8], maxima[2]
@@ -930,7 +923,7 @@ k_gram_finish(const TestDesc* __restrict__ descs,
       }
       __syncthreads();
       float vm = 0.0f;  // one emit call site: the maxima combine afterwards
-      emit_half<true>(o, half, tl, vm);
+      emit_half(o, half, tl, vm);
       if (DUAL && out) vmax1 = fmaxf(vmax1, vm);
       else vmax0 = fmaxf(vmax0, vm);
     }

@@ -353,12 +353,11 @@ etest_status check_launch_sizes(const TestPlan* plans, size_t n) {
   return ETEST_OK;
 }
 
-// A split stream of more workgroups than the chip holds at once (8 per CU of MI355X's 256)
-// keeps every CU's vector ALU busy; there 32 splits per workgroup instead of 16 keep twice as
+// A split stream of more workgroups than the chip holds at once (MEMBER_WIDE_MIN_WG) keeps
+// every CU's vector ALU busy; there 32 splits per workgroup instead of 16 keep twice as
 // many lanes of each selection scan busy, and fewer, larger workgroups leave more room to
-// the memory-bound stages beside it (the batched workload of 256 tests: 6.53-6.60 ->
-// 6.36-6.37 ms per step).  Smaller streams keep 16: they are latency-bound walks, and
-// halving their workgroup count would leave CUs idle.
+// the memory-bound stages beside it.  Smaller streams keep 16: they are latency-bound walks,
+// and halving their workgroup count would leave CUs idle.
 etest_status build_batch(const etest_request* reqs, int64_t n, bool internal_perm, Batch* b) {
   b->plans.clear();
   b->member_wide = false;
@@ -610,7 +609,10 @@ void free_batch(Batch* b, hipStream_t st, bool stream_ordered) {
 // Split stream after the block stage once it has more workgroups than the chip holds at
 // once (8 per CU of MI355X's 256), or when the block stage runs on super tiles, whose
 // workgroups take a CU's LDS and register file whole and leave the split stream no room
-// beside them.  ETEST_SPLIT_LATE = 0 / 1 forces either order.
+// beside them.  Whole batches, forked first / after the block stage: 16 mixed tests (up to 1500 +
+// 1500 rows, 2000 splits; 2016 workgroups) 543 / 557 us, 64 1645 / 1647, 256 6280 / 6150; 2000 +
+// 2000 rows x 1000, 10000 splits 457 / 495, 40000 (1251 wide workgroups) 1256 / 1327.
+// ETEST_SPLIT_LATE = 0 / 1 forces either order.
 constexpr int64_t SPLIT_EARLY_MAX_WG = 8 * 256;
 static bool split_late(int64_t member_wg, int64_t super_wg) {
   static const int env = env_int("ETEST_SPLIT_LATE", -1, -1, 1);
@@ -723,8 +725,11 @@ static const Fork* thread_fork() {
 // and a wait on either stream, about 15 us of an eager pass and 8 us of a graph's, which a walk
 // over few tiles does not take.  Eager, 200 splits: 400 rows 109 us forked, 94 not; 1200 rows 115
 // and 112; 1600 rows 119 and 122 (10000 splits: 116 / 104, 156 / 155, 193 / 194).  As a graph: 400
-// rows 102 and 95, 800 rows 105 and 106, 1200 rows 109 and 114.  Split streams that follow the
-// block stage (split_late) are always forked.
+// rows 102 and 95, 800 rows 105 and 106, 1200 rows 109 and 114.  Graphs of several tests of at
+// most five tiles: 4 tests of 100 + 100 rows 97 forked, 87 not; 30 of them 117 and 117; but 16 of
+// 300 + 200 rows 127 and 134, 31 of 256 + 384 rows 174 and 184, 8 of 250 + 300 rows, 4000 splits
+// 147 and 155, which the line by tiles alone leaves in line.  Split streams that follow the block
+// stage (split_late) are always forked.
 constexpr int32_t FORK_MIN_TILES = 11, FORK_MIN_TILES_GRAPH = 6;
 const Fork* batch_fork(const Batch& b, bool graph) {
   int32_t nt = 0;
