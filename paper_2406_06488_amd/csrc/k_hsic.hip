@@ -230,8 +230,8 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 // half of the pairs' entries are never touched.  The products of two FP32 entries are exact
 // in FP64; a lane adds CH of a row's four, then adds such chains, and the wave its lanes, with
 // compensation (the three terms of the estimator cancel to a small fraction of their size), and
-// so are the waves' sums (part[b][slice][group]).  Bound by the gathers (random LDS banks) and,
-// in the FP32 form, as much by the vector ALU.
+// so are the waves' sums (part[b][slice][group]).  Bound by the vector ALU in the FP32 form (76%
+// busy, the gathers' random LDS banks 58%).
 //
 // FP32 form: S has one bit more than an FP32 value and no sign, so it is staged as 8 exponent
 // and 24 mantissa bits: bits 28..59 of the FP64 value S 2^-896, which two shifts restore.
@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(1024) k_hsic_sums(const TestDesc* __restrict__
 // 8 rows (a row of Lt staged for each of them, every entry read), 416 us in this form without
 // the reads one permutation ahead and with the pairs' ownership tested per entry, 201 us with it
 // tested row by row on the scalar unit, 155 us with them chosen over the lanes but every sum of a
-// wave by plain additions (LDS 65% busy, vector ALU 60%), 179 us now.  Whole tests, plain / now:
+// wave by plain additions (vector ALU 60% busy, LDS 65%), 179 us now.  Whole tests, plain / now:
 // that one 286 / 303 us, n = 4096 1000 / 1111 (1147 with the lanes' sums by ds_bpermute); FP64
 // form 1780 / 1795.  Four rows interleaved, so that one 16-byte read gathers them all: 314 us, 54
 // LDS cycles per read.
