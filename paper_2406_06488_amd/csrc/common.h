@@ -8,11 +8,12 @@
 //   nrm    [n_pad]          squared row norms of the staged rows
 //   D      [ntiles][T][T]   upper tiles (i <= j) of the pooled tile grid: XX upper
 //                           tiles, every XY tile, YY upper tiles -- never a YX tile
-//   tsum   [ntiles][2][T]   FP64 row / column sums of each stored tile
+//   tsum   [ntiles][3][T]   FP64 row sums and two half-tile column sums of each stored tile
+//                           (FP64 form [ntiles][6][T], in the plane region of a test that has one)
 //   rsum   [n_pad][2]       pooled row sums: same-sample part, cross-sample part
 //   planes [ntiles][S][T*T] double-centred tiles, scaled by a power of two and split
 //                           into fp16 planes (hi, lo * 2^11) in MFMA A-fragment
-//                           order (FP64 form: one FP64 row-major tile)
+//                           order (FP64 form: one FP64 tile in that order)
 //   Z      [n_pad/32][B_pad] split membership bits, word w of column c holds items
 //                           32w..32w+31; columns 0..B-1 drawn splits, column B the
 //                           identity split, the rest zero
